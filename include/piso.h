@@ -121,7 +121,14 @@ typedef enum {
                                iteration (2^d cells per aggregate inside each block, Galerkin
                                coarse operators, damped Jacobi smoothing).  The paper names
                                multigrid for the pressure as the way to a faster solver
-                               (Sec. 6, App. A.6); the converged solution is the same. */
+                               (Sec. 6, App. A.6); the converged solution is the same.
+                               On a single tensor-product block (walls or periodic sides,
+                               axes of at most 512 cells, uniform where periodic) the
+                               operator is close to one that 1D eigenbases diagonalise, and
+                               that exact inverse takes the V-cycle's place for every
+                               operator close enough to it (judged per solve, on the device;
+                               PISO_MG_LINE or PISO_ZMARCH set at piso_create keep the
+                               V-cycle). */
   PISO_PRECOND_ILU0 = 2,    /* velocity BiCGStab only: ILU(0) of C in red-black order (App. A.6
                                names ILU for BiCGStab).  Cells of one colour couple only to the
                                other colour, so the factors need no fill-in except on the

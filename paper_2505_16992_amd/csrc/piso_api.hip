@@ -489,8 +489,8 @@ int piso_create(const piso_domain_desc* desc, int32_t precision, piso_ctx** out)
   piso_ctx* c = new piso_ctx();
   c->N = topo.N;
   c->NB = topo.NB;
-  c->h_tab.swap(topo.tab);
-  c->h_fmap.swap(topo.fmap);
+  c->h_tab = topo.tab;
+  c->h_fmap = topo.fmap;
   c->ilu_ok = topo.ilu_ok;
   c->dim = desc->dim;
   c->nblocks = desc->n_blocks;
@@ -504,6 +504,7 @@ int piso_create(const piso_domain_desc* desc, int32_t precision, piso_ctx** out)
   if (!rc) rc = alloc_workspaces(c);
   if (!rc) rc = mg_build(c);
   if (!rc && !c->mg.empty()) rc = line_choose(c, desc);
+  if (!rc) rc = fdm_build(c, desc, topo);
   if (!rc) rc = outflow_build(c);
   if (rc) {
     g_create_error = c->err;

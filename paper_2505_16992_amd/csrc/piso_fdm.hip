@@ -1,0 +1,1086 @@
+// Fast-diagonalisation preconditioner of the pressure PCG on single tensor-product blocks
+// (plan and mathematics: piso_fdm_plan.h).  z = B r with one dense product per axis and
+// direction, and one tridiagonal system per mode along the line axis: GEMM-shaped work on
+// fields of N cells, done with the FP32 / FP64 matrix instructions (full precision of the
+// type, no narrower operands).
+//
+// What bounds it.  2 n flops per cell and product over two field streams: at n = 96 in FP32
+// that is 24 flop/B, about the ratio of the chip's 150 TFLOP/s of FP32 matrix rate to its
+// 5 TB/s, and a pass over a 96^3 field is a few microseconds either way, where the launch
+// counts as much.  So every product reads its operand once into LDS and the small basis
+// from the L2, and products are fused with what stands next to them:
+//   k_fdm_row, MODE 1   PCG update (alpha, x, r') and the forward product along x
+//   k_fdm_col, MODE 0   forward product along the remaining axis (3D)
+//   k_fdm_line          the tridiagonal systems; without a line axis (y and z periodic)
+//                       k_fdm_col, MODE 2: forward product, 1 / Lambda, inverse product
+//   k_fdm_col, MODE 1   inverse product along the remaining axis (3D)
+//   k_fdm_row, MODE 2   inverse product along x and the partial sums of r.z, r.r
+// An iteration is these and the stencil kernel: 4 launches in 2D and 6 in 3D, against 7 to
+// 11 with the multigrid V-cycle, and it needs 2 to 25 iterations where the V-cycle needs
+// 15 to 80 (the spectrum of B M lies within the spread of the ratios of the face weights of
+// M and M0).
+//
+// Tiles.  Matrix instructions of 16 x 16 outputs: the basis is the A operand, packed on the
+// host so that a lane's four consecutive k are one 16- or 32-byte load; the field tile is
+// the B operand, from LDS.  The order of k is the same in both, so any order will do: lane
+// group g takes k = k0 + 4 g + t for the t-th of four instructions.  A wave owns 16-row
+// output tiles over all columns of the work-group's field tile; where a field has too few
+// tiles to fill the chip (2D), several work-groups share a field tile and split its output
+// rows (`splits`).
+//
+// The constant mode.  M has it for its null space and the residual's sum is zero, but in FP32
+// the sum left by rounding is enough to stop the iteration from reaching 1e-7 (a 105 x 171
+// cavity went from 2e-7 to 1 and stayed there).  The kernel that meets the null mode knows
+// the residual's mean exactly; it leaves it in device memory, and the next kernels that read
+// the residual take it off (no pass of its own).
+//
+// Per operator (once a step for both correctors): k_fdm_stats and k_fdm_select compare its
+// face weights with each rung's, keep the plane means as the line systems' profiles and the
+// rung of the smallest spread in device memory (no read-back); a spread above kFdmMaxSpread
+// marks the operator as rejected, k_cg_check ends the solve before its first iteration and
+// the host runs it with multigrid.  k_fdm_factor then forms the pivots.
+#include <algorithm>
+#include <cstdlib>
+#include <new>
+#include <string>
+#include <vector>
+
+#include "piso_fdm_plan.h"
+#include "piso_impl.h"
+
+namespace piso {
+
+namespace {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+typedef double f64x2 __attribute__((ext_vector_type(2)));
+
+template <typename R>
+struct Vec4;
+template <>
+struct Vec4<float> {
+  using T = f32x4;
+};
+template <>
+struct Vec4<double> {
+  using T = f64x4;
+};
+
+__device__ __forceinline__ f32x4 mma(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+__device__ __forceinline__ f64x4 mma(double a, double b, f64x4 c) {
+  return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
+}
+
+// Row of the 16-row output tile in which register r of lane group g holds its result, and
+// its inverse, the packing order that makes that row 4 g + r in both types: the FP32
+// instruction returns row 4 g + r, the FP64 one row 4 r + g.
+template <typename R>
+constexpr int packed_row(int m) {
+  return sizeof(R) == 4 ? m : 4 * (m % 4) + m / 4;
+}
+
+constexpr int kFdmMaxWaves = 8;
+constexpr int kFdmPad = 4;   // LDS row padding: the 16 rows (row tiles) or the four k groups
+                             // (column tiles) of an operand read fall on different banks
+
+}  // namespace
+
+// ------------------------------------------------------------------- products along x
+
+template <typename R>
+struct FdmRow {
+  int n, rows, kc, mt, splits, mper, ntiles, ld;   // mper: output tiles per split
+  uint32_t div_lo, div_hi;                         // division by n (or n / 4)
+  int div_sh, quad;
+  const R* V;
+  size_t vstride;
+  const FdmSel* sel;   // rung and the mean of r
+  const R* in;         // MODE 0: r; MODE 1: r (before the update); MODE 2: transformed field
+  R* out;
+  R *x, *rout;         // MODE 1
+  const R *dnew, *q;
+  const R* r;          // MODE 2: residual for the partial sums
+  CgState* st;
+  const double* partA;
+  double* partB;
+  int Gp, par;
+};
+
+// Sum of G partials, the same in every thread of every work-group of the launch.
+__device__ __forceinline__ double fdm_partials(const double* __restrict__ part, int G, double* red) {
+  double v = 0.0;
+  for (int w0 = 0; w0 < G; w0 += 8 * (int)blockDim.x) {
+    double u[8];
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+      const int w = w0 + (int)threadIdx.x + c * (int)blockDim.x;
+      u[c] = w < G ? part[w] : 0.0;
+    }
+#pragma unroll
+    for (int c = 0; c < 8; ++c) v += u[c];
+  }
+  v = wave_sum(v);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
+  __syncthreads();
+  double t = 0.0;
+  for (int w = 0; w < (int)blockDim.x >> 6; ++w) t += red[w];
+  __syncthreads();
+  return t;
+}
+
+template <typename R>
+__device__ __forceinline__ typename Vec4<R>::T lds4(const R* p) {
+  typename Vec4<R>::T v;
+  if constexpr (sizeof(R) == 4) {
+    v = *reinterpret_cast<const f32x4*>(p);
+  } else {
+    const f64x2 a = *reinterpret_cast<const f64x2*>(p), b = *reinterpret_cast<const f64x2*>(p + 2);
+    v[0] = a[0];
+    v[1] = a[1];
+    v[2] = b[0];
+    v[3] = b[1];
+  }
+  return v;
+}
+
+template <typename R, int NT, int MODE>
+__global__ void __launch_bounds__(64 * kFdmMaxWaves) k_fdm_row(FdmRow<R> a) {
+  using V4 = typename Vec4<R>::T;
+  extern __shared__ __align__(32) char smem[];
+  __shared__ double red[2 * kFdmMaxWaves];
+  R* X = (R*)smem;   // [16 NT][ld]
+  const int done = a.st->done;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nth = blockDim.x;
+  const int g = lane >> 4, nl = lane & 15;
+  const uint64_t dm = (uint64_t)a.div_lo | ((uint64_t)a.div_hi << 32);
+  const int per_row = a.quad ? a.n >> 2 : a.n;
+  const int total = a.ntiles * a.splits;
+  R alpha = R(0);
+  if constexpr (MODE == 1) {
+    const double rzp = a.st->rz[a.par];
+    const double dq = fdm_partials(a.partA, a.Gp, red);
+    if (done) return;
+    if (!(dq > 0.0) || !std::isfinite(dq)) {
+      if (blockIdx.x == 0 && tid == 0) {
+        a.st->status = std::isfinite(dq) ? PISO_BREAKDOWN : PISO_E_NAN;
+        a.st->iters = a.st->k;
+        a.st->done = 1;
+      }
+      return;
+    }
+    alpha = (R)(rzp / dq);
+    if (blockIdx.x == 0 && tid == 0) a.st->k = a.st->k + 1;   // no other work-group reads it here
+  } else {
+    if (done) return;
+  }
+  const R* Vq = a.V + (size_t)a.sel->q * a.vstride;
+  const R mean = MODE == 0 ? R(0) : (R)a.sel->mean;
+  double acc_rz = 0.0, acc_rr = 0.0;
+  for (int lt = xcd_logical_group(); lt < total; lt += gridDim.x) {
+    const int tile = lt / a.splits, sp = lt % a.splits;
+    const int row0 = tile * 16 * NT;
+    const int rows = min(16 * NT, a.rows - row0);
+    const size_t base = (size_t)row0 * a.n;
+    // field tile into LDS (contiguous in memory); the first split also stores the update
+    for (int e = tid; e < rows * per_row; e += nth) {
+      const int r = (int)fast_div((uint32_t)e, dm, a.div_sh);
+      if (a.quad) {
+        const int c = (e - r * per_row) << 2;
+        const size_t P = base + (size_t)e * 4;
+        V4 v = *reinterpret_cast<const V4*>(a.in + P);
+        if constexpr (MODE == 1) {
+          const V4 qv = *reinterpret_cast<const V4*>(a.q + P);
+          const bool own = sp == 0;
+          V4 xv, dv;
+          if (own) {
+            xv = *reinterpret_cast<const V4*>(a.x + P);
+            dv = *reinterpret_cast<const V4*>(a.dnew + P);
+          }
+#pragma unroll
+          for (int t = 0; t < 4; ++t) v[t] = (v[t] - mean) - alpha * qv[t];
+          if (own) {
+#pragma unroll
+            for (int t = 0; t < 4; ++t) xv[t] += alpha * dv[t];
+            *reinterpret_cast<V4*>(a.x + P) = xv;
+            *reinterpret_cast<V4*>(a.rout + P) = v;
+          }
+        }
+        R* d = X + r * a.ld + c;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) d[t] = v[t];
+      } else {
+        const int c = e - r * per_row;
+        const size_t P = base + e;
+        R v = a.in[P];
+        if constexpr (MODE == 1) {
+          v = (v - mean) - alpha * a.q[P];
+          if (sp == 0) {
+            a.x[P] += alpha * a.dnew[P];
+            a.rout[P] = v;
+          }
+        }
+        X[r * a.ld + c] = v;
+      }
+    }
+    // zeros beyond the row's end and in missing rows (the packed basis is zero there too, but
+    // stale LDS may hold NaN)
+    const int tail = a.kc * 16 - a.n;
+    for (int e = tid; e < 16 * NT * tail; e += nth) X[(e / tail) * a.ld + a.n + e % tail] = R(0);
+    for (int e = tid; e < (16 * NT - rows) * a.n; e += nth) X[(rows + e / a.n) * a.ld + e % a.n] = R(0);
+    __syncthreads();
+    const int mend = min(a.mt, (sp + 1) * a.mper);
+    for (int mt = sp * a.mper + wave; mt < mend; mt += nth >> 6) {
+      V4 acc[NT];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[t] = V4{R(0), R(0), R(0), R(0)};
+      const R* vp = Vq + ((size_t)mt * a.kc * 64 + lane) * 4;
+#pragma unroll 4
+      for (int k = 0; k < a.kc; ++k) {
+        const V4 av = *reinterpret_cast<const V4*>(vp + (size_t)k * 256);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) {
+          const V4 bv = lds4<R>(X + (t * 16 + nl) * a.ld + k * 16 + 4 * g);
+#pragma unroll
+          for (int u = 0; u < 4; ++u) acc[t] = mma(av[u], bv[u], acc[t]);
+        }
+      }
+      const int col = mt * 16 + 4 * g;
+#pragma unroll
+      for (int t = 0; t < NT; ++t) {
+        const int r = t * 16 + nl;
+        if (r >= rows || col >= a.n) continue;
+        const size_t P = base + (size_t)r * a.n + col;
+        if (a.quad) {
+          *reinterpret_cast<V4*>(a.out + P) = acc[t];
+          if constexpr (MODE == 2) {
+            const V4 rv = *reinterpret_cast<const V4*>(a.r + P);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const double rp = (double)(rv[u] - mean);
+              acc_rz += rp * (double)acc[t][u];
+              acc_rr += rp * rp;
+            }
+          }
+        } else {
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            if (col + u >= a.n) continue;
+            a.out[P + u] = acc[t][u];
+            if constexpr (MODE == 2) {
+              const double rp = (double)(a.r[P + u] - mean);
+              acc_rz += rp * (double)acc[t][u];
+              acc_rr += rp * rp;
+            }
+          }
+        }
+      }
+    }
+    __syncthreads();   // before the next tile overwrites X
+  }
+  if constexpr (MODE == 2) {
+    const double s0 = wave_sum(acc_rz), s1 = wave_sum(acc_rr);
+    if (lane == 0) {
+      red[wave] = s0;
+      red[kFdmMaxWaves + wave] = s1;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      double t0 = 0.0, t1 = 0.0;
+      for (int w = 0; w < nth >> 6; ++w) {
+        t0 += red[w];
+        t1 += red[kFdmMaxWaves + w];
+      }
+      a.partB[blockIdx.x] = t0;
+      a.partB[gridDim.x + blockIdx.x] = t1;
+    }
+  }
+}
+
+// --------------------------------------------------------------- products along y or z
+
+template <typename R>
+struct FdmCol {
+  int n, kc, mt, splits, mper, ld;
+  int cols, ctiles;      // contiguous columns of one slab, tiles per slab
+  int slabs;
+  size_t sstride, rstride;   // cells between slabs, between rows
+  int quad;
+  const R *Vf, *Vi;
+  size_t vstride;
+  const R *lr, *lc, *ls;     // eigenvalues along the rows, the columns, the slabs (or null)
+  const double* ones;
+  FdmSel* sel;
+  const R* in;
+  R* out;
+  const CgState* st;
+};
+
+// MODE 0: forward; 1: inverse; 2: forward, 1 / Lambda, inverse; 3: forward, 1 / Lambda.
+template <typename R, int NT, int MODE>
+__global__ void __launch_bounds__(64 * kFdmMaxWaves) k_fdm_col(FdmCol<R> a) {
+  using V4 = typename Vec4<R>::T;
+  constexpr int TN = 16 * NT;
+  extern __shared__ __align__(32) char smem[];
+  R* X = (R*)smem;                       // [16 kc][ld]
+  R* Y = X + (size_t)a.kc * 16 * a.ld;   // MODE 2: [16 kc][ld]
+  if (a.st->done) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nth = blockDim.x;
+  const int g = lane >> 4, nl = lane & 15;
+  const int lt = xcd_logical_group();
+  const int sp = lt % a.splits, tile = lt / a.splits;
+  const int slab = tile / a.ctiles, c0 = (tile - slab * a.ctiles) * TN;
+  const size_t base = (size_t)slab * a.sstride + c0;
+  const int q = a.sel->q;
+  if (a.quad) {
+    for (int e = tid; e < a.kc * 16 * (TN / 4); e += nth) {
+      const int r = e / (TN / 4), c = (e % (TN / 4)) * 4;
+      V4 v = V4{R(0), R(0), R(0), R(0)};
+      if (r < a.n && c0 + c < a.cols) v = *reinterpret_cast<const V4*>(a.in + base + (size_t)r * a.rstride + c);
+      R* d = X + r * a.ld + c;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) d[t] = v[t];
+    }
+  } else {
+    for (int e = tid; e < a.kc * 16 * TN; e += nth) {
+      const int r = e / TN, c = e % TN;
+      X[r * a.ld + c] = r < a.n && c0 + c < a.cols ? a.in[base + (size_t)r * a.rstride + c] : R(0);
+    }
+  }
+  __syncthreads();
+  const R* Vq = (MODE == 1 ? a.Vi : a.Vf) + (size_t)q * a.vstride;
+  R lcol[NT] = {};
+  if constexpr (MODE >= 2) {
+    const R ls = a.ls ? a.ls[(size_t)q * a.slabs + slab] : R(0);
+#pragma unroll
+    for (int t = 0; t < NT; ++t) {
+      const int c = c0 + t * 16 + nl;
+      lcol[t] = ls + a.lc[(size_t)q * a.cols + (c < a.cols ? c : 0)];
+    }
+  }
+  const R* src = X;
+#pragma unroll
+  for (int pass = 0; pass < (MODE == 2 ? 2 : 1); ++pass) {
+    const int mend = min(a.mt, (sp + 1) * a.mper);
+    for (int mt = sp * a.mper + wave; mt < mend; mt += nth >> 6) {
+      V4 acc[NT];
+#pragma unroll
+      for (int t = 0; t < NT; ++t) acc[t] = V4{R(0), R(0), R(0), R(0)};
+      const R* vp = Vq + ((size_t)mt * a.kc * 64 + lane) * 4;
+#pragma unroll 4
+      for (int k = 0; k < a.kc; ++k) {
+        const V4 av = *reinterpret_cast<const V4*>(vp + (size_t)k * 256);
+        const R* xs = src + (size_t)(k * 16 + 4 * g) * a.ld + nl;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int t = 0; t < NT; ++t) acc[t] = mma(av[u], xs[u * a.ld + t * 16], acc[t]);
+      }
+      const int row = mt * 16 + 4 * g;
+      if constexpr (MODE >= 2) {
+        if (pass == 0) {
+          if (slab == 0 && c0 == 0 && mt == 0 && lane == 0) a.sel->mean = (double)acc[0][0] * a.ones[q];
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            const R lr = row + u < a.n ? a.lr[(size_t)q * a.n + row + u] : R(0);
+#pragma unroll
+            for (int t = 0; t < NT; ++t) {
+              const R l = lr + lcol[t];
+              acc[t][u] = row + u < a.n && l > R(0) ? acc[t][u] / l : R(0);   // the null mode is left out
+            }
+          }
+        }
+      }
+      if (MODE == 2 && pass == 0) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+#pragma unroll
+          for (int t = 0; t < NT; ++t) Y[(row + u) * a.ld + t * 16 + nl] = acc[t][u];
+      } else {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          if (row + u >= a.n) continue;
+          R* o = a.out + base + (size_t)(row + u) * a.rstride;
+#pragma unroll
+          for (int t = 0; t < NT; ++t)
+            if (c0 + t * 16 + nl < a.cols) o[t * 16 + nl] = acc[t][u];
+        }
+      }
+    }
+    if (MODE == 2 && pass == 0) {
+      __syncthreads();
+      src = Y;
+      Vq = a.Vi + (size_t)q * a.vstride;
+    }
+  }
+}
+
+// ------------------------------------------------------------ tridiagonal line systems
+
+// Per mode (c, slab) of the other two axes the rows of [K + diag(lc c_x + ls c_s)] w = h, K
+// the stiffness of the couplings k.  Factorised from both ends to the middle row m = n / 2
+// (two lanes a column, half the chain of dependent steps), every step a sum of positive
+// terms: with e the row's excess over its open coupling,
+//   top:    e_j = q_j + k_{j-1} e_{j-1} / p_{j-1},  p_j = k_j + e_j
+//   bottom: e_j = q_j + k_j e_{j+1} / p_{j+1},      p_j = k_{j-1} + e_j
+//   middle: p_m = q_m + both neighbours' terms,
+// so that the smallest pivots (smooth modes) keep their relative accuracy in FP32 fields.
+// The null mode (q = 0) is pinned at the middle row; its right-hand side and its solution are
+// freed of their means.
+template <typename R>
+struct FdmLine {
+  int n, cols, slabs;
+  size_t sstride, rstride;
+  const R *lc, *ls;      // [rung][cols], [rung][slabs] (or null)
+  const double *k, *cx, *cs;   // profiles along the line: couplings, weights of lc and of ls
+  const double* ones;
+  FdmSel* sel;
+  R* piv;
+  const R* in;
+  R* out;
+  const CgState* st;
+};
+
+template <typename R>
+__global__ void __launch_bounds__(64) k_fdm_factor(FdmLine<R> a) {
+  if (a.sel->bad) return;
+  const int lane = threadIdx.x, half = lane >> 5;
+  const int per = (a.cols + 31) / 32;
+  const int slab = blockIdx.x / per, c0 = (blockIdx.x - slab * per) * 32 + (lane & 31);
+  const bool on = c0 < a.cols;
+  const int c = on ? c0 : a.cols - 1;
+  const int q = a.sel->q, n = a.n, m = n / 2;
+  const double lx = (double)a.lc[(size_t)q * a.cols + c];
+  const double ls = a.ls ? (double)a.ls[(size_t)q * a.slabs + slab] : 0.0;
+  R* piv = a.piv + (size_t)slab * a.sstride + c;
+  auto diag = [&](int j) { return lx * a.cx[j] + (a.ls ? ls * a.cs[j] : 0.0); };
+  // rows 0 .. m - 1 downward (half 0), n - 1 .. m + 1 upward (half 1)
+  const int steps = half ? n - 1 - m : m;
+  double carry = 0.0;   // k e / p of the row before
+  for (int t = 0; t < steps; ++t) {
+    const int j = half ? n - 1 - t : t;
+    const double open = a.k[half ? j - 1 : j];
+    const double e = diag(j) + carry;
+    const double p = open + e;
+    carry = open * e / p;
+    if (on) piv[(size_t)j * a.rstride] = (R)(1.0 / p);
+  }
+  const double other = __shfl_xor(carry, 32, 64);
+  if (half == 0 && on) {
+    double p = diag(m) + (carry + other);
+    if (!(p > 0.0)) p = n > 1 ? (m > 0 ? a.k[m - 1] : 0.0) + (m + 1 < n ? a.k[m] : 0.0) : 0.0;
+    piv[(size_t)m * a.rstride] = p > 0.0 ? (R)(1.0 / p) : R(0);
+  }
+}
+
+// The solve: a tile of TN columns goes to LDS with all its waves' loads in flight, one wave
+// runs the recurrences (one FMA a row and direction, its factor k / p formed off the
+// chain), and all write the result.
+template <typename R, int TN>
+__global__ void __launch_bounds__(kWG) k_fdm_line(FdmLine<R> a) {
+  extern __shared__ __align__(32) char smem[];
+  constexpr int ld = TN + 1;
+  const int n = a.n;
+  R* X = (R*)smem;            // [n][ld] right-hand side, then the solution
+  R* I = X + (size_t)n * ld;  // [n][ld] reciprocal pivots
+  R* K = I + (size_t)n * ld;  // [n] couplings
+  if (a.st->done) return;
+  const int per = (a.cols + TN - 1) / TN;
+  const int tile = xcd_logical_group(), slab = tile / per, c0 = (tile - slab * per) * TN;
+  const size_t base = (size_t)slab * a.sstride + c0;
+  const int w = min(TN, a.cols - c0);
+  constexpr int U = 4;
+  for (int e0 = threadIdx.x; e0 < n * TN; e0 += U * kWG) {
+    R xv[U], iv[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = e0 + u * kWG, j = e / TN, c = e % TN;
+      const bool on = j < n && c < w;
+      const size_t P = on ? base + (size_t)j * a.rstride + c : base;
+      xv[u] = a.in[P];
+      iv[u] = a.piv[P];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = e0 + u * kWG, j = e / TN, c = e % TN;
+      if (j >= n) continue;
+      X[j * ld + c] = xv[u];
+      I[j * ld + c] = iv[u];
+    }
+  }
+  for (int j = threadIdx.x; j < n; j += kWG) K[j] = (R)a.k[j];
+  __syncthreads();
+  const bool null = slab == 0 && c0 == 0;   // column 0 of this tile is the null mode
+  auto column_mean = [&]() {                // off column 0, by the first wave
+    double t = 0.0;
+    for (int j = threadIdx.x; j < n; j += 64) t += (double)X[j * ld];
+    t = wave_sum(t);
+    for (int j = threadIdx.x; j < n; j += 64) X[j * ld] -= (R)(t / n);
+    return t;
+  };
+  if (null && threadIdx.x < 64) {
+    const double t = column_mean();
+    if (threadIdx.x == 0) a.sel->mean = t * a.ones[a.sel->q];
+  }
+  if (threadIdx.x < 2 * TN) {
+    const int half = threadIdx.x / TN, c = threadIdx.x % TN;
+    const int m = n / 2, steps = half ? n - 1 - m : m;
+    R d = R(0), f = R(0);   // value and factor k / p of the row before
+#pragma unroll 4
+    for (int t = 0; t < steps; ++t) {
+      const int j = half ? n - 1 - t : t;
+      d = X[j * ld + c] + f * d;
+      f = K[half ? j - 1 : j] * I[j * ld + c];
+      X[j * ld + c] = d;
+    }
+    const R mine = f * d;
+    const R other = __shfl_xor(mine, TN, 64);
+    R x = (X[m * ld + c] + (half ? other + mine : mine + other)) * I[m * ld + c];
+    if (half == 0) X[m * ld + c] = x;
+#pragma unroll 4
+    for (int t = steps - 1; t >= 0; --t) {
+      const int j = half ? n - 1 - t : t;
+      const R iv = I[j * ld + c];
+      x = X[j * ld + c] * iv + (K[half ? j - 1 : j] * iv) * x;
+      X[j * ld + c] = x;
+    }
+  }
+  if (null && threadIdx.x < 64) column_mean();
+  __syncthreads();
+  for (int e = threadIdx.x; e < n * TN; e += kWG) {
+    const int j = e / TN, c = e % TN;
+    if (c < w) a.out[base + (size_t)j * a.rstride + c] = X[j * ld + c];
+  }
+}
+
+// ------------------------------------------------------ profiles and choice of a rung
+
+template <typename R>
+struct FdmStats {
+  int dim, rungs, pa, oa, splits;   // planes normal to pa; oa: the other axis of their rows
+  int n[3], wrap[3];
+  size_t stride[3];
+  size_t N;
+  const R* wt[3][3];   // [j][m]: [rung][n_m]
+};
+constexpr int kFdmStatValues = 3 * 3;   // per rung: term, then smallest, largest, sum
+
+// Smallest, largest and sum of the ratios of the operator's face weights to each rung's over
+// the planes normal to pa, `splits` work-groups a plane.  A weight that is not positive or
+// not finite gives an infinite spread.  One read of P_f, once per operator.
+template <typename R>
+__global__ void __launch_bounds__(kWG) k_fdm_stats(FdmStats<R> a, const R* __restrict__ Pf, float* __restrict__ out) {
+  __shared__ float sh[kFdmRungs * kFdmStatValues][kWaves];
+  float lo[kFdmRungs][3], hi[kFdmRungs][3], sum[kFdmRungs][3];
+#pragma unroll
+  for (int q = 0; q < kFdmRungs; ++q)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      lo[q][j] = INFINITY;
+      hi[q][j] = sum[q][j] = 0.f;
+    }
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lg = xcd_logical_group(), plane = lg / a.splits, sp = lg % a.splits;
+  const int nx = a.n[0], segs = (nx + 63) / 64, rows = a.n[a.oa];
+  for (int w = sp * kWaves + wave; w < rows * segs; w += a.splits * kWaves) {
+    const int o = w / segs, i = (w - o * segs) * 64 + lane;
+    if (i >= nx) continue;
+    const size_t P = (size_t)plane * a.stride[a.pa] + (size_t)o * a.stride[a.oa] + i;
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      if (j >= a.dim) continue;
+      const int pos = j == 0 ? i : (j == a.pa ? plane : o);
+      if (pos + 1 >= a.n[j] && !a.wrap[j]) continue;
+      const R p = Pf[(size_t)j * a.N + P];
+#pragma unroll
+      for (int q = 0; q < kFdmRungs; ++q) {
+        if (q >= a.rungs) continue;
+        R m = a.wt[j][0][q * nx + i] * a.wt[j][a.pa][q * a.n[a.pa] + plane];
+        if (a.dim == 3) m *= a.wt[j][a.oa][q * rows + o];
+        const float v = (float)(p / m);
+        const bool ok = v > 0.f && std::isfinite(v);
+        lo[q][j] = ok ? fminf(lo[q][j], v) : 0.f;
+        hi[q][j] = ok ? fmaxf(hi[q][j], v) : INFINITY;
+        sum[q][j] += v;
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < kFdmRungs; ++q)
+#pragma unroll
+    for (int j = 0; j < 3; ++j) {
+      if (q >= a.rungs) continue;
+#pragma unroll
+      for (int s = 32; s > 0; s >>= 1) {
+        lo[q][j] = fminf(lo[q][j], __shfl_xor(lo[q][j], s, 64));
+        hi[q][j] = fmaxf(hi[q][j], __shfl_xor(hi[q][j], s, 64));
+        sum[q][j] += __shfl_xor(sum[q][j], s, 64);
+      }
+      if (lane == 0) {
+        float(*v)[kWaves] = &sh[q * kFdmStatValues + 3 * j];
+        v[0][wave] = lo[q][j];
+        v[1][wave] = hi[q][j];
+        v[2][wave] = sum[q][j];
+      }
+    }
+  __syncthreads();
+  const int v = threadIdx.x;
+  if (v < a.rungs * kFdmStatValues) {
+    float t = sh[v][0];
+    for (int w = 1; w < kWaves; ++w) t = v % 3 == 0 ? fminf(t, sh[v][w]) : (v % 3 == 1 ? fmaxf(t, sh[v][w]) : t + sh[v][w]);
+    out[(size_t)v * gridDim.x + lg] = t;
+  }
+}
+
+// Rung of the smallest spread over all faces (relative to the plane means along a line axis),
+// and the means as that rung's profiles: prof[0] couplings along the line, prof[1] weights of
+// the x term, prof[2] weights of the third term.  One work-group.
+__global__ void __launch_bounds__(kWG)
+k_fdm_select(const float* __restrict__ st, int planes, int splits, int rungs, int dim, int pa, int line,
+             int3 faces, int last_open, float limit, double* __restrict__ prof, FdmSel* sel) {
+  __shared__ float slo[kFdmRungs][kWaves], shi[kFdmRungs][kWaves];
+  __shared__ int best;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const size_t G = (size_t)planes * splits;
+  auto of = [&](int q, int j, int v, int pl) {
+    const float* p = st + (size_t)(q * kFdmStatValues + 3 * j + v) * G + (size_t)pl * splits;
+    float t = p[0];
+    for (int s = 1; s < splits; ++s) t = v == 0 ? fminf(t, p[s]) : (v == 1 ? fmaxf(t, p[s]) : t + p[s]);
+    return t;
+  };
+  auto count = [&](int j, int pl) {
+    if (j == pa && last_open && pl + 1 == planes) return 0;
+    return j == 0 ? faces.x : (j == 1 ? faces.y : faces.z);
+  };
+  for (int q = 0; q < rungs; ++q) {
+    float lo = INFINITY, hi = 0.f;
+    for (int pl = threadIdx.x; pl < planes; pl += kWG)
+      for (int j = 0; j < dim; ++j) {
+        const int cnt = count(j, pl);
+        if (cnt == 0) continue;
+        const float mean = line ? of(q, j, 2, pl) / (float)cnt : 1.f;
+        const float l = of(q, j, 0, pl) / mean, h = of(q, j, 1, pl) / mean;
+        lo = l > 0.f ? fminf(lo, l) : 0.f;     // also 0 where the mean is infinite or NaN
+        hi = h > 0.f ? fmaxf(hi, h) : INFINITY;
+      }
+#pragma unroll
+    for (int s = 32; s > 0; s >>= 1) {
+      lo = fminf(lo, __shfl_xor(lo, s, 64));
+      hi = fmaxf(hi, __shfl_xor(hi, s, 64));
+    }
+    if (lane == 0) {
+      slo[q][wave] = lo;
+      shi[q][wave] = hi;
+    }
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    float top = INFINITY;
+    int bq = 0;
+    for (int q = 0; q < rungs; ++q) {
+      float lo = slo[q][0], hi = shi[q][0];
+      for (int w = 1; w < kWaves; ++w) {
+        lo = fminf(lo, slo[q][w]);
+        hi = fmaxf(hi, shi[q][w]);
+      }
+      const float spread = lo > 0.f ? hi / lo : INFINITY;
+      if (spread < top) {
+        top = spread;
+        bq = q;
+      }
+    }
+    sel->q = best = bq;
+    sel->kappa = top;
+    sel->bad = top <= limit ? 0 : 1;
+  }
+  __syncthreads();
+  if (!line) return;
+  for (int pl = threadIdx.x; pl < planes; pl += kWG)
+    for (int j = 0; j < dim; ++j) {
+      const int cnt = count(j, pl);
+      const int slot = j == pa ? 0 : (j == 0 ? 1 : 2);
+      prof[(size_t)slot * planes + pl] = cnt ? (double)of(best, j, 2, pl) / cnt : 0.0;
+    }
+}
+
+// ------------------------------------------------------------------------- host side
+
+namespace {
+
+// V (or its transpose) of every rung in operand order, zero-padded to multiples of 16.
+template <typename R>
+std::vector<R> pack(const FdmPlan& p, int m, bool fwd) {
+  const int n = p.n[m], T = (n + 15) / 16;
+  std::vector<R> out((size_t)p.rungs * T * T * 256, R(0));
+  for (int q = 0; q < p.rungs; ++q)
+    for (int mt = 0; mt < T; ++mt)
+      for (int kc = 0; kc < T; ++kc)
+        for (int lane = 0; lane < 64; ++lane)
+          for (int t = 0; t < 4; ++t) {
+            const int o = mt * 16 + packed_row<R>(lane % 16), k = kc * 16 + 4 * (lane / 16) + t;
+            if (o >= n || k >= n) continue;
+            const size_t row = fwd ? k : o, col = fwd ? o : k;
+            out[((((size_t)q * T + mt) * T + kc) * 64 + lane) * 4 + t] =
+                (R)p.V[m][((size_t)q * n + row) * n + col];
+          }
+  return out;
+}
+
+template <typename R>
+std::vector<R> narrow(const std::vector<double>& v) {
+  return std::vector<R>(v.begin(), v.end());
+}
+
+template <typename R>
+int upload_plan(piso_ctx* c, const FdmPlan& p) {
+  FdmState& f = c->fdm;
+  for (int m = 0; m < p.dim; ++m) {
+    if (m != p.line) {
+      if (int rc = upload(c, &f.fwd[m], pack<R>(p, m, true))) return rc;
+      if (int rc = upload(c, &f.inv[m], pack<R>(p, m, false))) return rc;
+      if (int rc = upload(c, &f.lam[m], narrow<R>(p.lam[m]))) return rc;
+    }
+    for (int j = 0; j < p.dim; ++j)
+      if (int rc = upload(c, &f.wt[j][m], narrow<R>(p.wt[j][m]))) return rc;
+  }
+  std::vector<double> ones(p.rungs, 1.0 / c->N);
+  for (int m = 0; m < p.dim; ++m)
+    for (int q = 0; q < p.rungs && m != p.line; ++q) ones[q] /= p.V[m][(size_t)q * p.n[m] * p.n[m]];
+  if (int rc = upload(c, (void**)&f.ones, ones)) return rc;
+  if (p.line >= 0)
+    if (int rc = dev_alloc(c, &f.piv, (size_t)c->N * sizeof(R))) return rc;
+  return dev_alloc(c, &f.hat, (size_t)c->N * sizeof(R));
+}
+
+// Columns per field tile (16 NT), work-groups sharing a tile and waves per work-group for an
+// axis of mt output tiles and `units` columns or rows.  Wide tiles reuse a basis operand for
+// several instructions; narrow ones and splits keep about two work-groups per CU in flight.
+struct Shape {
+  int nt, splits, mper, waves;
+};
+Shape shape_for(long units, int mt, int max_nt, bool may_split) {
+  Shape s;
+  s.nt = 1;
+  while (s.nt < max_nt && units / (16L * s.nt * 2) >= 512) s.nt *= 2;
+  const long tiles = (units + 16L * s.nt - 1) / (16L * s.nt);
+  s.splits = 1;
+  if (may_split)
+    while (tiles * s.splits < 256 && (mt + 2 * s.splits - 1) / (2 * s.splits) >= 2) s.splits *= 2;
+  s.mper = (mt + s.splits - 1) / s.splits;
+  s.splits = (mt + s.mper - 1) / s.mper;
+  // as many waves as divide the output tiles evenly, at least 4 for the loads
+  const int trips = (s.mper + kFdmMaxWaves - 1) / kFdmMaxWaves;
+  s.waves = std::max(4, (s.mper + trips - 1) / trips);
+  return s;
+}
+
+// LDS of a column tile; MODE 2 holds two
+template <typename R>
+size_t col_lds(int n, int nt, bool fused) {
+  return (size_t)((n + 15) / 16 * 16) * (16 * nt + kFdmPad) * sizeof(R) * (fused ? 2 : 1);
+}
+constexpr size_t kFdmLds = 150 * 1024;
+
+template <typename R, int MODE>
+void launch_row(piso_ctx* c, hipStream_t s, int kind, FdmRow<R> a, const Shape& sh, int G) {
+  const size_t lds = (size_t)16 * sh.nt * a.ld * sizeof(R);
+  const int wg = 64 * sh.waves;
+  if (sh.nt == 1) launch_timed_lds(c, s, kind, k_fdm_row<R, 1, MODE>, G, wg, lds, a);
+  else if (sh.nt == 2) launch_timed_lds(c, s, kind, k_fdm_row<R, 2, MODE>, G, wg, lds, a);
+  else launch_timed_lds(c, s, kind, k_fdm_row<R, 4, MODE>, G, wg, lds, a);
+}
+
+template <typename R, int MODE>
+void launch_col(piso_ctx* c, hipStream_t s, FdmCol<R> a, const Shape& sh) {
+  a.ld = 16 * sh.nt + kFdmPad;
+  a.splits = sh.splits;
+  a.mper = sh.mper;
+  a.ctiles = (a.cols + 16 * sh.nt - 1) / (16 * sh.nt);
+  const size_t lds = col_lds<R>(a.n, sh.nt, MODE == 2);
+  const int G = a.slabs * a.ctiles * a.splits, wg = 64 * sh.waves;
+  if (sh.nt == 1) launch_timed_lds(c, s, kTimeMgCoarse, k_fdm_col<R, 1, MODE>, G, wg, lds, a);
+  else if (sh.nt == 2) launch_timed_lds(c, s, kTimeMgCoarse, k_fdm_col<R, 2, MODE>, G, wg, lds, a);
+  else launch_timed_lds(c, s, kTimeMgCoarse, k_fdm_col<R, 4, MODE>, G, wg, lds, a);
+}
+
+template <typename R>
+Shape row_shape(const piso_ctx* c) {
+  const int nx = c->fdm.n[0];
+  const int max_nt = nx * sizeof(R) <= 1024 ? 4 : 2;   // tile within half the LDS
+  return shape_for((long)c->N / nx, (nx + 15) / 16, max_nt, true);
+}
+
+template <typename R>
+int row_tiles(const piso_ctx* c, const Shape& sh) {
+  const int rows = c->N / c->fdm.n[0];
+  return (rows + 16 * sh.nt - 1) / (16 * sh.nt) * sh.splits;
+}
+
+int fdm_check(piso_ctx* c) {
+  const hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return fail(c, PISO_E_HIP, std::string("k_fdm: ") + hipGetErrorString(e));
+  return PISO_OK;
+}
+
+template <typename R>
+FdmRow<R> row_args(piso_ctx* c, const Shape& sh, CgState* st) {
+  const FdmState& f = c->fdm;
+  FdmRow<R> a{};
+  a.n = f.n[0];
+  a.rows = c->N / a.n;
+  a.kc = a.mt = (a.n + 15) / 16;
+  a.splits = sh.splits;
+  a.mper = sh.mper;
+  a.ntiles = (a.rows + 16 * sh.nt - 1) / (16 * sh.nt);
+  a.ld = a.kc * 16 + kFdmPad;
+  a.quad = a.n % 4 == 0;
+  div_magic((uint32_t)(a.quad ? a.n / 4 : a.n), a.div_lo, a.div_hi, a.div_sh);
+  a.vstride = (size_t)a.mt * a.kc * 256;
+  a.sel = f.sel;
+  a.st = st;
+  return a;
+}
+
+// Arguments of the line kernels: columns along x, slabs along the remaining axis.
+template <typename R>
+FdmLine<R> line_args(piso_ctx* c) {
+  const FdmState& f = c->fdm;
+  const bool d3 = c->dim == 3;
+  const int la = f.line, oa = la == 1 ? 2 : 1;
+  FdmLine<R> a{};
+  a.n = f.n[la];
+  a.cols = f.n[0];
+  a.slabs = f.n[oa];   // 1 in 2D
+  a.rstride = la == 1 ? f.n[0] : (size_t)f.n[0] * f.n[1];
+  a.sstride = la == 1 ? (size_t)f.n[0] * f.n[1] : f.n[0];
+  a.lc = (const R*)f.lam[0];
+  a.ls = d3 ? (const R*)f.lam[oa] : nullptr;
+  a.ones = f.ones;
+  a.k = f.prof;
+  a.cx = f.prof + f.planes;
+  a.cs = f.prof + 2 * (size_t)f.planes;
+  a.sel = f.sel;
+  a.piv = (R*)f.piv;
+  return a;
+}
+
+// 32 columns a tile (whole 128-byte lines in FP32), 16 where the chip would not fill or two
+// tiles of the line do not fit the LDS
+template <typename R>
+int line_cols(const FdmLine<R>& a) {
+  const bool fits = ((size_t)a.n * 2 * 33 + a.n) * sizeof(R) <= kFdmLds;
+  return fits && (long)a.slabs * ((a.cols + 31) / 32) >= 128 ? 32 : 16;
+}
+
+// The products and solves between the two products along x: transformed field in c->k_y,
+// result in *res.
+template <typename R>
+int middle(piso_ctx* c, hipStream_t s, CgState* st, R** res) {
+  const FdmState& f = c->fdm;
+  const bool d3 = c->dim == 3;
+  const int nx = f.n[0], ny = f.n[1], nz = f.n[2];
+  R *u = (R*)c->k_y, *v = (R*)f.hat;
+  FdmCol<R> a{};
+  a.quad = nx % 4 == 0;
+  a.sel = f.sel;
+  a.st = st;
+  auto along = [&](int m) {
+    a.n = f.n[m];
+    a.kc = a.mt = (a.n + 15) / 16;
+    a.vstride = (size_t)a.mt * a.kc * 256;
+    a.Vf = (const R*)f.fwd[m];
+    a.Vi = (const R*)f.inv[m];
+    a.rstride = m == 1 ? nx : (size_t)nx * ny;
+    a.cols = m == 1 ? nx : nx * ny;
+    a.slabs = m == 1 ? nz : 1;
+    a.sstride = (size_t)nx * ny;
+  };
+  auto step = [&](auto mode, const Shape& sh) {
+    a.in = u;
+    a.out = v;
+    launch_col<R, decltype(mode)::value>(c, s, a, sh);
+    std::swap(u, v);
+  };
+  // 3D: the axis between x and the line (z, or y where the lines run along z)
+  const int ma = f.line == 2 ? 1 : 2;
+  Shape shm{};
+  if (d3) {
+    along(ma);
+    const int max_nt =
+        col_lds<R>(a.n, 4, false) <= kFdmLds / 2 ? 4 : (col_lds<R>(a.n, 2, false) <= kFdmLds / 2 ? 2 : 1);
+    shm = shape_for((long)a.cols * a.slabs, a.mt, max_nt, true);
+    step(std::integral_constant<int, 0>{}, shm);
+  }
+  if (f.line >= 0) {
+    FdmLine<R> l = line_args<R>(c);
+    l.in = u;
+    l.out = v;
+    l.st = st;
+    const int tn = line_cols(l);
+    const size_t lds = ((size_t)l.n * 2 * (tn + 1) + l.n) * sizeof(R);
+    const int G = l.slabs * ((l.cols + tn - 1) / tn);
+    if (tn == 32) launch_timed_lds(c, s, kTimeMgCoarse, k_fdm_line<R, 32>, G, kWG, lds, l);
+    else launch_timed_lds(c, s, kTimeMgCoarse, k_fdm_line<R, 16>, G, kWG, lds, l);
+    std::swap(u, v);
+  } else {
+    along(1);
+    a.lr = (const R*)f.lam[1];
+    a.lc = (const R*)f.lam[0];
+    a.ls = d3 ? (const R*)f.lam[2] : nullptr;
+    a.ones = f.ones;
+    // one kernel for both products and the scaling between them where its tiles fill the
+    // chip (or the axis is short), else the output rows of each are split over work-groups:
+    // a 2D 256^2 grid has 16 tiles of 16 columns
+    const int max_nt = col_lds<R>(ny, 2, true) <= kFdmLds / 2 ? 2 : 1;
+    const Shape shf = shape_for((long)nx * nz, a.mt, max_nt, false);
+    const long tiles = (long)nz * ((nx + 16 * shf.nt - 1) / (16 * shf.nt));
+    if (col_lds<R>(ny, shf.nt, true) <= kFdmLds && (tiles >= 96 || a.mt <= 4)) {
+      step(std::integral_constant<int, 2>{}, shf);
+    } else {
+      const Shape sh = shape_for((long)nx * nz, a.mt, col_lds<R>(ny, 4, false) <= kFdmLds / 2 ? 4 : 1, true);
+      step(std::integral_constant<int, 3>{}, sh);
+      step(std::integral_constant<int, 1>{}, sh);
+    }
+  }
+  if (d3) {
+    along(ma);
+    step(std::integral_constant<int, 1>{}, shm);
+  }
+  *res = u;
+  return fdm_check(c);
+}
+
+template <typename R>
+int finish(piso_ctx* c, hipStream_t s, const R* r, R* z, CgState* st, double* partB) {
+  R* hat = nullptr;
+  if (int rc = middle<R>(c, s, st, &hat)) return rc;
+  const Shape sh = row_shape<R>(c);
+  FdmRow<R> a = row_args<R>(c, sh, st);
+  a.V = (const R*)c->fdm.inv[0];
+  a.in = hat;
+  a.out = z;
+  a.r = r;
+  a.partB = partB;
+  launch_row<R, 2>(c, s, kTimeMgUp0, a, sh, fdm_groups<R>(c));
+  return fdm_check(c);
+}
+
+}  // namespace
+
+int fdm_build(piso_ctx* c, const piso_domain_desc* desc, const Topology& topo) {
+  // a multigrid form asked for by name keeps the multigrid (PISO_MG_LINE and PISO_ZMARCH
+  // choose its fine-level kernels)
+  if (c->mg.empty() || std::getenv("PISO_MG_LINE") || std::getenv("PISO_ZMARCH")) return PISO_OK;
+  if (c->dim == 3 && c->N < kFdmMinCells3) return PISO_OK;
+  FdmPlan p;
+  try {
+    fdm_plan(desc, topo, &p);
+    if (!p.on) return PISO_OK;
+    FdmState& f = c->fdm;
+    f.rungs = p.rungs;
+    f.line = p.line;
+    for (int m = 0; m < 3; ++m) {
+      f.n[m] = p.n[m];
+      f.wrap[m] = p.wrap[m];
+    }
+    if (int rc = c->prec == PISO_F64 ? upload_plan<double>(c, p) : upload_plan<float>(c, p)) return rc;
+    // statistics: up to about 512 work-groups, at least a row segment per wave
+    const int pa = f.line == 2 ? 2 : 1, oa = pa == 1 ? 2 : 1;
+    f.planes = f.n[pa];
+    const int units = f.n[oa] * ((f.n[0] + 63) / 64);
+    f.splits = std::max(1, std::min(512 / f.planes, (units + kWaves - 1) / kWaves));
+    if (int rc = dev_alloc(c, (void**)&f.stats,
+                           sizeof(float) * kFdmRungs * kFdmStatValues * (size_t)f.planes * f.splits))
+      return rc;
+    if (int rc = dev_alloc(c, (void**)&f.prof, sizeof(double) * 3 * (size_t)f.planes)) return rc;
+    if (int rc = dev_alloc(c, (void**)&f.sel, sizeof(FdmSel))) return rc;
+    PISO_HIP(c, hipMemset(f.sel, 0, sizeof(FdmSel)));
+    f.on = true;
+  } catch (const std::bad_alloc&) {
+    return fail(c, PISO_E_OOM, "fast diagonalisation: host memory");
+  }
+  return PISO_OK;
+}
+
+template <typename R>
+int fdm_groups(const piso_ctx* c) {
+  return std::min(row_tiles<R>(c, row_shape<R>(c)), kRedGrid);
+}
+
+template <typename R>
+int fdm_setup(piso_ctx* c, hipStream_t s, const R* Pf) {
+  const FdmState& f = c->fdm;
+  FdmStats<R> a{};
+  a.dim = c->dim;
+  a.N = c->N;
+  a.rungs = f.rungs;
+  a.pa = f.line == 2 ? 2 : 1;
+  a.oa = a.pa == 1 ? 2 : 1;
+  a.splits = f.splits;
+  a.stride[0] = 1;
+  a.stride[1] = f.n[0];
+  a.stride[2] = (size_t)f.n[0] * f.n[1];
+  int3 faces;
+  int* nf[3] = {&faces.x, &faces.y, &faces.z};
+  for (int m = 0; m < 3; ++m) {
+    a.n[m] = f.n[m];
+    a.wrap[m] = f.wrap[m];
+    for (int j = 0; j < 3; ++j) a.wt[j][m] = (const R*)f.wt[j][m];
+    const int cells = c->N / f.n[a.pa];   // of a plane
+    *nf[m] = m == a.pa || f.wrap[m] ? cells : cells / f.n[m] * (f.n[m] - 1);
+  }
+  k_fdm_stats<R><<<f.planes * f.splits, kWG, 0, s>>>(a, Pf, f.stats);
+  k_fdm_select<<<1, kWG, 0, s>>>(f.stats, f.planes, f.splits, f.rungs, c->dim, a.pa, f.line >= 0 ? 1 : 0, faces,
+                                 f.wrap[a.pa] ? 0 : 1, kFdmMaxSpread, f.prof, f.sel);
+  if (f.line >= 0) {
+    const FdmLine<R> l = line_args<R>(c);
+    k_fdm_factor<R><<<l.slabs * ((l.cols + 31) / 32), 64, 0, s>>>(l);
+  }
+  return fdm_check(c);
+}
+
+const int* fdm_rejected(const piso_ctx* c) { return &c->fdm.sel->bad; }
+
+template <typename R>
+int fdm_apply(piso_ctx* c, hipStream_t s, const R* r, R* z, CgState* st, double* partB) {
+  const Shape sh = row_shape<R>(c);
+  FdmRow<R> a = row_args<R>(c, sh, st);
+  a.V = (const R*)c->fdm.fwd[0];
+  a.in = r;
+  a.out = (R*)c->k_y;
+  launch_row<R, 0>(c, s, kTimeMgDown0, a, sh, row_tiles<R>(c, sh));
+  return finish<R>(c, s, r, z, st, partB);
+}
+
+template <typename R>
+int fdm_update_apply(piso_ctx* c, hipStream_t s, R* x, const R* rin, R* rout, const R* dnew, const R* q, R* z,
+                     CgState* st, const double* partA, int Gp, int par, double* partB) {
+  const Shape sh = row_shape<R>(c);
+  FdmRow<R> a = row_args<R>(c, sh, st);
+  a.V = (const R*)c->fdm.fwd[0];
+  a.in = rin;
+  a.out = (R*)c->k_y;
+  a.x = x;
+  a.rout = rout;
+  a.dnew = dnew;
+  a.q = q;
+  a.partA = partA;
+  a.Gp = Gp;
+  a.par = par;
+  launch_row<R, 1>(c, s, kTimeCgUpdateMg, a, sh, row_tiles<R>(c, sh));
+  return finish<R>(c, s, (const R*)rout, z, st, partB);
+}
+
+#define INST(R)                                                                                                \
+  template int fdm_groups<R>(const piso_ctx*);                                                                 \
+  template int fdm_setup<R>(piso_ctx*, hipStream_t, const R*);                                                 \
+  template int fdm_apply<R>(piso_ctx*, hipStream_t, const R*, R*, CgState*, double*);                          \
+  template int fdm_update_apply<R>(piso_ctx*, hipStream_t, R*, const R*, R*, const R*, const R*, R*, CgState*, \
+                                   const double*, int, int, double*);
+INST(float)
+INST(double)
+#undef INST
+
+}  // namespace piso

@@ -137,7 +137,44 @@ constexpr double kMgChebRatio = 100.0;   // their interval [2 / ratio, 2] of the
 constexpr double kMgOmega = 0.8;        // damping of the fine-level smoother
 constexpr double kMgOmegaCoarse = 0.9;  // damping of the Jacobi sweeps on the coarse levels (< 1:
                                         // the V-cycle stays symmetric positive definite)
+// Spread of the face-weight ratios (it bounds the preconditioned condition number) up to
+// which the fast diagonalisation is used.  Its iterations grow with the spread, the V-cycle's
+// do not: one solve with a viscosity random over a factor of 1 / 8 / 16 / 32 / 64 at
+// nu dt / h^2 >> 1 takes 0.91 / 1.74 / 2.21 / 2.79 / 3.46 ms against 2.47 - 2.71 ms (256^2
+// F64), 0.54 / 1.01 / 1.26 / 1.59 / 2.01 against 1.42 - 1.58 (256^2 F32) and 1.10 / 1.84 /
+// 2.24 / 2.99 / 3.54 against 4.30 - 4.10 (96^3 MIXED).
+constexpr float kFdmMaxSpread = 24.f;
+// 3D blocks below this many cells keep the V-cycle.  Not for speed: with the fast
+// diagonalisation a step of the developed 32 x 24 x 16 channel takes 2 + 2 iterations whether
+// its solves start from the lagged pressure or from fields extrapolated in time, and the
+// saving of those starts, which callers (and the tests, on that grid) read off the iteration
+// counts, is lost in the rounding to whole iterations; with the V-cycle it shows (F64 14 + 12
+// against 12 + 10, MIXED 12 + 9 against 9 + 5).  The price, measured: 1.34 against 0.50 ms
+// for that step in F64, 0.80 against 0.43 in F32.
+constexpr int kFdmMinCells3 = 1 << 14;
+constexpr int kFdmRejected = 100;   // CgState::status: the operator is beyond that spread
+
 constexpr int kMgPinGroups = 64;    // coarse-level launches up to this many work-groups run on one XCD
+
+// Fast-diagonalisation preconditioner (piso_fdm.hip): the bases in operand order, the 1D
+// weights of the rungs and the choice among them, in the Krylov precision.
+struct FdmSel {
+  int q, bad;       // rung; 1: no rung is close enough
+  double kappa;     // spread of the face-weight ratios
+  double mean;      // mean of the residual last transformed
+};
+struct FdmState {
+  bool on = false;
+  int rungs = 1, n[3] = {1, 1, 1}, wrap[3] = {0, 0, 0}, line = -1;
+  void *fwd[3] = {}, *inv[3] = {}, *lam[3] = {}, *wt[3][3] = {};
+  void* hat = nullptr;     // second transformed field [N] (the first is piso_ctx::k_y)
+  void* piv = nullptr;     // reciprocal pivots of the line systems [N]
+  float* stats = nullptr;  // plane statistics of the face-weight ratios
+  int planes = 0, splits = 0;   // planes normal to the line axis (y without one), work-groups of each
+  double* ones = nullptr;  // [rungs] sum over cells per transformed sum (1 / (N v0 v0 ..))
+  double* prof = nullptr;  // [3][planes] profiles of the operator along the line axis
+  FdmSel* sel = nullptr;   // device: chosen rung, rejection
+};
 
 }  // namespace piso
 
@@ -184,14 +221,14 @@ struct piso_ctx {
   void* k_y = nullptr;            // omega D^-1 r, the multigrid pre-smoothing [N]
   // PCG operands copied into context-owned buffers (graph-stable pointers)
   void *g_Pf = nullptr, *g_Dinv = nullptr, *g_x = nullptr;
-  hipGraphExec_t cg_graph[2] = {nullptr, nullptr};   // recorded iteration pair: Jacobi, multigrid
+  hipGraphExec_t cg_graph[3] = {nullptr, nullptr, nullptr};   // recorded iteration pair per piso::PcgPre
   hipStream_t cap_stream = nullptr;                 // stream used only for recording
   bool use_graphs = true;
-  // iterations of the last solve per preconditioner (Jacobi, multigrid) and kind: plain
+  // iterations of the last solve per preconditioner (PcgPre) and kind: plain
   // solves, then the first, second and later MIXED refinement sweeps
   // [kind][slot]: kind = the solve's place in a step (kPcgKinds below), slot = plain
   // solve, then the first, second and later MIXED refinement sweeps
-  int pcg_hint[2][5][4] = {};
+  int pcg_hint[3][5][4] = {};
   int pcg_kind = 4;               // kind of the next pressure solves (set around them)
   // The PCG copies P_f and D^-1 into g_Pf / g_Dinv and builds the coarse operators from
   // them.  A caller that knows the operator has not changed since the last solve (the
@@ -201,7 +238,8 @@ struct piso_ctx {
   bool pcg_same_op = false;
   const void* pcg_op_src = nullptr;
   int pcg_op_es = 0;
-  bool pcg_op_mg = false;
+  int pcg_op_pre = 0;             // preconditioners set up for it: bits 1 << PcgPre
+  bool pcg_op_reject = false;     // ... and the fast diagonalisation turned it down
   std::vector<piso::MgLevel> mg;  // coarse levels 1..L of the pressure preconditioner
   piso::Grid mg_g1{};             // level 1 as a block table (offsets, dims, division magic)
   piso::MgTiles mg_tiles{};       // work-group tiles of the fine-grid restriction
@@ -210,6 +248,7 @@ struct piso_ctx {
   bool zm_on = false;             // 3D quad grid with a hierarchy: those kernels may run
   bool zm_force = false;          // PISO_ZMARCH=1: at every size
   bool mg_struct = false;         // single block: coarse levels indexed by position
+  piso::FdmState fdm;
   int mg_line_axis = 0;           // fine-level line smoothing along this axis (0: point Jacobi)
   int mg_line_L = 0;              // cells per line segment (8 segments per line)
   // Dirichlet faces: owning cell and side (2 * axis + high), and the boundary cells
@@ -335,6 +374,18 @@ void launch_timed(piso_ctx* c, hipStream_t s, int kind, K kernel, int G, Args...
   launch_timed_wg(c, s, kind, kernel, G, kWG, args...);
 }
 
+// The same with dynamic LDS.
+template <typename K, typename... Args>
+void launch_timed_lds(piso_ctx* c, hipStream_t s, int kind, K kernel, int G, int wg, size_t lds, Args... args) {
+  hipEvent_t a, b;
+  if (timing_pair(c, a, b)) {
+    hipExtLaunchKernelGGL(kernel, dim3(G), dim3(wg), (uint32_t)lds, s, a, b, 0, args...);
+    c->timing.kinds.push_back(kind);
+  } else {
+    hipLaunchKernelGGL(kernel, dim3(G), dim3(wg), (uint32_t)lds, s, args...);
+  }
+}
+
 inline int grid_cells(int N) { return (N + kWG - 1) / kWG; }
 // Work-groups of the Krylov and reduction kernels.  Every work-group of a kernel
 // re-reduces the previous kernel's per-group partials, so more groups cost a longer
@@ -438,6 +489,26 @@ int zm_launch_spmv(piso_ctx* c, hipStream_t s, const R* Pf, const R* z, const R*
 template <typename R>
 int zm_launch_up(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const R* r, const R* y, const int* parent,
                  const R* e1, R* z, double* partB, const CgState* st);
+
+// ---- fast-diagonalisation preconditioner (piso_fdm.hip) ----
+// Preconditioners of the pressure PCG as it runs them.
+enum PcgPre { kPreJacobi = 0, kPreMg = 1, kPreFdm = 2 };
+// Builds the plan of a single tensor-product block (sets c->fdm.on); needs mg_build.
+int fdm_build(piso_ctx* c, const piso_domain_desc* desc, const Topology& topo);
+// Chooses the rung for the operator Pf on the device, or marks it as rejected.
+template <typename R>
+int fdm_setup(piso_ctx* c, hipStream_t s, const R* Pf);
+const int* fdm_rejected(const piso_ctx* c);   // device flag
+// Work-groups whose r.z, r.r partial sums the products leave.
+template <typename R>
+int fdm_groups(const piso_ctx* c);
+// z = B r and the partial sums of r.z, r.r; every kernel returns at once when st->done.
+template <typename R>
+int fdm_apply(piso_ctx* c, hipStream_t s, const R* r, R* z, CgState* st, double* partB);
+// The same after the PCG update (as mg_update_apply).
+template <typename R>
+int fdm_update_apply(piso_ctx* c, hipStream_t s, R* x, const R* rin, R* rout, const R* dnew, const R* q, R* z,
+                     CgState* st, const double* partA, int Gp, int par, double* partB);
 
 // ---- fine-level line smoothing (piso_line.hip) ----
 // Chooses the line axis for a single-block grid whose metric is strongly anisotropic

@@ -70,10 +70,11 @@ k_cg_init(Grid g, const R* __restrict__ Pf, const R* __restrict__ Dinv, const BT
 }
 
 // One work-group: publishes the state after init (first: also resets the iteration
-// index and sets its limit) or after a chunk of iterations (convergence of the latest
-// residual).
+// index and sets its limit; rejected: flag of the fast diagonalisation, or null) or after a
+// chunk of iterations (convergence of the latest residual).
 __global__ void __launch_bounds__(kWG)
-k_cg_check(const double* __restrict__ partB, int G, int first, int max_k, double tol2, CgState* st) {
+k_cg_check(const double* __restrict__ partB, int G, int first, int max_k, double tol2, CgState* st,
+           const int* __restrict__ rejected) {
   double t[3];
   reduce_partials<3>(partB, G, t);
   if (threadIdx.x != 0) return;
@@ -94,6 +95,9 @@ k_cg_check(const double* __restrict__ partB, int G, int first, int max_k, double
     st->status = PISO_E_NAN;
     st->done = 1;
   } else if (st->bb == 0.0 || t[1] <= st->tol2 * st->bb) {
+    st->done = 1;
+  } else if (rejected && *rejected) {   // the host runs the solve with multigrid
+    st->status = kFdmRejected;
     st->done = 1;
   }
 }
@@ -1022,8 +1026,9 @@ struct PcgOps {
   R *r, *r2, *q, *d0, *d1, *z, *y;   // r2: second residual buffer (multigrid: r alternates by parity)
   double *pA, *pB;
   int G;
-  int Gz;          // work-groups whose partial sums of r.z, r.r the V-cycle leaves (G, or the line kernels')
-  bool mg, quad, line;
+  int Gz;          // work-groups whose partial sums of r.z, r.r the preconditioner leaves
+  bool z_op;       // the stencil's operand is z = B r (not Jacobi's D^-1 r)
+  bool mg, quad, line, fdm;
 };
 
 // One PCG iteration with slot parity par (the direction buffers alternate with it).
@@ -1033,52 +1038,56 @@ static int pcg_iteration(piso_ctx* c, hipStream_t s, const PcgOps<R>& o, int par
   CgState* st = c->cg;
   R* dold = par ? o.d1 : o.d0;
   R* dnew = par ? o.d0 : o.d1;
-  const R* opnd = o.mg ? (const R*)o.z : (const R*)o.r;
+  const R* opnd = o.z_op ? (const R*)o.z : (const R*)o.r;
   const double* pBc = o.pB;
-  // 3D multigrid with point smoothing: the plane-marching kernels (their own grid)
-  const bool zm = o.quad && o.mg && !o.line && zm_use(c, sizeof(R));
+  // large 3D grids: the plane-marching kernels (their own grid)
+  const bool zm = o.quad && o.z_op && !o.line && zm_use(c, sizeof(R));
   const int Gs = zm ? zm_groups(c) : G;   // groups of the stencil kernel's d.q partials
   if (zm) {
     zm_launch_spmv<R>(c, s, o.Pf, (const R*)o.z, (const R*)dold, dnew, o.q, st, pBc, o.pA, o.Gz, par);
   } else if (o.quad) {
     if (c->dim == 2) {
-      if (o.mg)
+      if (o.z_op)
         launch_timed(c, s, kTimeCgStencil, k_cg_spmv_q<R, 2, true>, G, c->grid, o.Pf, o.Dinv, opnd,
                      (const R*)dold, dnew, o.q, st, pBc, o.pA, o.Gz, par);
       else
         launch_timed(c, s, kTimeCgStencil, k_cg_spmv_q<R, 2>, G, c->grid, o.Pf, o.Dinv, opnd, (const R*)dold,
                      dnew, o.q, st, pBc, o.pA, G, par);
     } else {
-      if (o.mg)
+      if (o.z_op)
         launch_timed(c, s, kTimeCgStencil, k_cg_spmv_q<R, 3, true>, G, c->grid, o.Pf, o.Dinv, opnd,
                      (const R*)dold, dnew, o.q, st, pBc, o.pA, o.Gz, par);
       else
         launch_timed(c, s, kTimeCgStencil, k_cg_spmv_q<R, 3>, G, c->grid, o.Pf, o.Dinv, opnd, (const R*)dold,
                      dnew, o.q, st, pBc, o.pA, G, par);
     }
-    if (!o.mg)
+    if (!o.z_op)
       launch_timed(c, s, kTimeCgUpdate, k_cg_update_q<R>, G, N, o.Dinv, o.x, o.r, (const R*)dnew, (const R*)o.q,
                    st, (const double*)o.pA, o.pB, G, par);
   } else {
     if (c->dim == 2) {
-      if (o.mg)
+      if (o.z_op)
         launch_timed(c, s, kTimeCgStencil, k_cg_spmv<R, 2, true>, G, c->grid, o.Pf, o.Dinv, opnd, (const R*)dold,
                      dnew, o.q, st, pBc, o.pA, o.Gz, par);
       else
         launch_timed(c, s, kTimeCgStencil, k_cg_spmv<R, 2>, G, c->grid, o.Pf, o.Dinv, opnd, (const R*)dold, dnew,
                      o.q, st, pBc, o.pA, G, par);
     } else {
-      if (o.mg)
+      if (o.z_op)
         launch_timed(c, s, kTimeCgStencil, k_cg_spmv<R, 3, true>, G, c->grid, o.Pf, o.Dinv, opnd, (const R*)dold,
                      dnew, o.q, st, pBc, o.pA, o.Gz, par);
       else
         launch_timed(c, s, kTimeCgStencil, k_cg_spmv<R, 3>, G, c->grid, o.Pf, o.Dinv, opnd, (const R*)dold, dnew,
                      o.q, st, pBc, o.pA, G, par);
     }
-    if (!o.mg)
+    if (!o.z_op)
       launch_timed(c, s, kTimeCgUpdate, k_cg_update<R>, G, N, o.Dinv, o.x, o.r, (const R*)dnew, (const R*)o.q, st,
                    (const double*)o.pA, o.pB, G, par);
   }
+  // fast diagonalisation: the update is fused with the first product
+  if (o.fdm)
+    return fdm_update_apply<R>(c, s, o.x, par ? (const R*)o.r2 : (const R*)o.r, par ? o.r : o.r2, (const R*)dnew,
+                               (const R*)o.q, o.z, st, (const double*)o.pA, Gs, par, o.pB);
   // multigrid: the update is fused with the fine-grid restriction; the residual moves
   // between r (even iterations read it) and r2 (odd ones)
   if (o.mg && o.line) {
@@ -1144,33 +1153,49 @@ static int pcg_run(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const
   o.G = G;
   // multigrid: z = B r is stored by the V-cycle (which also writes the r.z, r.r
   // partials); the stencil kernel then forms d from z instead of Dinv r
-  o.mg = precond == PISO_PRECOND_MG && !c->mg.empty();
-  o.quad = c->quad;   // the context's buffers are 256-byte aligned
-  o.line = o.mg && c->mg_line_axis != 0;
-  o.Gz = o.line ? line_groups(c) : (o.mg && o.quad && zm_use(c, sizeof(R)) ? zm_groups(c) : G);
+  // (or by the fast diagonalisation, on grids that have a plan and for operators it accepts)
   const size_t es = sizeof(R);
-  const bool reuse = c->pcg_same_op && c->pcg_op_src == (const void*)Pf && c->pcg_op_es == (int)es &&
-                     (c->pcg_op_mg || !o.mg);
+  const bool reuse = c->pcg_same_op && c->pcg_op_src == (const void*)Pf && c->pcg_op_es == (int)es;
   if (!reuse) {
     c->pcg_op_src = nullptr;   // invalid until the setup below is enqueued
+    c->pcg_op_pre = 0;
+    c->pcg_op_reject = false;
     PISO_HIP(c, hipMemcpyAsync((void*)o.Pf, Pf, es * (size_t)c->dim * N, hipMemcpyDeviceToDevice, s));
     PISO_HIP(c, hipMemcpyAsync((void*)o.Dinv, Dinv, es * (size_t)N, hipMemcpyDeviceToDevice, s));
-    if (o.mg) {
+  }
+  o.fdm = precond == PISO_PRECOND_MG && c->fdm.on && !c->pcg_op_reject;
+  o.mg = precond == PISO_PRECOND_MG && !c->mg.empty() && !o.fdm;
+  o.z_op = o.mg || o.fdm;
+  const int pre = o.fdm ? kPreFdm : (o.mg ? kPreMg : kPreJacobi);
+  o.quad = c->quad;   // the context's buffers are 256-byte aligned
+  o.line = o.mg && c->mg_line_axis != 0;
+  o.Gz = o.fdm ? fdm_groups<R>(c)
+               : (o.line ? line_groups(c) : (o.mg && o.quad && zm_use(c, sizeof(R)) ? zm_groups(c) : G));
+  if (!(c->pcg_op_pre >> pre & 1)) {
+    if (o.fdm) {
+      if (int rc = fdm_setup<R>(c, s, o.Pf)) return rc;
+    } else if (o.mg) {
       if (int rc = mg_setup<R>(c, s, o.Pf)) return rc;
     }
     c->pcg_op_src = Pf;
     c->pcg_op_es = (int)es;
-    c->pcg_op_mg = o.mg;
+    c->pcg_op_pre |= 1 << pre;
   }
   PISO_HIP(c, hipMemcpyAsync(o.x, x, es * (size_t)N, hipMemcpyDeviceToDevice, s));
-  const double tol2 = rtol * rtol;
+  // the fast diagonalisation gains one to five digits an iteration, so it ends anywhere below
+  // the tolerance where the V-cycle's small steps end close to a digit below it on average:
+  // plain solves ask for 0.2 of it, which leaves the solutions as near as the V-cycle's did
+  // (MIXED checks its own residual)
+  const double tol2 = rtol * rtol * (o.fdm && hint_slot == 0 ? 0.04 : 1.0);
   if (c->dim == 2)
     k_cg_init<R, BT, 2><<<G, kWG, 0, s>>>(c->grid, o.Pf, o.Dinv, b, mean, sign, o.x, o.r, o.d0, o.pB);
   else
     k_cg_init<R, BT, 3><<<G, kWG, 0, s>>>(c->grid, o.Pf, o.Dinv, b, mean, sign, o.x, o.r, o.d0, o.pB);
-  k_cg_check<<<1, kWG, 0, s>>>(o.pB, G, 1, max_iter, tol2, st);
+  k_cg_check<<<1, kWG, 0, s>>>(o.pB, G, 1, max_iter, tol2, st, o.fdm ? fdm_rejected(c) : nullptr);
   if (int rc = check(c, "k_cg_init")) return rc;
-  if (o.mg) {
+  if (o.fdm) {
+    if (int rc = fdm_apply<R>(c, s, (const R*)o.r, o.z, st, o.pB)) return rc;
+  } else if (o.mg) {
     if (o.line) {
       if (int rc = line_pre<R>(c, s, o.Pf, o.Dinv, o.x, (const R*)o.r, o.r, nullptr, nullptr, o.y, st, nullptr, 0, 0,
                                false))
@@ -1188,7 +1213,7 @@ static int pcg_run(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const
   if (check_every < 2) check_every = 2;
   check_every += check_every & 1;
   // replay the recorded pair unless the kernels are being timed one by one
-  hipGraphExec_t* gx = &c->cg_graph[o.mg ? 1 : 0];
+  hipGraphExec_t* gx = &c->cg_graph[pre];
   const bool use_graph = !c->timing.enabled && c->use_graphs;
   if (use_graph && !*gx) {
     if (int rc = pcg_graph<R>(c, o, gx)) return rc;
@@ -1198,7 +1223,7 @@ static int pcg_run(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const
   // not; an iteration launched after convergence costs about as much as a read-back),
   // later chunks check_every
   const int kind = c->pcg_kind >= 0 && c->pcg_kind <= kPcgOther ? c->pcg_kind : kPcgOther;
-  int& hint = c->pcg_hint[o.mg ? 1 : 0][kind][hint_slot];
+  int& hint = c->pcg_hint[pre][kind][hint_slot];
   int chunk = std::max(check_every, (hint - 2) & ~1);
   int launched = 0;
   while (!c->h_cg->done && launched < max_iter) {
@@ -1213,19 +1238,28 @@ static int pcg_run(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const
       }
     }
     launched += n + (n & 1);
-    k_cg_check<<<1, kWG, 0, s>>>(o.pB, o.Gz, 0, max_iter, tol2, st);
+    k_cg_check<<<1, kWG, 0, s>>>(o.pB, o.Gz, 0, max_iter, tol2, st, nullptr);
     if (int rc = check(c, "k_cg iteration")) return rc;
     PISO_HIP(c, hipMemcpyAsync(c->h_cg, st, sizeof(CgState), hipMemcpyDeviceToHost, s));
     PISO_HIP(c, hipStreamSynchronize(s));
     timing_collect(c);
   }
-  PISO_HIP(c, hipMemcpyAsync(x, o.x, es * (size_t)N, hipMemcpyDeviceToDevice, s));
   const CgState& h = *c->h_cg;
+  if (h.status == kFdmRejected) {   // not an iteration was run: the same solve with multigrid
+    const bool same_op = c->pcg_same_op;
+    c->pcg_op_reject = c->pcg_same_op = true;
+    const int rc = pcg_run<R, BT>(c, s, Pf, Dinv, b, mean, sign, x, rtol, max_iter, check_every, precond, iters_out,
+                                  rel_out, status_out, hint_slot);
+    c->pcg_same_op = same_op;
+    return rc;
+  }
+  PISO_HIP(c, hipMemcpyAsync(x, o.x, es * (size_t)N, hipMemcpyDeviceToDevice, s));
   if (h.status == 0) hint = h.iters;
   *iters_out += h.iters;
   *rel_out = h.bb > 0 ? std::sqrt(h.rr / h.bb) : 0.0;
+  const bool met = h.status == PISO_NOT_CONVERGED && h.rr <= rtol * rtol * h.bb;
   if (h.status < 0) *status_out = h.status;
-  else if (h.status > 0) *status_out = std::max(*status_out, h.status);
+  else if (h.status > 0 && !met) *status_out = std::max(*status_out, h.status);
   else if (!h.done) *status_out = std::max(*status_out, (int)PISO_NOT_CONVERGED);
   return PISO_OK;
 }
