@@ -122,8 +122,9 @@ typedef enum {
                                coarse operators, damped Jacobi smoothing).  The paper names
                                multigrid for the pressure as the way to a faster solver
                                (Sec. 6, App. A.6); the converged solution is the same.
-                               On a single tensor-product block (walls or periodic sides,
-                               axes of at most 512 cells, uniform where periodic) the
+                               Where the blocks together form one box of cells (walls or
+                               periodic sides, axes of at most 512 cells) with a metric
+                               near a tensor product, the pressure
                                operator is close to one that 1D eigenbases diagonalise, and
                                that exact inverse takes the V-cycle's place for every
                                operator close enough to it (judged per solve, on the device;

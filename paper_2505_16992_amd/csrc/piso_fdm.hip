@@ -1,8 +1,8 @@
-// Fast-diagonalisation preconditioner of the pressure PCG on single tensor-product blocks
-// (plan and mathematics: piso_fdm_plan.h).  z = B r with one dense product per axis and
-// direction, and one tridiagonal system per mode along the line axis: GEMM-shaped work on
-// fields of N cells, done with the FP32 / FP64 matrix instructions (full precision of the
-// type, no narrower operands).
+// Fast-diagonalisation preconditioner of the pressure PCG on blocks that form a logical box
+// with a metric near a tensor product (plan and mathematics: piso_fdm_plan.h).  z = B r with
+// one dense product per axis and direction, and one tridiagonal system per mode along the line
+// axis: GEMM-shaped work on fields of N cells, done with the FP32 / FP64 matrix instructions
+// (full precision of the type, no narrower operands).
 //
 // What bounds it.  2 n flops per cell and product over two field streams: at n = 96 in FP32
 // that is 24 flop/B, about the ratio of the chip's 150 TFLOP/s of FP32 matrix rate to its
@@ -28,6 +28,9 @@
 // tiles to fill the chip (2D), several work-groups share a field tile and split its output
 // rows (`splits`).
 //
+// Transformed fields are in box order.  Where that is not the cells' order (several blocks,
+// x and y exchanged) the two products along x, which meet the cells, go through a map.
+//
 // The constant mode.  M has it for its null space and the residual's sum is zero, but in FP32
 // the sum left by rounding is enough to stop the iteration from reaching 1e-7 (a 105 x 171
 // cavity went from 2e-7 to 1 and stayed there).  The kernel that meets the null mode knows
@@ -43,6 +46,7 @@
 #include <cstdlib>
 #include <new>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "piso_fdm_plan.h"
@@ -95,6 +99,8 @@ struct FdmRow {
   int n, rows, kc, mt, splits, mper, ntiles, ld;   // mper: output tiles per split
   uint32_t div_lo, div_hi;                         // division by n (or n / 4)
   int div_sh, quad;
+  const int* map;
+  int rowfast;
   const R* V;
   size_t vstride;
   const FdmSel* sel;   // rung and the mean of r
@@ -146,7 +152,10 @@ __device__ __forceinline__ typename Vec4<R>::T lds4(const R* p) {
   return v;
 }
 
-template <typename R, int NT, int MODE>
+// GATHER (MODE 0 and 1): cells one by one, through the map or on rows that are no quads; a form
+// of its own, since its eight loads in flight cost the quad form registers (96^3: 9.5 us
+// alone, 12.0 with both in one kernel).
+template <typename R, int NT, int MODE, bool GATHER>
 __global__ void __launch_bounds__(64 * kFdmMaxWaves) k_fdm_row(FdmRow<R> a) {
   using V4 = typename Vec4<R>::T;
   extern __shared__ __align__(32) char smem[];
@@ -156,7 +165,8 @@ __global__ void __launch_bounds__(64 * kFdmMaxWaves) k_fdm_row(FdmRow<R> a) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nth = blockDim.x;
   const int g = lane >> 4, nl = lane & 15;
   const uint64_t dm = (uint64_t)a.div_lo | ((uint64_t)a.div_hi << 32);
-  const int per_row = a.quad ? a.n >> 2 : a.n;
+  const bool qin = a.quad && !GATHER;
+  const int per_row = qin ? a.n >> 2 : a.n;
   const int total = a.ntiles * a.splits;
   R alpha = R(0);
   if constexpr (MODE == 1) {
@@ -184,10 +194,66 @@ __global__ void __launch_bounds__(64 * kFdmMaxWaves) k_fdm_row(FdmRow<R> a) {
     const int row0 = tile * 16 * NT;
     const int rows = min(16 * NT, a.rows - row0);
     const size_t base = (size_t)row0 * a.n;
-    // field tile into LDS (contiguous in memory); the first split also stores the update
-    for (int e = tid; e < rows * per_row; e += nth) {
-      const int r = (int)fast_div((uint32_t)e, dm, a.div_sh);
-      if (a.quad) {
+    // field tile into LDS (without a map contiguous in memory); the first split also stores
+    // the update
+    // (eight elements' loads at a time: through the map each is two loads in a row, and one by
+    // one a 256 x 256 grid took 12.5 us here)
+    auto gather = [&](int count, auto&& at) {
+      constexpr int U = 8;
+      for (int e0 = tid; e0 < count; e0 += U * nth) {
+        int rr[U], cc[U];
+        size_t P[U];
+        R v[U], qv[U], xv[U], dv[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          const int e = min(e0 + u * nth, count - 1);
+          P[u] = at(e, rr[u], cc[u]);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          v[u] = a.in[P[u]];
+          if constexpr (MODE == 1) {
+            qv[u] = a.q[P[u]];
+            if (sp == 0) {
+              xv[u] = a.x[P[u]];
+              dv[u] = a.dnew[P[u]];
+            }
+          }
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+          if (e0 + u * nth >= count || rr[u] >= rows) continue;
+          if constexpr (MODE == 1) {
+            v[u] = (v[u] - mean) - alpha * qv[u];
+            if (sp == 0) {
+              a.x[P[u]] = xv[u] + alpha * dv[u];
+              a.rout[P[u]] = v[u];
+            }
+          }
+          X[rr[u] * a.ld + cc[u]] = v[u];
+        }
+      }
+    };
+    if constexpr (GATHER) {
+      if (a.rowfast)
+        gather(16 * NT * a.n, [&](int e, int& r, int& c) {
+          r = e % (16 * NT);
+          c = e / (16 * NT);
+          return (size_t)a.map[(size_t)c * a.rows + row0 + min(r, rows - 1)];
+        });
+      else
+        gather(rows * per_row, [&](int e, int& r, int& c) {
+          r = (int)fast_div((uint32_t)e, dm, a.div_sh);
+          c = e - r * per_row;
+          return a.map ? (size_t)a.map[base + e] : base + e;
+        });
+    } else {
+      for (int e = tid; e < rows * per_row; e += nth) {
+        const int r = (int)fast_div((uint32_t)e, dm, a.div_sh);
+        if (MODE == 2 && !qin) {   // the transformed field is in box order
+          X[r * a.ld + (e - r * per_row)] = a.in[base + e];
+          continue;
+        }
         const int c = (e - r * per_row) << 2;
         const size_t P = base + (size_t)e * 4;
         V4 v = *reinterpret_cast<const V4*>(a.in + P);
@@ -211,18 +277,6 @@ __global__ void __launch_bounds__(64 * kFdmMaxWaves) k_fdm_row(FdmRow<R> a) {
         R* d = X + r * a.ld + c;
 #pragma unroll
         for (int t = 0; t < 4; ++t) d[t] = v[t];
-      } else {
-        const int c = e - r * per_row;
-        const size_t P = base + e;
-        R v = a.in[P];
-        if constexpr (MODE == 1) {
-          v = (v - mean) - alpha * a.q[P];
-          if (sp == 0) {
-            a.x[P] += alpha * a.dnew[P];
-            a.rout[P] = v;
-          }
-        }
-        X[r * a.ld + c] = v;
       }
     }
     // zeros beyond the row's end and in missing rows (the packed basis is zero there too, but
@@ -253,7 +307,7 @@ __global__ void __launch_bounds__(64 * kFdmMaxWaves) k_fdm_row(FdmRow<R> a) {
         const int r = t * 16 + nl;
         if (r >= rows || col >= a.n) continue;
         const size_t P = base + (size_t)r * a.n + col;
-        if (a.quad) {
+        if (a.quad && (MODE != 2 || !a.map)) {
           *reinterpret_cast<V4*>(a.out + P) = acc[t];
           if constexpr (MODE == 2) {
             const V4 rv = *reinterpret_cast<const V4*>(a.r + P);
@@ -268,9 +322,11 @@ __global__ void __launch_bounds__(64 * kFdmMaxWaves) k_fdm_row(FdmRow<R> a) {
 #pragma unroll
           for (int u = 0; u < 4; ++u) {
             if (col + u >= a.n) continue;
-            a.out[P + u] = acc[t][u];
+            size_t Q = P + u;
+            if (MODE == 2 && a.map) Q = a.map[a.rowfast ? (size_t)(col + u) * a.rows + row0 + r : Q];
+            a.out[Q] = acc[t][u];
             if constexpr (MODE == 2) {
-              const double rp = (double)(a.r[P + u] - mean);
+              const double rp = (double)(a.r[Q] - mean);
               acc_rz += rp * (double)acc[t][u];
               acc_rr += rp * rp;
             }
@@ -456,16 +512,28 @@ __global__ void __launch_bounds__(64) k_fdm_factor(FdmLine<R> a) {
   const double ls = a.ls ? (double)a.ls[(size_t)q * a.slabs + slab] : 0.0;
   R* piv = a.piv + (size_t)slab * a.sstride + c;
   auto diag = [&](int j) { return lx * a.cx[j] + (a.ls ? ls * a.cs[j] : 0.0); };
-  // rows 0 .. m - 1 downward (half 0), n - 1 .. m + 1 upward (half 1)
+  // rows 0 .. m - 1 downward (half 0), n - 1 .. m + 1 upward (half 1); eight rows' profile
+  // loads at a time, ahead of the chain
   const int steps = half ? n - 1 - m : m;
   double carry = 0.0;   // k e / p of the row before
-  for (int t = 0; t < steps; ++t) {
-    const int j = half ? n - 1 - t : t;
-    const double open = a.k[half ? j - 1 : j];
-    const double e = diag(j) + carry;
-    const double p = open + e;
-    carry = open * e / p;
-    if (on) piv[(size_t)j * a.rstride] = (R)(1.0 / p);
+  constexpr int B = 8;
+  for (int t0 = 0; t0 < steps; t0 += B) {
+    double open[B], dg[B];
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      const int t = min(t0 + u, steps - 1), j = half ? n - 1 - t : t;
+      open[u] = a.k[half ? j - 1 : j];
+      dg[u] = diag(j);
+    }
+#pragma unroll
+    for (int u = 0; u < B; ++u) {
+      if (t0 + u >= steps) break;
+      const int j = half ? n - 1 - (t0 + u) : t0 + u;
+      const double e = dg[u] + carry;
+      const double ip = 1.0 / (open[u] + e);
+      carry = open[u] * e * ip;
+      if (on) piv[(size_t)j * a.rstride] = (R)ip;
+    }
   }
   const double other = __shfl_xor(carry, 32, 64);
   if (half == 0 && on) {
@@ -475,83 +543,158 @@ __global__ void __launch_bounds__(64) k_fdm_factor(FdmLine<R> a) {
   }
 }
 
-// The solve: a tile of TN columns goes to LDS with all its waves' loads in flight, one wave
-// runs the recurrences (one FMA a row and direction, its factor k / p formed off the
-// chain), and all write the result.
+// The solve.  With y = value / pivot the recurrences are one FMA a row,
+//   forward  y_j = r_j I_j + (k_before I_j) y_before,   backward  x_j = y_j + (k_after I_j) x_after
+// (I: reciprocal pivots), and all three coefficients are formed by the whole work-group while
+// it brings a tile of TN columns to LDS.  What is left to the one wave that runs the chains is
+// then issue-bound: rows lie contiguous per column in the order the chain meets them (the
+// lower half reversed, zeros ahead of its first row up to a multiple of four), so that four
+// rows are two 16-byte LDS reads, four FMAs and a write.  256 rows of 256 columns: 20 us with
+// row-by-row addressing, of which the two chains took most, now 9.0.
+__host__ __device__ inline int line_len(int n) { return (n / 2 + 3) / 4 * 4; }   // longer half, padded
+// column stride: 4 modulo 8, so that the columns' 16-byte reads spread over the banks
+__host__ __device__ inline int line_stride(int n) { return line_len(n) + (line_len(n) % 8 ? 8 : 4); }
+template <typename R>
+inline size_t line_lds(int n, int tn) {
+  return ((size_t)6 * tn * line_stride(n) + 4 * (size_t)tn) * sizeof(R);
+}
+
+template <typename R>
+__device__ __forceinline__ void sts4(R* p, typename Vec4<R>::T v) {
+  if constexpr (sizeof(R) == 4) {
+    *reinterpret_cast<f32x4*>(p) = v;
+  } else {
+    *reinterpret_cast<f64x2*>(p) = f64x2{v[0], v[1]};
+    *reinterpret_cast<f64x2*>(p + 2) = f64x2{v[2], v[3]};
+  }
+}
+
 template <typename R, int TN>
 __global__ void __launch_bounds__(kWG) k_fdm_line(FdmLine<R> a) {
+  using V4 = typename Vec4<R>::T;
   extern __shared__ __align__(32) char smem[];
-  constexpr int ld = TN + 1;
-  const int n = a.n;
-  R* X = (R*)smem;            // [n][ld] right-hand side, then the solution
-  R* I = X + (size_t)n * ld;  // [n][ld] reciprocal pivots
-  R* K = I + (size_t)n * ld;  // [n] couplings
+  __shared__ double red[kWaves];
+  const int n = a.n, m = n / 2, Lp = line_len(n), L = line_stride(n), T = 2 * TN * L;
+  R* Y = (R*)smem;     // [half][column][L]: r I, then y, then the solution
+  R* G = Y + T;        // k_before I
+  R* F = G + T;        // k_after I
+  R* Rm = F + T;       // [TN] middle row's r I, then its solution
+  R* Mc = Rm + TN;     // [half][TN] middle row's k I towards each half
   if (a.st->done) return;
+  const int tid = threadIdx.x;
   const int per = (a.cols + TN - 1) / TN;
   const int tile = xcd_logical_group(), slab = tile / per, c0 = (tile - slab * per) * TN;
   const size_t base = (size_t)slab * a.sstride + c0;
   const int w = min(TN, a.cols - c0);
-  constexpr int U = 4;
-  for (int e0 = threadIdx.x; e0 < n * TN; e0 += U * kWG) {
-    R xv[U], iv[U];
+  // the null mode is column 0 of the first tile: its right-hand side's mean
+  const bool null = slab == 0 && c0 == 0;
+  R off = R(0);
+  auto block_sum = [&](double t) {
+    t = wave_sum(t);
+    if ((tid & 63) == 0) red[tid >> 6] = t;
+    __syncthreads();
+    double v = 0.0;
+#pragma unroll
+    for (int q = 0; q < kWaves; ++q) v += red[q];
+    __syncthreads();
+    return v;
+  };
+  if (null) {
+    double t = 0.0;
+    for (int j = tid; j < n; j += kWG) t += (double)a.in[(size_t)j * a.rstride];
+    t = block_sum(t);
+    off = (R)(t / n);
+    if (tid == 0) a.sel->mean = t * a.ones[a.sel->q];
+  }
+  constexpr int U = 8;
+  for (int e0 = tid; e0 < n * TN; e0 += U * kWG) {
+    R xv[U], iv[U], kb[U], ka[U];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int e = e0 + u * kWG, j = e / TN, c = e % TN;
-      const bool on = j < n && c < w;
-      const size_t P = on ? base + (size_t)j * a.rstride + c : base;
+      const int e = e0 + u * kWG, j = min(e / TN, n - 1), c = e % TN;
+      const size_t P = c < w ? base + (size_t)j * a.rstride + c : base;
       xv[u] = a.in[P];
       iv[u] = a.piv[P];
+      kb[u] = (R)a.k[max(j - 1, 0)];
+      ka[u] = (R)a.k[j];
     }
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       const int e = e0 + u * kWG, j = e / TN, c = e % TN;
       if (j >= n) continue;
-      X[j * ld + c] = xv[u];
-      I[j * ld + c] = iv[u];
+      const R x = c == 0 ? xv[u] - off : xv[u];
+      const R lo = j > 0 ? kb[u] * iv[u] : R(0), hi = j + 1 < n ? ka[u] * iv[u] : R(0);
+      if (j == m) {
+        Rm[c] = x * iv[u];
+        Mc[c] = lo;
+        Mc[TN + c] = hi;
+      } else {
+        const int half = j > m, steps = half ? n - 1 - m : m, t = half ? n - 1 - j : j;
+        const int q = (half * TN + c) * L + Lp - steps + t;
+        Y[q] = x * iv[u];
+        G[q] = half ? hi : lo;
+        F[q] = half ? lo : hi;
+      }
     }
   }
-  for (int j = threadIdx.x; j < n; j += kWG) K[j] = (R)a.k[j];
+  for (int e = tid; e < 2 * TN * 4; e += kWG) {   // zeros ahead of a half's first row
+    const int half = e / (TN * 4), c = e / 4 % TN, p = e % 4;
+    if (p < Lp - (half ? n - 1 - m : m)) {
+      const int q = (half * TN + c) * L + p;
+      Y[q] = G[q] = F[q] = R(0);
+    }
+  }
   __syncthreads();
-  const bool null = slab == 0 && c0 == 0;   // column 0 of this tile is the null mode
-  auto column_mean = [&]() {                // off column 0, by the first wave
-    double t = 0.0;
-    for (int j = threadIdx.x; j < n; j += 64) t += (double)X[j * ld];
-    t = wave_sum(t);
-    for (int j = threadIdx.x; j < n; j += 64) X[j * ld] -= (R)(t / n);
-    return t;
-  };
-  if (null && threadIdx.x < 64) {
-    const double t = column_mean();
-    if (threadIdx.x == 0) a.sel->mean = t * a.ones[a.sel->q];
-  }
-  if (threadIdx.x < 2 * TN) {
-    const int half = threadIdx.x / TN, c = threadIdx.x % TN;
-    const int m = n / 2, steps = half ? n - 1 - m : m;
-    R d = R(0), f = R(0);   // value and factor k / p of the row before
-#pragma unroll 4
-    for (int t = 0; t < steps; ++t) {
-      const int j = half ? n - 1 - t : t;
-      d = X[j * ld + c] + f * d;
-      f = K[half ? j - 1 : j] * I[j * ld + c];
-      X[j * ld + c] = d;
+  if (tid < 2 * TN) {
+    const int half = tid / TN, c = tid % TN;
+    R *y = Y + (half * TN + c) * L, *g = G + (half * TN + c) * L, *f = F + (half * TN + c) * L;
+    R d = R(0);
+    V4 yv = lds4<R>(y), gv = lds4<R>(g);
+    for (int p = 0; p < Lp; p += 4) {
+      const V4 yn = lds4<R>(y + p + 4), gn = lds4<R>(g + p + 4);   // the padding behind the last
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        d = yv[u] + gv[u] * d;
+        yv[u] = d;
+      }
+      sts4<R>(y + p, yv);
+      yv = yn;
+      gv = gn;
     }
-    const R mine = f * d;
+    const R mine = Mc[half * TN + c] * d;
     const R other = __shfl_xor(mine, TN, 64);
-    R x = (X[m * ld + c] + (half ? other + mine : mine + other)) * I[m * ld + c];
-    if (half == 0) X[m * ld + c] = x;
-#pragma unroll 4
-    for (int t = steps - 1; t >= 0; --t) {
-      const int j = half ? n - 1 - t : t;
-      const R iv = I[j * ld + c];
-      x = X[j * ld + c] * iv + (K[half ? j - 1 : j] * iv) * x;
-      X[j * ld + c] = x;
+    R x = Rm[c] + (half ? other + mine : mine + other);
+    if (half == 0) Rm[c] = x;
+    if (Lp > 0) {
+      V4 ya = lds4<R>(y + Lp - 4), fa = lds4<R>(f + Lp - 4);
+      for (int p = Lp - 4; p >= 0; p -= 4) {
+        const int pn = max(p - 4, 0);
+        const V4 yn = lds4<R>(y + pn), fn = lds4<R>(f + pn);
+#pragma unroll
+        for (int u = 3; u >= 0; --u) {
+          x = ya[u] + fa[u] * x;
+          ya[u] = x;
+        }
+        sts4<R>(y + p, ya);
+        ya = yn;
+        fa = fn;
+      }
     }
   }
-  if (null && threadIdx.x < 64) column_mean();
   __syncthreads();
-  for (int e = threadIdx.x; e < n * TN; e += kWG) {
+  auto value = [&](int j, int c) {
+    const int half = j > m, steps = half ? n - 1 - m : m, t = half ? n - 1 - j : j;
+    return j == m ? Rm[c] : Y[(half * TN + c) * L + Lp - steps + t];
+  };
+  R shift = R(0);   // the null mode's solution without its mean
+  if (null) {
+    double t = 0.0;
+    for (int j = tid; j < n; j += kWG) t += (double)value(j, 0);
+    shift = (R)(block_sum(t) / n);
+  }
+  for (int e = tid; e < n * TN; e += kWG) {
     const int j = e / TN, c = e % TN;
-    if (c < w) a.out[base + (size_t)j * a.rstride + c] = X[j * ld + c];
+    if (c < w) a.out[base + (size_t)j * a.rstride + c] = value(j, c) - (c == 0 ? shift : R(0));
   }
 }
 
@@ -560,9 +703,11 @@ __global__ void __launch_bounds__(kWG) k_fdm_line(FdmLine<R> a) {
 template <typename R>
 struct FdmStats {
   int dim, rungs, pa, oa, splits;   // planes normal to pa; oa: the other axis of their rows
-  int n[3], wrap[3];
+  int n[3], wrap[3], perm[3];
   size_t stride[3];
   size_t N;
+  const int* map;
+  int rowfast;
   const R* wt[3][3];   // [j][m]: [rung][n_m]
 };
 constexpr int kFdmStatValues = 3 * 3;   // per rung: term, then smallest, largest, sum
@@ -587,13 +732,14 @@ __global__ void __launch_bounds__(kWG) k_fdm_stats(FdmStats<R> a, const R* __res
   for (int w = sp * kWaves + wave; w < rows * segs; w += a.splits * kWaves) {
     const int o = w / segs, i = (w - o * segs) * 64 + lane;
     if (i >= nx) continue;
-    const size_t P = (size_t)plane * a.stride[a.pa] + (size_t)o * a.stride[a.oa] + i;
+    size_t P = (size_t)plane * a.stride[a.pa] + (size_t)o * a.stride[a.oa] + i;
+    if (a.map) P = a.map[a.rowfast ? (size_t)i * (a.N / nx) + P / nx : P];
 #pragma unroll
     for (int j = 0; j < 3; ++j) {
       if (j >= a.dim) continue;
       const int pos = j == 0 ? i : (j == a.pa ? plane : o);
       if (pos + 1 >= a.n[j] && !a.wrap[j]) continue;
-      const R p = Pf[(size_t)j * a.N + P];
+      const R p = Pf[(size_t)a.perm[j] * a.N + P];
 #pragma unroll
       for (int q = 0; q < kFdmRungs; ++q) {
         if (q >= a.rungs) continue;
@@ -785,11 +931,24 @@ constexpr size_t kFdmLds = 150 * 1024;
 
 template <typename R, int MODE>
 void launch_row(piso_ctx* c, hipStream_t s, int kind, FdmRow<R> a, const Shape& sh, int G) {
+  const bool gather = MODE != 2 && (!a.quad || a.map);
+  const bool qin = a.quad && !gather;   // as in the kernel
+  div_magic((uint32_t)(qin ? a.n / 4 : a.n), a.div_lo, a.div_hi, a.div_sh);
   const size_t lds = (size_t)16 * sh.nt * a.ld * sizeof(R);
   const int wg = 64 * sh.waves;
-  if (sh.nt == 1) launch_timed_lds(c, s, kind, k_fdm_row<R, 1, MODE>, G, wg, lds, a);
-  else if (sh.nt == 2) launch_timed_lds(c, s, kind, k_fdm_row<R, 2, MODE>, G, wg, lds, a);
-  else launch_timed_lds(c, s, kind, k_fdm_row<R, 4, MODE>, G, wg, lds, a);
+  auto launch = [&](auto nt) {
+    constexpr int NT = decltype(nt)::value;
+    if constexpr (MODE != 2) {
+      if (gather) {
+        launch_timed_lds(c, s, kind, k_fdm_row<R, NT, MODE, true>, G, wg, lds, a);
+        return;
+      }
+    }
+    launch_timed_lds(c, s, kind, k_fdm_row<R, NT, MODE, false>, G, wg, lds, a);
+  };
+  if (sh.nt == 1) launch(std::integral_constant<int, 1>{});
+  else if (sh.nt == 2) launch(std::integral_constant<int, 2>{});
+  else launch(std::integral_constant<int, 4>{});
 }
 
 template <typename R, int MODE>
@@ -836,7 +995,8 @@ FdmRow<R> row_args(piso_ctx* c, const Shape& sh, CgState* st) {
   a.ntiles = (a.rows + 16 * sh.nt - 1) / (16 * sh.nt);
   a.ld = a.kc * 16 + kFdmPad;
   a.quad = a.n % 4 == 0;
-  div_magic((uint32_t)(a.quad ? a.n / 4 : a.n), a.div_lo, a.div_hi, a.div_sh);
+  a.map = f.map;
+  a.rowfast = f.rowfast;
   a.vstride = (size_t)a.mt * a.kc * 256;
   a.sel = f.sel;
   a.st = st;
@@ -866,12 +1026,15 @@ FdmLine<R> line_args(piso_ctx* c) {
   return a;
 }
 
-// 32 columns a tile (whole 128-byte lines in FP32), 16 where the chip would not fill or two
+// 32 columns a tile (whole 128-byte lines in FP32), fewer where the chip would not fill or two
 // tiles of the line do not fit the LDS
 template <typename R>
 int line_cols(const FdmLine<R>& a) {
-  const bool fits = ((size_t)a.n * 2 * 33 + a.n) * sizeof(R) <= kFdmLds;
-  return fits && (long)a.slabs * ((a.cols + 31) / 32) >= 128 ? 32 : 16;
+  for (int tn : {32, 16}) {
+    const bool fits = line_lds<R>(a.n, tn) <= kFdmLds;
+    if (fits && (long)a.slabs * ((a.cols + tn - 1) / tn) >= 4 * tn) return tn;
+  }
+  return 8;
 }
 
 // The products and solves between the two products along x: transformed field in c->k_y,
@@ -919,10 +1082,11 @@ int middle(piso_ctx* c, hipStream_t s, CgState* st, R** res) {
     l.out = v;
     l.st = st;
     const int tn = line_cols(l);
-    const size_t lds = ((size_t)l.n * 2 * (tn + 1) + l.n) * sizeof(R);
+    const size_t lds = line_lds<R>(l.n, tn);
     const int G = l.slabs * ((l.cols + tn - 1) / tn);
     if (tn == 32) launch_timed_lds(c, s, kTimeMgCoarse, k_fdm_line<R, 32>, G, kWG, lds, l);
-    else launch_timed_lds(c, s, kTimeMgCoarse, k_fdm_line<R, 16>, G, kWG, lds, l);
+    else if (tn == 16) launch_timed_lds(c, s, kTimeMgCoarse, k_fdm_line<R, 16>, G, kWG, lds, l);
+    else launch_timed_lds(c, s, kTimeMgCoarse, k_fdm_line<R, 8>, G, kWG, lds, l);
     std::swap(u, v);
   } else {
     along(1);
@@ -984,13 +1148,25 @@ int fdm_build(piso_ctx* c, const piso_domain_desc* desc, const Topology& topo) {
     for (int m = 0; m < 3; ++m) {
       f.n[m] = p.n[m];
       f.wrap[m] = p.wrap[m];
+      f.perm[m] = p.perm[m];
+    }
+    if (!p.plain) {
+      f.rowfast = p.perm[0] != 0;
+      if (f.rowfast) {
+        const int nx = p.n[0], rows = c->N / nx;
+        std::vector<int> t(c->N);
+        for (int r = 0; r < rows; ++r)
+          for (int i = 0; i < nx; ++i) t[(size_t)i * rows + r] = p.cell[(size_t)r * nx + i];
+        p.cell.swap(t);
+      }
+      if (int rc = upload(c, (void**)&f.map, p.cell)) return rc;
     }
     if (int rc = c->prec == PISO_F64 ? upload_plan<double>(c, p) : upload_plan<float>(c, p)) return rc;
     // statistics: up to about 512 work-groups, at least a row segment per wave
     const int pa = f.line == 2 ? 2 : 1, oa = pa == 1 ? 2 : 1;
     f.planes = f.n[pa];
     const int units = f.n[oa] * ((f.n[0] + 63) / 64);
-    f.splits = std::max(1, std::min(512 / f.planes, (units + kWaves - 1) / kWaves));
+    f.splits = std::max(1, std::min({4, 512 / f.planes, (units + kWaves - 1) / kWaves}));
     if (int rc = dev_alloc(c, (void**)&f.stats,
                            sizeof(float) * kFdmRungs * kFdmStatValues * (size_t)f.planes * f.splits))
       return rc;
@@ -1022,11 +1198,14 @@ int fdm_setup(piso_ctx* c, hipStream_t s, const R* Pf) {
   a.stride[0] = 1;
   a.stride[1] = f.n[0];
   a.stride[2] = (size_t)f.n[0] * f.n[1];
+  a.map = f.map;
+  a.rowfast = f.rowfast;
   int3 faces;
   int* nf[3] = {&faces.x, &faces.y, &faces.z};
   for (int m = 0; m < 3; ++m) {
     a.n[m] = f.n[m];
     a.wrap[m] = f.wrap[m];
+    a.perm[m] = f.perm[m];
     for (int j = 0; j < 3; ++j) a.wt[j][m] = (const R*)f.wt[j][m];
     const int cells = c->N / f.n[a.pa];   // of a plane
     *nf[m] = m == a.pa || f.wrap[m] ? cells : cells / f.n[m] * (f.n[m] - 1);

@@ -2,6 +2,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <cstdlib>
 #include <numeric>
 #include <system_error>
 #include <thread>
@@ -69,7 +70,7 @@ namespace {
 // One axis, one rung: K from the cell factors kf (face weights their mean), weights D.
 bool axis_basis(const std::vector<double>& kf, const std::vector<double>& D, bool wrap, double* lam, double* V) {
   const int n = (int)kf.size();
-  if (wrap) {   // uniform: the real Fourier basis
+  if (wrap) {   // the real Fourier basis (kf and D constant)
     const double pi = 3.14159265358979323846;
     for (int k = 0; k < n; ++k) {
       const int f = (k + 1) / 2;   // frequencies 0, 1, 1, 2, 2, ...: cosines at odd k, sines at even
@@ -105,104 +106,245 @@ bool axis_basis(const std::vector<double>& kf, const std::vector<double>& D, boo
   return true;
 }
 
+// Places the blocks on the lattice of a box: extents, periodic axes and the cell of every
+// position.  False where they do not tile one, or a face is not where the box has it.
+bool logical_box(const piso_domain_desc* d, const Topology& topo, int n[3], bool wrap[3], std::vector<int>* cell) {
+  const int D = d->dim, B = d->n_blocks;
+  const int* tab = topo.tab.data();
+  auto ext = [&](int b, int m) { return tab[(size_t)b * kTabStride + 1 + m]; };
+  std::vector<int> off(3 * (size_t)B, 0), todo(1, 0);
+  std::vector<char> placed(B, 0);
+  int period[3] = {0, 0, 0};
+  placed[0] = 1;
+  while (!todo.empty()) {
+    const int b = todo.back();
+    todo.pop_back();
+    for (int s = 0; s < d->n_sides; ++s) {
+      const piso_side_desc& sd = d->sides[s];
+      if (sd.block != b || sd.kind != PISO_SIDE_CONNECT) continue;
+      const int o = sd.other_block, a = sd.side / 2;
+      int at[3], q = 0;
+      for (int m = 0; m < 3; ++m) {
+        at[m] = off[3 * b + m];
+        if (m != a && q < 2) {
+          at[m] += sd.begin[q] - sd.other_begin[q];
+          ++q;
+        }
+      }
+      at[a] += sd.side % 2 ? ext(b, a) : -ext(o, a);
+      if (!placed[o]) {
+        for (int m = 0; m < 3; ++m) off[3 * o + m] = at[m];
+        placed[o] = 1;
+        todo.push_back(o);
+        continue;
+      }
+      // a second way to a block: a period along one axis
+      int axis = -1, moved = 0;
+      for (int m = 0; m < 3; ++m)
+        if (at[m] != off[3 * o + m]) {
+          axis = m;
+          ++moved;
+        }
+      if (moved == 0) continue;
+      const int len = std::abs(at[axis] - off[3 * o + axis]);
+      if (moved > 1 || (period[axis] && period[axis] != len)) return false;
+      period[axis] = len;
+    }
+  }
+  for (int b = 0; b < B; ++b)
+    if (!placed[b]) return false;
+  long total = 1;
+  int lo[3];
+  for (int m = 0; m < 3; ++m) {
+    int hi = off[m] + ext(0, m);
+    lo[m] = off[m];
+    for (int b = 1; b < B; ++b) {
+      lo[m] = std::min(lo[m], off[3 * b + m]);
+      hi = std::max(hi, off[3 * b + m] + ext(b, m));
+    }
+    wrap[m] = period[m] > 0;
+    n[m] = wrap[m] ? period[m] : hi - lo[m];
+    if (n[m] < 1 || n[m] > topo.N) return false;
+    total *= n[m];
+    if (total > topo.N) return false;
+  }
+  if (total != topo.N) return false;
+  cell->assign(topo.N, -1);
+  std::vector<int> where(topo.N);   // position of each cell
+  for (int b = 0; b < B; ++b) {
+    int P = tab[(size_t)b * kTabStride];
+    for (int k = 0; k < ext(b, 2); ++k)
+      for (int j = 0; j < ext(b, 1); ++j)
+        for (int i = 0; i < ext(b, 0); ++i, ++P) {
+          const int x[3] = {off[3 * b] - lo[0] + i, off[3 * b + 1] - lo[1] + j, off[3 * b + 2] - lo[2] + k};
+          const int L = x[0] % n[0] + n[0] * (x[1] % n[1] + n[1] * (x[2] % n[2]));
+          if ((*cell)[L] >= 0) return false;
+          (*cell)[L] = P;
+          where[P] = L;
+        }
+  }
+  // every face of every block's side
+  const int st[3] = {1, n[0], n[0] * n[1]};
+  for (int b = 0; b < B; ++b)
+    for (int side = 0; side < 2 * D; ++side) {
+      const int* t = tab + (size_t)b * kTabStride;
+      const int a = side / 2, hi = side % 2;
+      int o[2], q = 0;
+      for (int m = 0; m < 3; ++m)
+        if (m != a && q < 2) o[q++] = m;
+      const int bs[3] = {1, ext(b, 0), ext(b, 0) * ext(b, 1)};
+      for (int v = 0, f = 0; v < ext(b, o[1]); ++v)
+        for (int u = 0; u < ext(b, o[0]); ++u, ++f) {
+          const int P = t[0] + (hi ? ext(b, a) - 1 : 0) * bs[a] + u * bs[o[0]] + v * bs[o[1]];
+          const int F = topo.fmap[(size_t)t[4 + side] + f];
+          const int x = where[P] / st[a] % n[a], y = hi ? x + 1 : x - 1;
+          if (F < 0) {
+            if (wrap[a] || (y >= 0 && y < n[a])) return false;
+          } else {
+            if (!wrap[a] && (y < 0 || y >= n[a])) return false;
+            if (where[F] != where[P] + ((y + n[a]) % n[a] - x) * st[a]) return false;
+          }
+        }
+    }
+  return true;
+}
+
 }  // namespace
 
 void fdm_plan(const piso_domain_desc* d, const Topology& topo, FdmPlan* plan) {
   plan->on = false;
   const int D = d->dim, N = topo.N;
-  if (d->n_blocks != 1 || N < 2) return;
-  const int* t = topo.tab.data();
+  if (N < 2) return;
+  int nb[3];
+  bool wb[3];
+  std::vector<int> box;
+  if (!logical_box(d, topo, nb, wb, &box)) return;
+  for (int m = 0; m < D; ++m)
+    if (nb[m] > kFdmMaxN) return;
+  plan->dim = D;
+  // the line axis: y where it has walls, else z, else x (then x and y change places: the
+  // line axis has to be strided in the box)
+  const int walls = !wb[1] ? 1 : (D == 3 && !wb[2] ? 2 : (!wb[0] ? 0 : -1));
+  if (walls == 0) std::swap(plan->perm[0], plan->perm[1]);
+  const int la = plan->line = walls == 0 ? 1 : walls;
   int n[3], stride[3];
-  for (int m = 0; m < 3; ++m) n[m] = t[1 + m];
+  for (int m = 0; m < 3; ++m) {
+    plan->n[m] = n[m] = nb[plan->perm[m]];
+    plan->wrap[m] = wb[plan->perm[m]];
+  }
   stride[0] = 1;
   stride[1] = n[0];
   stride[2] = n[0] * n[1];
-  plan->dim = D;
-  for (int m = 0; m < D; ++m) {
-    if (n[m] > kFdmMaxN) return;
-    const int w = (t[kTabWrap] >> (2 * m)) & 3;
-    if (w == 1 || w == 2) return;
-    plan->wrap[m] = w == 3;
-    if (w == 0) {
-      const int faces = N / n[m];
-      for (int sd = 0; sd < 2; ++sd)
-        for (int f = 0; f < faces; ++f)
-          if (topo.fmap[(size_t)t[4 + 2 * m + sd] + f] >= 0) return;
-    }
+  if (walls == 0) {
+    plan->cell.resize(N);
+    for (int k = 0, L = 0; k < n[2]; ++k)
+      for (int j = 0; j < n[1]; ++j)
+        for (int i = 0; i < n[0]; ++i, ++L) plan->cell[L] = box[j + nb[0] * (i + nb[1] * k)];
+  } else {
+    plan->cell.swap(box);
   }
-  for (int m = 0; m < 3; ++m) plan->n[m] = n[m];
-  // the line axis: y where it has walls, else z
-  const int la = plan->line = !plan->wrap[1] ? 1 : (D == 3 && !plan->wrap[2] ? 2 : -1);
-  // alpha_jj on the three mid-lines, then the test that it is their product everywhere
-  auto alpha = [&](int j, size_t P) {
+  plan->plain = true;
+  for (int L = 0; L < N && plan->plain; ++L) plan->plain = plan->cell[L] == L;
+  // alpha_jj by box axis and position
+  auto alpha = [&](int j, int L) {
+    const size_t P = plan->cell[L];
+    const double* T = d->T + (size_t)plan->perm[j] * D * N + P;
     double s = 0.0;
-    for (int i = 0; i < D; ++i) {
-      const double v = d->T[(size_t)(j * D + i) * N + P];
-      s += v * v;
-    }
+    for (int i = 0; i < D; ++i) s += T[(size_t)i * N] * T[(size_t)i * N];
     return d->J[P] * s;
   };
-  size_t mid = 0;
-  for (int m = 0; m < D; ++m) mid += (size_t)(n[m] / 2) * stride[m];
+  // up to 24 points of every axis, both ends' neighbourhoods among them
+  std::vector<int> pick[3];
+  for (int m = 0; m < 3; ++m) {
+    const int c = std::min(n[m], 24);
+    for (int u = 0; u < c; ++u) pick[m].push_back((int)((2L * u + 1) * n[m] / (2 * c)));
+  }
+  // f[j][m]: factor of alpha_jj along m, cj its scale (means of the logarithm); g[m]: the
+  // faces of axis m in the diagonal of the diffusion (walls: 2 alpha), per volume
   std::vector<double> f[3][3], g[3];
-  double cj[3] = {0, 0, 0};
-  for (int j = 0; j < D; ++j) {
-    cj[j] = alpha(j, mid);
-    if (!(cj[j] > 0.0) || !std::isfinite(cj[j])) return;
-    for (int m = 0; m < D; ++m) {
-      f[j][m].resize(n[m]);
-      for (int i = 0; i < n[m]; ++i) {
-        f[j][m][i] = alpha(j, mid + ((long)i - n[m] / 2) * stride[m]) / cj[j];
-        if (!(f[j][m][i] > 0.0) || !std::isfinite(f[j][m][i])) return;
-      }
-    }
-  }
-  // (a tolerance well above rounding: the basis only preconditions)
-  const double tol = 1e-8;
-  for (int k = 0, P = 0; k < n[2]; ++k)
-    for (int jj = 0; jj < n[1]; ++jj) {
-      double row[3];
-      for (int j = 0; j < D; ++j) row[j] = cj[j] * f[j][1][jj] * (D == 3 ? f[j][2][k] : 1.0);
-      for (int i = 0; i < n[0]; ++i, ++P)
-        for (int j = 0; j < D; ++j) {
-          const double v = row[j] * f[j][0][i];
-          if (!(std::fabs(alpha(j, P) - v) <= tol * v)) return;
-        }
-    }
-  // the weights of an axis with a basis have to be the same in every other direction's term
-  for (int m = 0; m < D && D == 3; ++m) {
-    if (m == la) continue;
-    const int j0 = m == 0 ? 1 : 0, j1 = m == 2 ? 1 : 2;
-    for (int i = 0; i < n[m]; ++i)
-      if (!(std::fabs(f[j0][m][i] - f[j1][m][i]) <= tol * f[j0][m][i])) return;
-  }
-  // g_m(i): the faces of axis m in the diagonal of the diffusion (walls: 2 alpha), per volume
-  double gmax = 0.0;
+  double cj[3] = {1, 1, 1}, gmax = 0.0;
   bool shape = false;
   for (int m = 0; m < D; ++m) {
-    g[m].resize(n[m]);
-    double lo = 0.0, hi = 0.0;
-    for (int i = 0; i < n[m]; ++i) {
-      const double own = f[m][m][i];
-      double s = 0.0;
-      for (int sd = -1; sd <= 1; sd += 2) {
-        int r = i + sd;
-        if (plan->wrap[m]) r = (r + n[m]) % n[m];
-        s += r < 0 || r >= n[m] ? 2.0 * own : 0.5 * (own + f[m][m][r]);
-      }
-      g[m][i] = cj[m] * s / d->J[mid + ((long)i - n[m] / 2) * stride[m]];
-      lo = i ? std::min(lo, g[m][i]) : g[m][i];
-      hi = std::max(hi, g[m][i]);
-    }
-    if (!std::isfinite(hi)) return;
-    if (plan->wrap[m]) {   // Fourier basis: uniform axes only
-      for (int i = 0; i < n[m]; ++i)
-        for (int j = 0; j < D; ++j)
-          if (!(std::fabs(f[j][m][i] - f[j][m][0]) <= tol * f[j][m][0])) return;
-    } else if (m != la && hi > 1.05 * lo) {
-      shape = true;
+    const int o0 = m == 0 ? 1 : 0, o1 = m == 2 ? 1 : 2;
+    const std::vector<int> one(1, 0);
+    const std::vector<int>&p0 = pick[o0], &p1 = D == 3 ? pick[o1] : one;
+    const double cnt = (double)p0.size() * p1.size();
+    g[m].assign(n[m], 0.0);
+    for (int j = 0; j < D; ++j) f[j][m].assign(n[m], 0.0);
+    for (int i = 0; i < n[m]; ++i)
+      for (int u : p0)
+        for (int v : p1) {
+          const int L = i * stride[m] + u * stride[o0] + (D == 3 ? v * stride[o1] : 0);
+          for (int j = 0; j < D; ++j) f[j][m][i] += std::log(alpha(j, L)) / cnt;
+          const double own = alpha(m, L);
+          double s = 0.0;
+          for (int sd = -1; sd <= 1; sd += 2) {
+            int r = i + sd;
+            if (plan->wrap[m]) r = (r + n[m]) % n[m];
+            s += r < 0 || r >= n[m] ? 2.0 * own : 0.5 * (own + alpha(m, L + (r - i) * stride[m]));
+          }
+          g[m][i] += s / d->J[plan->cell[L]] / cnt;
+        }
+    double lo = g[m][0], hi = g[m][0];
+    for (double v : g[m]) {
+      lo = std::min(lo, v);
+      hi = std::max(hi, v);
     }
     gmax += hi;
+    if (m != la && !plan->wrap[m] && hi > 1.05 * lo) shape = true;
+    for (int j = 0; j < D; ++j) {
+      double mean = 0.0;
+      for (double v : f[j][m]) mean += v / n[m];
+      if (m == 0) cj[j] = std::exp(mean);
+      for (double& v : f[j][m]) {
+        v = plan->wrap[m] && m != la ? 1.0 : std::exp(v - mean);   // Fourier basis: constant factors
+        if (!(v > 0.0) || !std::isfinite(v)) return;
+      }
+      if (!(cj[j] > 0.0) || !std::isfinite(cj[j])) return;
+    }
+  }
+  if (!std::isfinite(gmax)) return;
+  // weights of an axis with a basis: one for all other directions' terms
+  std::vector<double> w[3];
+  for (int m = 0; m < D; ++m) {
+    w[m].assign(n[m], 1.0);
+    for (int i = 0; i < n[m]; ++i) {
+      double l = 0.0;
+      for (int j = 0; j < D; ++j)
+        if (j != m) l += std::log(f[j][m][i]) / (D - 1);
+      w[m][i] = std::exp(l);
+    }
+  }
+  // spread of the metric's face weights about the product, relative to the plane means
+  {
+    const int pa = la >= 0 ? la : 1;
+    const int cells = N / n[pa];
+    std::vector<double> v(3 * (size_t)n[pa] * 3, 0.0);   // [plane][term][min, max, sum]
+    for (int q = 0; q < 3 * n[pa]; ++q) v[3 * (size_t)q] = HUGE_VAL;
+    for (int k = 0, L = 0; k < n[2]; ++k)
+      for (int jj = 0; jj < n[1]; ++jj)
+        for (int i = 0; i < n[0]; ++i, ++L) {
+          const int x[3] = {i, jj, k};
+          double* pv = &v[(size_t)x[pa] * 9];
+          for (int j = 0; j < D; ++j) {
+            double m0 = cj[j];
+            for (int m = 0; m < D; ++m)
+              if (m != la) m0 *= m == j ? f[m][m][x[m]] : w[m][x[m]];
+            const double r = alpha(j, L) / m0;
+            pv[3 * j] = std::min(pv[3 * j], r);
+            pv[3 * j + 1] = std::max(pv[3 * j + 1], r);
+            pv[3 * j + 2] += r / cells;
+          }
+        }
+    double lo = HUGE_VAL, hi = 0.0;
+    for (int pl = 0; pl < n[pa]; ++pl)
+      for (int j = 0; j < D; ++j) {
+        const double* pv = &v[(size_t)pl * 9 + 3 * j];
+        const double mean = la >= 0 ? pv[2] : 1.0;
+        lo = std::min(lo, pv[0] / mean);
+        hi = std::max(hi, pv[1] / mean);
+      }
+    if (!(hi <= kFdmMaxShape * lo) || !(lo > 0.0)) return;
   }
   plan->rungs = shape ? kFdmRungs : 1;
   const int Q = plan->rungs;
@@ -223,30 +365,24 @@ void fdm_plan(const piso_domain_desc* d, const Topology& topo, FdmPlan* plan) {
     const double s = kFdmLadder[q] / gmax;
     for (int m = 0; m < D; ++m) {
       if (m == la) continue;
-      // a_m: mean of log 1 / (1 + s g) over the other axes, up to 24 points of each
+      // a_m: mean of log 1 / (1 + s g) over the other axes
       std::vector<double> a(n[m], 1.0);
       if (s > 0.0 && !plan->wrap[m]) {
         const int o0 = m == 0 ? 1 : 0, o1 = m == 2 ? 1 : 2;
-        const int c0 = std::min(n[o0], 24), c1 = D == 3 ? std::min(n[o1], 24) : 1;
         double mean = 0.0;
         for (int i = 0; i < n[m]; ++i) {
           double l = 0.0;
-          for (int u = 0; u < c0; ++u)
-            for (int v = 0; v < c1; ++v) {
-              const double g0 = g[o0][(int)((2L * u + 1) * n[o0] / (2 * c0))];
-              const double g1 = D == 3 ? g[o1][(int)((2L * v + 1) * n[o1] / (2 * c1))] : 0.0;
-              l -= std::log(1.0 + s * (g[m][i] + g0 + g1));
-            }
-          a[i] = l / ((double)c0 * c1);
+          for (int u : pick[o0])
+            for (int v : pick[o1]) l -= std::log(1.0 + s * (g[m][i] + g[o0][u] + (D == 3 ? g[o1][v] : 0.0)));
+          a[i] = l / ((double)pick[o0].size() * pick[o1].size());
           mean += a[i] / n[m];
         }
         for (double& v : a) v = std::exp(v - mean);
       }
-      const int other = m == 0 ? 1 : 0;
       Job job{m, q, std::vector<double>(n[m]), std::vector<double>(n[m]), false};
       for (int i = 0; i < n[m]; ++i) {
         job.kf[i] = cj[m] * f[m][m][i] * a[i];
-        job.D[i] = f[other][m][i] * a[i];
+        job.D[i] = w[m][i] * a[i];
         for (int j = 0; j < D; ++j) plan->wt[j][m][(size_t)q * n[m] + i] = job.D[i];
       }
       for (int i = 0; i < n[m]; ++i) {

@@ -165,7 +165,9 @@ struct FdmSel {
 };
 struct FdmState {
   bool on = false;
-  int rungs = 1, n[3] = {1, 1, 1}, wrap[3] = {0, 0, 0}, line = -1;
+  int rungs = 1, n[3] = {1, 1, 1}, wrap[3] = {0, 0, 0}, perm[3] = {0, 1, 2}, line = -1;
+  int* map = nullptr;      // cell of each position of the box (null: the same): [row][n[0]], or,
+  int rowfast = 0;         // where the rows and not x are contiguous in memory, [n[0]][row]
   void *fwd[3] = {}, *inv[3] = {}, *lam[3] = {}, *wt[3][3] = {};
   void* hat = nullptr;     // second transformed field [N] (the first is piso_ctx::k_y)
   void* piv = nullptr;     // reciprocal pivots of the line systems [N]

@@ -87,8 +87,88 @@ static std::vector<double> stretched(int n) {
   return w;
 }
 
+// 2D layouts of unit cells: blocks as {nx, ny}, connections as {block, side, begin, end,
+// other, other begin} (both directions listed), every other side Dirichlet.
+struct Join { int b, side, t0, t1, o, ot0; };
+static bool layout(std::vector<std::vector<int>> blocks, std::vector<Join> joins, FdmPlan* p, int* n0, int* n1) {
+  std::vector<int> cells;
+  std::vector<piso_side_desc> sides;
+  size_t N = 0;
+  for (size_t b = 0; b < blocks.size(); ++b) {
+    cells.insert(cells.end(), {blocks[b][0], blocks[b][1], 1});
+    N += (size_t)blocks[b][0] * blocks[b][1];
+    for (int s = 0; s < 4; ++s) {
+      bool any = false;
+      for (const Join& j : joins) {
+        if (j.b != (int)b || j.side != s) continue;
+        any = true;
+        piso_side_desc d{};
+        d.block = j.b;
+        d.side = s;
+        d.kind = PISO_SIDE_CONNECT;
+        d.begin[0] = j.t0;
+        d.end[0] = j.t1;
+        d.end[1] = 1;
+        d.other_block = j.o;
+        d.other_begin[0] = j.ot0;
+        sides.push_back(d);
+      }
+      if (any) continue;
+      piso_side_desc d{};
+      d.block = (int)b;
+      d.side = s;
+      d.kind = PISO_SIDE_DIRICHLET;
+      d.end[0] = blocks[b][1 - s / 2];
+      d.end[1] = 1;
+      sides.push_back(d);
+    }
+  }
+  std::vector<double> T(4 * N, 0.0), J(N, 1.0);
+  for (size_t P = 0; P < N; ++P) T[P] = T[3 * N + P] = 1.0;
+  piso_domain_desc d{};
+  d.dim = 2;
+  d.n_blocks = (int)blocks.size();
+  d.n_sides = (int)sides.size();
+  d.block_cells = cells.data();
+  d.sides = sides.data();
+  d.T = T.data();
+  d.J = J.data();
+  Topology t;
+  std::string err;
+  CHECK(build_topology(&d, &t, &err) == PISO_OK, "%s", err.c_str());
+  *p = FdmPlan();
+  fdm_plan(&d, t, p);
+  *n0 = p->n[0];
+  *n1 = p->n[1];
+  return p->on;
+}
+
 int main() {
   FdmPlan p;
+  int n0 = 0, n1 = 0;
+  // two blocks side by side; the same joined at both ends (periodic)
+  CHECK(layout({{4, 3}, {6, 3}}, {{0, 1, 0, 3, 1, 0}, {1, 0, 0, 3, 0, 0}}, &p, &n0, &n1) && n0 == 10 && n1 == 3 &&
+        p.cell[4] == 12 && !p.wrap[0], "two blocks");
+  CHECK(layout({{4, 3}, {6, 3}}, {{0, 1, 0, 3, 1, 0}, {1, 0, 0, 3, 0, 0}, {1, 1, 0, 3, 0, 0}, {0, 0, 0, 3, 1, 0}}, &p,
+               &n0, &n1) && n0 == 10 && p.wrap[0] && p.line == 1, "two blocks, periodic");
+  // an annulus of 5 x 8 with four blocks of 3 x 2 around it (perm: theta becomes the first axis)
+  std::vector<Join> oh = {{0, 2, 0, 5, 0, 0}, {0, 3, 0, 5, 0, 0}};
+  for (int k = 0; k < 4; ++k) {
+    oh.push_back({0, 1, 2 * k, 2 * k + 2, 1 + k, 0});
+    oh.push_back({1 + k, 0, 0, 2, 0, 2 * k});
+    oh.push_back({1 + k, 2, 0, 3, 1 + (k + 3) % 4, 0});
+    oh.push_back({1 + k, 3, 0, 3, 1 + (k + 1) % 4, 0});
+  }
+  CHECK(layout({{5, 8}, {3, 2}, {3, 2}, {3, 2}, {3, 2}}, oh, &p, &n0, &n1) && n0 == 8 && n1 == 8 && p.wrap[0] &&
+        !p.wrap[1] && p.cell[8 * 5 + 2] == 40 + 6, "annulus and transition blocks");
+  // three blocks in an L
+  CHECK(!layout({{4, 4}, {4, 4}, {4, 4}}, {{0, 1, 0, 4, 1, 0}, {1, 0, 0, 4, 0, 0}, {0, 3, 0, 4, 2, 0}, {2, 2, 0, 4, 0, 0}},
+                &p, &n0, &n1), "L of three blocks");
+  // four blocks around a point, one pair not joined (a slit inside the box)
+  CHECK(!layout({{4, 4}, {4, 4}, {4, 4}, {4, 4}},
+                {{0, 1, 0, 4, 1, 0}, {1, 0, 0, 4, 0, 0}, {0, 3, 0, 4, 2, 0}, {2, 2, 0, 4, 0, 0}, {1, 3, 0, 4, 3, 0},
+                 {3, 2, 0, 4, 1, 0}}, &p, &n0, &n1), "slit");
+  p = FdmPlan();
   CHECK(plan_of({uniform(12, .5), stretched(17), uniform(9, .3)}, 5, 1.0, &p) && p.rungs == 1 && p.line == 1, "channel");
   diagonal(p);
   p = FdmPlan();
@@ -98,7 +178,8 @@ int main() {
   CHECK(plan_of({stretched(9), uniform(8, .5), stretched(33)}, 2, 1.0, &p) && p.line == 2, "lines along z");
   diagonal(p);
   p = FdmPlan();
-  CHECK(plan_of({stretched(33), uniform(8, .5)}, 2, 1.0, &p) && p.line == -1 && p.rungs == kFdmRungs, "no line axis");
+  CHECK(plan_of({stretched(33), uniform(8, .5)}, 2, 1.0, &p) && p.line == 1 && p.perm[0] == 1 && !p.plain &&
+        p.n[0] == 8 && p.cell[1] == 33, "x and y exchanged");
   diagonal(p);
   p = FdmPlan();
   CHECK(plan_of({uniform(6, .5), uniform(1, .5), uniform(2, 1.0)}, 7, 1.0, &p) && p.rungs == 1 && p.line == -1, "box");
@@ -108,9 +189,9 @@ int main() {
   p = FdmPlan();
   CHECK(!plan_of({uniform(kFdmMaxN + 1, .5), uniform(2, .5)}, 1, 1.0, &p), "too long");
   p = FdmPlan();
-  CHECK(!plan_of({stretched(8), uniform(8, .5)}, 3, 1.0, &p), "stretched periodic axis");
+  CHECK(plan_of({uniform(8, .5), stretched(8)}, 1, 1.5, &p), "nearly a product");
   p = FdmPlan();
-  CHECK(!plan_of({uniform(8, .5), stretched(8)}, 1, 1.001, &p), "no tensor product");
+  CHECK(!plan_of({uniform(8, .5), stretched(8)}, 1, 400.0, &p), "no product");
   std::printf("%s (%d failures)\n", failures ? "FAILED" : "passed", failures);
   return failures != 0;
 }

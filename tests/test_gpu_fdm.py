@@ -43,6 +43,41 @@ SHAPES = [((32, 32, 17), (0, 2)), ((33, 37, 15), (0,)), ((16, 48, 24), ()), ((18
           ((70, 30), (1,))]
 
 
+def _blocks():
+    """Layouts that are a box cut into blocks: the cylinder's O-H grid (theta becomes the
+    box's first axis, gathered through the map), and 3D channels cut in two along x (rows of
+    two blocks) and along y."""
+    out = {"cylinder": cases.cylinder_oh(32, 9, 7), "cylinder_q": cases.cylinder_oh(64, 24, 12)}
+    for axis in (0, 1):
+        whole = _case((28, 30, 23), (0, 2))
+        dims = [28, 30, 23]
+        cut = 11
+        parts, blocks = [], []
+        idx = np.arange(whole.domain.n_cells).reshape(23, 30, 28)
+        for sl in (slice(0, cut), slice(cut, dims[axis])):
+            pick = [slice(None)] * 3
+            pick[2 - axis] = sl
+            c = idx[tuple(pick)]
+            parts.append(c.ravel())
+            blocks.append(tuple(c.shape[::-1]))
+        order = np.concatenate(parts)
+        sides = []
+        for b in range(2):
+            for a in range(3):
+                for s in (0, 1):
+                    if a == axis and (axis == 0 or s == 1 - b):
+                        sides.append(cases.Side(b, 2 * a + s, cases.CONNECT, other_block=1 - b))
+                    elif a == 1:
+                        sides.append(cases.Side(b, 2 * a + s, cases.DIRICHLET))
+                    else:
+                        sides.append(cases.Side(b, 2 * a + s, cases.CONNECT, other_block=b))
+        dom = cases.Domain(3, blocks, sides, whole.domain.T[:, :, order], whole.domain.J[order])
+        n = dom.n_cells
+        out["cut%d" % axis] = cases.Case("cut", dom, np.zeros((3, n)), np.zeros(n), np.zeros((3, n)), 0.01, 0.01,
+                                         cases.boundary_values(dom, lambda si: np.zeros(3)), 1)
+    return out
+
+
 def _run(ctx, case, state, opts):
     u, p, S, ub, nu = state
     t = ctx.dtype
@@ -55,17 +90,17 @@ def _run(ctx, case, state, opts):
 
 
 @pytest.mark.parametrize("prec", ["f64", "mixed", "f32"])
-@pytest.mark.parametrize("dims,periodic", SHAPES)
+@pytest.mark.parametrize("dims,periodic", SHAPES + [(n, None) for n in ("cylinder", "cylinder_q", "cut0", "cut1")])
 def test_step_and_adjoint(dims, periodic, prec, monkeypatch):
     """Against the oracle (F64 and MIXED at 1e-12, F32 at its defaults), with
     fewer iterations than the V-cycle needs on the same system."""
     api = _api()
     say(dims, periodic, prec)
-    case = _case(dims, periodic)
+    case = _blocks()[dims] if periodic is None else _case(dims, periodic)
     state = random_state(case, seed=71)
     geo = Geometry(case.domain)
     u, p, S, ub, nu = [x.astype(np.float32).astype(np.float64) for x in state] if prec == "f32" else state
-    how = dict(mode="iterative", rtol=1e-13) if len(dims) == 3 else {}   # direct solves in 2D
+    how = dict(mode="iterative", rtol=1e-13) if case.domain.dim == 3 else {}   # direct solves in 2D
     ref = oracle_step(geo, u, p, nu, S, case.dt, ub, **how)
     iters = []
     for env in (None, "0"):
