@@ -28,6 +28,7 @@
 // a Dirichlet face giving the ghost 2 phi_b - phi_P (or phi_P when no face values are
 // given: the step's pressure gradient).
 #include <string>
+#include <type_traits>
 
 #include "piso_impl.h"
 
@@ -87,10 +88,10 @@ __device__ __forceinline__ double ipow(double x, int k) {
   return r;
 }
 
-__device__ __forceinline__ int binom(int n, int k) {
-  int r = 1;
-  for (int q = 1; q <= k; ++q) r = r * (n - k + q) / q;
-  return r;
+// C(n, k) for n <= 4
+__device__ __forceinline__ double binom4(int n, int k) {
+  if (k == 0 || k == n) return 1.0;
+  return n == 4 && k == 2 ? 6.0 : (double)n;
 }
 
 // Index of the multi-index with exponents e in the table (-1 if its order is below 2).
@@ -105,92 +106,159 @@ __device__ __forceinline__ int mom_find(const MomTab& t, int M, const int* e) {
 
 }  // namespace
 
-template <typename R, int M>
-__global__ void __launch_bounds__(kWG)
+// The multi-indices of M variables up to order K as constants, in momtab's order.
+struct MomTuples {
+  int n = 0;
+  signed char tup[kMomMaxAlpha][4] = {};
+};
+
+template <int M, int K>
+constexpr MomTuples mom_tuples() {
+  MomTuples t;
+  for (int o = 2; o <= K; ++o) {
+    int idx[4] = {0, 0, 0, 0};
+    for (bool more = true; more;) {
+      for (int q = 0; q < 4; ++q) t.tup[t.n][q] = q < o ? (signed char)idx[q] : (signed char)-1;
+      ++t.n;
+      int q = o - 1;
+      while (q >= 0 && idx[q] == M - 1) --q;
+      more = q >= 0;
+      if (more) {
+        ++idx[q];
+        for (int r = q + 1; r < o; ++r) idx[r] = idx[q];
+      }
+    }
+  }
+  return t;
+}
+
+// One work-group of 1024 threads per plane: a plane's samples are read twice (mean, central
+// sums), the second time mostly from the caches, so what counts is loads in flight on the
+// few CUs that have a plane, and the merge, which one thread did over all pairs of
+// multi-indices with a table in memory.  Now a thread per multi-index merges, the products
+// are unrolled from constants, and each thread has four samples' loads in flight: on 96
+// planes of 96^2 FP64 samples three variables to order 4 take 40 us (181 before), to order 2
+// 17 us (181), six variables to order 2 43 us (246).
+constexpr int kMomWG = 1024;
+
+template <typename R, int M, int K>
+__global__ void __launch_bounds__(kMomWG)
 k_mom_acc(const R* __restrict__ x, int N, int nx, int ny, int ms, int axis, MomTab tab,
           double* __restrict__ state) {
-  const int p = blockIdx.x;
-  const int NA = tab.n;
-  const int REC = 1 + M + NA;
+  constexpr MomTuples T = mom_tuples<M, K>();
+  constexpr int NA = T.n, REC = 1 + M + NA, W = kMomWG / 64, U = 4;
+  __shared__ double lds[(NA > M ? NA : M) * W];
+  __shared__ double mu[M], sb[NA], old[REC], powA[M][K + 1], powB[M][K + 1];
+  const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  double* rec = state + (size_t)p * REC;
+  if (tid < REC) old[tid] = rec[tid];
+  // sum of each value over the work-group in a fixed order, into out
+  auto reduce = [&](auto& v, auto count, double* out) {
+    constexpr int NV = decltype(count)::value;
+#pragma unroll
+    for (int q = 0; q < NV; ++q) {
+      const double t = wave_sum(v[q]);
+      if (lane == 0) lds[q * W + wave] = t;
+    }
+    __syncthreads();
+    if (tid < NV) {
+      double t = 0.0;
+      for (int w = 0; w < W; ++w) t += lds[tid * W + w];
+      out[tid] = t;
+    }
+    __syncthreads();
+  };
   double s1[M];
 #pragma unroll
   for (int i = 0; i < M; ++i) s1[i] = 0.0;
-  for (int t = threadIdx.x; t < ms; t += kWG) {
-    const int P = plane_cell_m(axis, p, t, nx, ny);
+  for (int t0 = tid; t0 < ms; t0 += U * kMomWG) {
+    R v[U][M];
 #pragma unroll
-    for (int i = 0; i < M; ++i) s1[i] += (double)x[(size_t)i * N + P];
+    for (int u = 0; u < U; ++u) {
+      const int P = plane_cell_m(axis, p, min(t0 + u * kMomWG, ms - 1), nx, ny);
+#pragma unroll
+      for (int i = 0; i < M; ++i) v[u][i] = x[(size_t)i * N + P];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (t0 + u * kMomWG >= ms) continue;
+#pragma unroll
+      for (int i = 0; i < M; ++i) s1[i] += (double)v[u][i];
+    }
   }
-  wg_sum_all<M>(s1);
+  reduce(s1, std::integral_constant<int, M>{}, mu);
   double mu_b[M];
 #pragma unroll
-  for (int i = 0; i < M; ++i) mu_b[i] = s1[i] / ms;
-  double s2[kMomMaxAlpha];
+  for (int i = 0; i < M; ++i) mu_b[i] = mu[i] / ms;
+  double s2[NA];
 #pragma unroll
-  for (int q = 0; q < kMomMaxAlpha; ++q) s2[q] = 0.0;
-  for (int t = threadIdx.x; t < ms; t += kWG) {
-    const int P = plane_cell_m(axis, p, t, nx, ny);
-    double dv[M];
+  for (int q = 0; q < NA; ++q) s2[q] = 0.0;
+  for (int t0 = tid; t0 < ms; t0 += 2 * kMomWG) {
+    R v[2][M];
 #pragma unroll
-    for (int i = 0; i < M; ++i) dv[i] = (double)x[(size_t)i * N + P] - mu_b[i];
+    for (int u = 0; u < 2; ++u) {
+      const int P = plane_cell_m(axis, p, min(t0 + u * kMomWG, ms - 1), nx, ny);
 #pragma unroll
-    for (int q = 0; q < kMomMaxAlpha; ++q) {
-      if (q < NA) {
+      for (int i = 0; i < M; ++i) v[u][i] = x[(size_t)i * N + P];
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      if (t0 + u * kMomWG >= ms) continue;
+      double dv[M];
+#pragma unroll
+      for (int i = 0; i < M; ++i) dv[i] = (double)v[u][i] - mu_b[i];
+#pragma unroll
+      for (int q = 0; q < NA; ++q) {
         double pr = 1.0;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int v = tab.tup[q][r];
-          if (v >= 0) pr *= dv[v];
-        }
+        for (int r = 0; r < 4; ++r)
+          if (T.tup[q][r] >= 0) pr *= dv[T.tup[q][r] < 0 ? 0 : T.tup[q][r]];
         s2[q] += pr;
       }
     }
   }
-  __shared__ double lds[kMomMaxAlpha * kWaves];
-  wg_sum<kMomMaxAlpha>(s2, lds);
-  if (threadIdx.x != 0) return;
-  double* rec = state + (size_t)p * REC;
-  const double nA = rec[0], nB = (double)ms, n = nA + nB;
-  double delta[M], cA[M], cB[M];
-#pragma unroll
-  for (int i = 0; i < M; ++i) {
-    delta[i] = mu_b[i] - rec[1 + i];
-    cA[i] = -delta[i] * (nB / n);
-    cB[i] = delta[i] * (nA / n);
-  }
-  double out[kMomMaxAlpha];
-  for (int q = 0; q < NA; ++q) {
-    // sum over beta <= alpha: beta = 0, then every table entry (order >= 2) below alpha;
-    // order-1 betas contribute nothing (central sums of order 1 vanish)
-    double acc = nA * 1.0, accB = nB * 1.0;
-    {
-      double pa = 1.0, pb = 1.0;
-      for (int v = 0; v < M; ++v) {
-        pa *= ipow(cA[v], tab.e[q][v]);
-        pb *= ipow(cB[v], tab.e[q][v]);
-      }
-      acc *= pa;
-      accB *= pb;
+  if (tid < M) {   // powers of the two shifts; read after the reduction's barriers
+    const double nA = old[0], nB = (double)ms, delta = mu[tid] / ms - old[1 + tid];
+    const double cA = -delta * (nB / (nA + nB)), cB = delta * (nA / (nA + nB));
+    double a = 1.0, b = 1.0;
+    for (int k = 0; k <= K; ++k, a *= cA, b *= cB) {
+      powA[tid][k] = a;
+      powB[tid][k] = b;
     }
-    double sum = acc + accB;
-    for (int b = 0; b < NA; ++b) {
-      bool le = true;
-      for (int v = 0; v < M; ++v) le &= tab.e[b][v] <= tab.e[q][v];
-      if (!le) continue;
-      double c = 1.0, pa = 1.0, pb = 1.0;
-      for (int v = 0; v < M; ++v) {
-        const int a = tab.e[q][v], bb = tab.e[b][v];
-        c *= binom(a, bb);
-        pa *= ipow(cA[v], a - bb);
-        pb *= ipow(cB[v], a - bb);
-      }
-      sum += c * (rec[1 + M + b] * pa + s2[b] * pb);
-    }
-    out[q] = sum;
   }
-  for (int q = 0; q < NA; ++q) rec[1 + M + q] = out[q];
+  reduce(s2, std::integral_constant<int, NA>{}, sb);
+  if (tid >= NA) return;
+  // thread q merges multi-index q: beta = 0, then every table entry (order >= 2) below alpha;
+  // order-1 betas contribute nothing (central sums of order 1 vanish)
+  const int q = tid;
+  const double nB = (double)ms, n = old[0] + nB;
+  double pa0 = 1.0, pb0 = 1.0;
+  int eq[M];
 #pragma unroll
-  for (int i = 0; i < M; ++i) rec[1 + i] += delta[i] * (nB / n);
-  rec[0] = n;
+  for (int v = 0; v < M; ++v) {
+    eq[v] = tab.e[q][v];
+    pa0 *= powA[v][eq[v]];
+    pb0 *= powB[v][eq[v]];
+  }
+  double sum = old[0] * pa0 + nB * pb0;
+  for (int b = 0; b < NA; ++b) {
+    bool le = true;
+#pragma unroll
+    for (int v = 0; v < M; ++v) le &= tab.e[b][v] <= eq[v];
+    if (!le) continue;
+    double c = 1.0, pa = 1.0, pb = 1.0;
+#pragma unroll
+    for (int v = 0; v < M; ++v) {
+      const int k = eq[v] - tab.e[b][v];
+      c *= binom4(eq[v], k);
+      pa *= powA[v][k];
+      pb *= powB[v][k];
+    }
+    sum += c * (old[1 + M + b] * pa + sb[b] * pb);
+  }
+  rec[1 + M + q] = sum;
+  if (q < M) rec[1 + q] = old[1 + q] + (mu[q] / ms - old[1 + q]) * (nB / n);
+  if (q == 0) rec[0] = n;
 }
 
 __global__ void __launch_bounds__(kWG)
@@ -289,27 +357,45 @@ k_field_grad(Grid g, const R* __restrict__ JT, const R* __restrict__ invJ, const
   }
 }
 
-// Budget terms per plane (one thread per plane) from the accumulated states: su (m = d,
-// order >= 3, table tu), sg[k] (m = d, order 2; k = 0 .. d-1, each REC_g long per plane),
-// sup (m = 2d, order 2, table tp).  Planes normal to axis a; tmet[p] = T_aa and jm[p] = J
-// of the plane.  out[term][p][pair], terms P, eps, T, D, Pi.
+// Budget terms from the accumulated states, one thread per plane and pair (one per plane
+// took 65 us for 96 planes, a chain of table searches; now 20): su (m = d, order >= 3, table tu),
+// sg[k] (m = d, order 2; k = 0 .. d-1, each REC_g long per plane), sup (m = 2d, order 2,
+// table tp).  Planes normal to axis a; tmet[p] = T_aa and jm[p] = J of the plane.
+// out[term][p][pair], terms P, eps, T, D, Pi.
+__device__ __forceinline__ int mom_find3(const MomTab& t, int i, int j, int k) {   // k < 0: a pair
+  int x = i < j ? i : j, y = i < j ? j : i, z = k;
+  if (z >= 0) {   // sorted
+    if (z < x) { const int w = x; x = z; z = y; y = w; }
+    else if (z < y) { const int w = y; y = z; z = w; }
+  }
+  for (int q = 0; q < t.n; ++q)
+    if (t.tup[q][0] == x && t.tup[q][1] == y && t.tup[q][2] == z && t.tup[q][3] < 0) return q;
+  return 0;   // not reached: every pair and (order >= 3) triple is in the table
+}
+
 template <int D>
 __global__ void __launch_bounds__(kWG)
 k_budget(int np, int a, int periodic, MomTab tu, MomTab tg, MomTab tp, const double* __restrict__ su,
          const double* __restrict__ sg, const double* __restrict__ sup, const double* __restrict__ tmet,
          const double* __restrict__ jm, double wl0, double wl1, double wl2, double wh0, double wh1, double wh2,
          double* __restrict__ out) {
-  const int p = blockIdx.x * kWG + threadIdx.x;
-  if (p >= np) return;
   constexpr int NP = D * (D + 1) / 2;
+  const int id = blockIdx.x * kWG + threadIdx.x;
+  if (id >= np * NP) return;
+  const int p = id / NP, q = id % NP;
+  int i = 0, j = q;   // pairs i <= j in storage order
+  while (j >= D - i) {
+    j -= D - i;
+    ++i;
+  }
+  j += i;
   const int RU = 1 + D + tu.n, RG = 1 + D + tg.n, RP = 1 + 2 * D + tp.n;
-  const double wl[3] = {wl0, wl1, wl2}, wh[3] = {wh0, wh1, wh2};
-  // moment of u for the exponent vector e (order 2 or 3) at plane q
-  auto Mu = [&](int q, const int* e) { const double* r = su + (size_t)q * RU; return r[1 + D + mom_find(tu, D, e)] / r[0]; };
-  auto Um = [&](int q, int i) { return su[(size_t)q * RU + 1 + i]; };
+  auto at3 = [](int k, double v0, double v1, double v2) { return k == 0 ? v0 : (k == 1 ? v1 : v2); };
   const int pp = p + 1 < np ? p + 1 : (periodic ? 0 : -1);
   const int pm = p > 0 ? p - 1 : (periodic ? np - 1 : -1);
   const double T = tmet[p], J = jm[p], al = J * T * T;
+  // central moment of u at plane pl, by its place in the table
+  auto Mu = [&](int pl, int e) { const double* r = su + (size_t)pl * RU; return r[1 + D + e] / r[0]; };
   auto d1 = [&](auto f, double fwl, double fwh) {
     const double fp = pp >= 0 ? f(pp) : 2.0 * fwh - f(p);
     const double fm = pm >= 0 ? f(pm) : 2.0 * fwl - f(p);
@@ -324,39 +410,24 @@ k_budget(int np, int a, int periodic, MomTab tu, MomTab tg, MomTab tp, const dou
     else s += 2.0 * al * (0.0 - fP);
     return s / J;
   };
-  double dU[D];
-#pragma unroll
-  for (int i = 0; i < D; ++i) dU[i] = d1([&](int q) { return Um(q, i); }, wl[i], wh[i]);
-  int q = 0;
-#pragma unroll
-  for (int i = 0; i < D; ++i)
-#pragma unroll
-    for (int j = i; j < D; ++j, ++q) {
-      int eia[D] = {}, eja[D] = {}, eij[D] = {}, eija[D] = {};
-      eia[i]++; eia[a]++;
-      eja[j]++; eja[a]++;
-      eij[i]++; eij[j]++;
-      eija[i]++; eija[j]++; eija[a]++;
-      const double P_ = -(Mu(p, eia) * dU[j] + Mu(p, eja) * dU[i]);
-      double eps = 0.0;
-      for (int k = 0; k < D; ++k) {
-        const double* r = sg + ((size_t)k * np + p) * RG;
-        eps += r[1 + D + mom_find(tg, D, eij)] / r[0];
-      }
-      eps *= 2.0;
-      const double Tt = -d1([&](int qq) { return Mu(qq, eija); }, 0.0, 0.0);
-      const double Dd = d2([&](int qq) { return Mu(qq, eij); });
-      int xij[2 * D] = {}, xji[2 * D] = {};
-      xij[i]++; xij[D + j]++;
-      xji[j]++; xji[D + i]++;
-      const double* r = sup + (size_t)p * RP;
-      const double Pi = -(r[1 + 2 * D + mom_find(tp, 2 * D, xij)] + r[1 + 2 * D + mom_find(tp, 2 * D, xji)]) / r[0];
-      out[((size_t)0 * np + p) * NP + q] = P_;
-      out[((size_t)1 * np + p) * NP + q] = eps;
-      out[((size_t)2 * np + p) * NP + q] = Tt;
-      out[((size_t)3 * np + p) * NP + q] = Dd;
-      out[((size_t)4 * np + p) * NP + q] = Pi;
-    }
+  auto dU = [&](int v) {
+    return d1([&](int pl) { return su[(size_t)pl * RU + 1 + v]; }, at3(v, wl0, wl1, wl2), at3(v, wh0, wh1, wh2));
+  };
+  const int ij = mom_find3(tu, i, j, -1), ija = mom_find3(tu, i, j, a);
+  double eps = 0.0;
+  const int gij = mom_find3(tg, i, j, -1);
+  for (int k = 0; k < D; ++k) {
+    const double* r = sg + ((size_t)k * np + p) * RG;
+    eps += r[1 + D + gij] / r[0];
+  }
+  const double* r = sup + (size_t)p * RP;
+  const double xij = r[1 + 2 * D + mom_find3(tp, i, D + j, -1)], xji = r[1 + 2 * D + mom_find3(tp, j, D + i, -1)];
+  out[((size_t)0 * np + p) * NP + q] =
+      -(Mu(p, mom_find3(tu, i, a, -1)) * dU(j) + Mu(p, mom_find3(tu, j, a, -1)) * dU(i));
+  out[((size_t)1 * np + p) * NP + q] = eps * 2.0;
+  out[((size_t)2 * np + p) * NP + q] = -d1([&](int pl) { return Mu(pl, ija); }, 0.0, 0.0);
+  out[((size_t)3 * np + p) * NP + q] = d2([&](int pl) { return Mu(pl, ij); });
+  out[((size_t)4 * np + p) * NP + q] = -(xij + xji) / r[0];
 }
 
 // Plane metric: T_aa and J of the first cell of each plane (computed from J T and 1/J).
@@ -404,12 +475,21 @@ int moments_accumulate(piso_ctx* c, hipStream_t s, const R* x, int m, int order,
   MomTab t;
   momtab(m, order, t);
   const int nx = c->h_tab[1], ny = c->h_tab[2];
-  switch (m) {
-    case 2: k_mom_acc<R, 2><<<np, kWG, 0, s>>>(x, c->N, nx, ny, ms, axis, t, state); break;
-    case 3: k_mom_acc<R, 3><<<np, kWG, 0, s>>>(x, c->N, nx, ny, ms, axis, t, state); break;
-    case 4: k_mom_acc<R, 4><<<np, kWG, 0, s>>>(x, c->N, nx, ny, ms, axis, t, state); break;
-    default: k_mom_acc<R, 6><<<np, kWG, 0, s>>>(x, c->N, nx, ny, ms, axis, t, state); break;
+#define MOM_ACC(M, K) k_mom_acc<R, M, K><<<np, kMomWG, 0, s>>>(x, c->N, nx, ny, ms, axis, t, state)
+  // every pair of at most kMomMaxAlpha multi-indices (moments_layout refuses the others)
+  switch (10 * m + order) {
+    case 22: MOM_ACC(2, 2); break;
+    case 23: MOM_ACC(2, 3); break;
+    case 24: MOM_ACC(2, 4); break;
+    case 32: MOM_ACC(3, 2); break;
+    case 33: MOM_ACC(3, 3); break;
+    case 34: MOM_ACC(3, 4); break;
+    case 42: MOM_ACC(4, 2); break;
+    case 43: MOM_ACC(4, 3); break;
+    case 62: MOM_ACC(6, 2); break;
+    default: return fail(c, PISO_E_ARG, "moments: unsupported order");
   }
+#undef MOM_ACC
   return mom_check(c, "k_mom_acc");
 }
 
@@ -485,10 +565,10 @@ int budget(piso_ctx* c, hipStream_t s, int axis, int order_u, const double* su, 
   const double wl[3] = {w[0], w[1], D == 3 ? w[2] : 0.0};
   const double wh[3] = {w[D], w[D + 1], D == 3 ? w[D + 2] : 0.0};
   if (D == 2)
-    k_budget<2><<<G, kWG, 0, s>>>(np, axis, periodic, tu, tg, tp, su, sg, sup, tmet, jm, wl[0], wl[1], wl[2], wh[0],
+    k_budget<2><<<grid_cells(3 * np), kWG, 0, s>>>(np, axis, periodic, tu, tg, tp, su, sg, sup, tmet, jm, wl[0], wl[1], wl[2], wh[0],
                                   wh[1], wh[2], out);
   else
-    k_budget<3><<<G, kWG, 0, s>>>(np, axis, periodic, tu, tg, tp, su, sg, sup, tmet, jm, wl[0], wl[1], wl[2], wh[0],
+    k_budget<3><<<grid_cells(6 * np), kWG, 0, s>>>(np, axis, periodic, tu, tg, tp, su, sg, sup, tmet, jm, wl[0], wl[1], wl[2], wh[0],
                                   wh[1], wh[2], out);
   return mom_check(c, "k_budget");
 }

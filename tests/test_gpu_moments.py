@@ -48,6 +48,31 @@ def test_moments_and_gradient_vs_oracle(prec, name, m, order, axis):
     assert eg < (1e-12 if prec == "f64" else 1e-6)
 
 
+@pytest.mark.parametrize("m,order,grid", [(2, 2, (33, 4, 31)), (2, 3, (32, 4, 32)), (2, 4, (41, 4, 25)),
+                                          (3, 2, (64, 4, 32)), (3, 3, (683, 4, 3)), (3, 4, (64, 4, 64)),
+                                          (4, 2, (17, 4, 241)), (4, 3, (2, 4, 2)), (6, 2, (7, 4, 16))])
+def test_moment_orders_and_plane_sizes(m, order, grid):
+    """Every pair of variables and order, planes of one sample short of, at and beyond a
+    work-group's threads and its batch of loads.  An FP64 sum of n <= 4100 terms is within
+    n eps ~ 1e-12 of exact relative to the sum of magnitudes: 1e-11 as elsewhere."""
+    api = _api()
+    case = cases.channel(*grid)
+    dims = case.domain.blocks[0]
+    ctx = api.Context(case.domain, "f64")
+    rng = np.random.default_rng(53 + 10 * m + order)
+    state = ctx.moments_state(m, order, 1)
+    ost = om.empty_state(dims[1], m, order)
+    for q in range(2):
+        x = 0.7 + (1 + q) * rng.standard_normal((m, ctx.N))
+        ctx.moments_accumulate(dev(x, ctx.dtype), state, order, 1)
+        ost = om.accumulate(ost, x, dims, 1)
+    mean, mom = ctx.moments_finalize(state, m, order, 1)
+    mref, oref = om.finalize(ost)
+    em, eo = rel(host(mean), mref), max_elem(host(mom), oref)
+    say("m=%d order=%d %s: mean %.2e moments %.2e" % (m, order, grid, em, eo))
+    assert em < 1e-13 and eo < 1e-11
+
+
 @pytest.mark.parametrize("name", ["channel", "sheared", "cylinder", "cavity12"])
 def test_field_gradient_vs_oracle(name):
     api = _api()
