@@ -84,6 +84,16 @@ __device__ __forceinline__ int neighbour_of(const Grid& g, int Q, int axis, int 
   return neighbour(g, c, Q, axis, side);
 }
 
+template <int D>
+__device__ __forceinline__ void faces_of(const Grid& g, int P, int (&Fp)[D], int (&Fm)[D]) {
+  const Cell c = locate(g, P);
+#pragma unroll
+  for (int j = 0; j < D; ++j) {
+    Fp[j] = neighbour(g, c, P, j, 1);
+    Fm[j] = neighbour(g, c, P, j, 0);
+  }
+}
+
 // ---------------------------------------------------------------- reductions (FP64)
 
 __device__ __forceinline__ double wave_sum(double v) {

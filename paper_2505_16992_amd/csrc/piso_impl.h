@@ -152,6 +152,17 @@ constexpr float kFdmMaxSpread = 24.f;
 // against 12 + 10, MIXED 12 + 9 against 9 + 5).  The price, measured: 1.34 against 0.50 ms
 // for that step in F64, 0.80 against 0.43 in F32.
 constexpr int kFdmMinCells3 = 1 << 14;
+
+// Grids whose solves run whole in one work-group (piso_small.hip): as many cells as its
+// registers hold without spilling (3D: half).  One work-group is the faster one up to
+// there, a step by launches against one work-group: 16^2 489 against 150 us (F64), 398 / 133
+// (F32); 64 x 32 718 / 263, 598 / 201 (periodic), 878 / 329, 688 / 251 (walls); 45^2 759 / 290,
+// 554 / 216; 128 x 16 932 / 352, 716 / 265; 12 x 170, the longest chains, 1923 / 703, 1514 /
+// 523.  Dense axes to 128 cells, whose bases (read from the L2 each iteration where the LDS
+// has no room) one CU reads in a few us.
+constexpr int kSmallCells = 2048;
+constexpr int kSmallTiles = 8;               // 16-cell tiles of a dense axis
+constexpr size_t kSmallLds = 150 * 1024;
 constexpr int kFdmRejected = 100;   // CgState::status: the operator is beyond that spread
 
 constexpr int kMgPinGroups = 64;    // coarse-level launches up to this many work-groups run on one XCD
@@ -242,6 +253,7 @@ struct piso_ctx {
   int pcg_op_es = 0;
   int pcg_op_pre = 0;             // preconditioners set up for it: bits 1 << PcgPre
   bool pcg_op_reject = false;     // ... and the fast diagonalisation turned it down
+  bool pcg_op_copied = false;     // P_f and D^-1 are in g_Pf and g_Dinv
   std::vector<piso::MgLevel> mg;  // coarse levels 1..L of the pressure preconditioner
   piso::Grid mg_g1{};             // level 1 as a block table (offsets, dims, division magic)
   piso::MgTiles mg_tiles{};       // work-group tiles of the fine-grid restriction
@@ -501,6 +513,18 @@ int fdm_build(piso_ctx* c, const piso_domain_desc* desc, const Topology& topo);
 template <typename R>
 int fdm_setup(piso_ctx* c, hipStream_t s, const R* Pf);
 const int* fdm_rejected(const piso_ctx* c);   // device flag
+// Whole solves of small grids in one launch, the state left in c->cg and c->h_cg (c->h_bi):
+// the pressure PCG with fast diagonalisation (gauge: x is freed of its mean) ...
+template <typename R>
+bool small_pcg_use(const piso_ctx* c);
+template <typename R>
+int small_pcg(piso_ctx* c, hipStream_t s, const R* Pf, const R* b, const double* mean, double sign, R* x, bool gauge,
+              double tol2, int max_iter);
+// ... and the Jacobi BiCGStab.
+bool small_bi_use(const piso_ctx* c);
+template <typename R>
+int small_bicgstab(piso_ctx* c, hipStream_t s, bool trans, const R* A, const R* C, const R* b, R* x, BiState* st,
+                   double tol2, int max_iter);
 // Work-groups whose r.z, r.r partial sums the products leave.
 template <typename R>
 int fdm_groups(const piso_ctx* c);

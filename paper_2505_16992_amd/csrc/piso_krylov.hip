@@ -16,16 +16,6 @@
 
 namespace piso {
 
-template <int D>
-__device__ __forceinline__ void faces_of(const Grid& g, int P, int (&Fp)[D], int (&Fm)[D]) {
-  const Cell c = locate(g, P);
-#pragma unroll
-  for (int j = 0; j < D; ++j) {
-    Fp[j] = neighbour(g, c, P, j, 1);
-    Fm[j] = neighbour(g, c, P, j, 0);
-  }
-}
-
 __device__ __forceinline__ bool lead() { return blockIdx.x == 0 && threadIdx.x == 0; }
 
 // ------------------------------------------------------------------------ PCG
@@ -1131,62 +1121,14 @@ static int pcg_groups(const piso_ctx* c) {
   return solver_groups(c->quad ? (long)c->N / 4 : (long)c->N);
 }
 
+// The solve by launches over the chip: from x (out: the iterate), its end state in c->h_cg.
 template <typename R, typename BT>
-static int pcg_run(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const BT* b,
-                   const double* mean, double sign, R* x, double rtol, int max_iter, int check_every,
-                   int precond, int* iters_out, double* rel_out, int* status_out, int hint_slot = 0) {
-  const int N = c->N, G = pcg_groups(c);
-  CgState* st = c->cg;
-  PcgOps<R> o;
-  o.Pf = (const R*)c->g_Pf;
-  o.Dinv = (const R*)c->g_Dinv;
-  o.x = (R*)c->g_x;
-  o.r = (R*)c->k_r;
-  o.r2 = (R*)c->k_r2;
-  o.q = (R*)c->k_q;
-  o.d0 = (R*)c->k_d0;
-  o.d1 = (R*)c->k_d1;
-  o.z = (R*)c->k_z;
-  o.y = (R*)c->k_y;
-  o.pA = part(c, kPartA);
-  o.pB = part(c, kPartB);
-  o.G = G;
-  // multigrid: z = B r is stored by the V-cycle (which also writes the r.z, r.r
-  // partials); the stencil kernel then forms d from z instead of Dinv r
-  // (or by the fast diagonalisation, on grids that have a plan and for operators it accepts)
+static int pcg_launched(piso_ctx* c, hipStream_t s, const PcgOps<R>& o, const BT* b, const double* mean, double sign,
+                        R* x, int max_iter, int check_every, double tol2, int pre, int hint_slot) {
+  const int N = c->N, G = o.G;
   const size_t es = sizeof(R);
-  const bool reuse = c->pcg_same_op && c->pcg_op_src == (const void*)Pf && c->pcg_op_es == (int)es;
-  if (!reuse) {
-    c->pcg_op_src = nullptr;   // invalid until the setup below is enqueued
-    c->pcg_op_pre = 0;
-    c->pcg_op_reject = false;
-    PISO_HIP(c, hipMemcpyAsync((void*)o.Pf, Pf, es * (size_t)c->dim * N, hipMemcpyDeviceToDevice, s));
-    PISO_HIP(c, hipMemcpyAsync((void*)o.Dinv, Dinv, es * (size_t)N, hipMemcpyDeviceToDevice, s));
-  }
-  o.fdm = precond == PISO_PRECOND_MG && c->fdm.on && !c->pcg_op_reject;
-  o.mg = precond == PISO_PRECOND_MG && !c->mg.empty() && !o.fdm;
-  o.z_op = o.mg || o.fdm;
-  const int pre = o.fdm ? kPreFdm : (o.mg ? kPreMg : kPreJacobi);
-  o.quad = c->quad;   // the context's buffers are 256-byte aligned
-  o.line = o.mg && c->mg_line_axis != 0;
-  o.Gz = o.fdm ? fdm_groups<R>(c)
-               : (o.line ? line_groups(c) : (o.mg && o.quad && zm_use(c, sizeof(R)) ? zm_groups(c) : G));
-  if (!(c->pcg_op_pre >> pre & 1)) {
-    if (o.fdm) {
-      if (int rc = fdm_setup<R>(c, s, o.Pf)) return rc;
-    } else if (o.mg) {
-      if (int rc = mg_setup<R>(c, s, o.Pf)) return rc;
-    }
-    c->pcg_op_src = Pf;
-    c->pcg_op_es = (int)es;
-    c->pcg_op_pre |= 1 << pre;
-  }
+  CgState* st = c->cg;
   PISO_HIP(c, hipMemcpyAsync(o.x, x, es * (size_t)N, hipMemcpyDeviceToDevice, s));
-  // the fast diagonalisation gains one to five digits an iteration, so it ends anywhere below
-  // the tolerance where the V-cycle's small steps end close to a digit below it on average:
-  // plain solves ask for 0.2 of it, which leaves the solutions as near as the V-cycle's did
-  // (MIXED checks its own residual)
-  const double tol2 = rtol * rtol * (o.fdm && hint_slot == 0 ? 0.04 : 1.0);
   if (c->dim == 2)
     k_cg_init<R, BT, 2><<<G, kWG, 0, s>>>(c->grid, o.Pf, o.Dinv, b, mean, sign, o.x, o.r, o.d0, o.pB);
   else
@@ -1244,17 +1186,88 @@ static int pcg_run(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const
     PISO_HIP(c, hipStreamSynchronize(s));
     timing_collect(c);
   }
+  if (c->h_cg->status == kFdmRejected) return PISO_OK;
+  PISO_HIP(c, hipMemcpyAsync(x, o.x, es * (size_t)N, hipMemcpyDeviceToDevice, s));
+  if (c->h_cg->status == 0) hint = c->h_cg->iters;
+  return PISO_OK;
+}
+
+// gauged (or null): the caller frees x of its mean unless *gauged is set.
+template <typename R, typename BT>
+static int pcg_run(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const BT* b,
+                   const double* mean, double sign, R* x, double rtol, int max_iter, int check_every,
+                   int precond, int* iters_out, double* rel_out, int* status_out, int hint_slot, bool* gauged) {
+  const int N = c->N, G = pcg_groups(c);
+  PcgOps<R> o;
+  o.Pf = (const R*)c->g_Pf;
+  o.Dinv = (const R*)c->g_Dinv;
+  o.x = (R*)c->g_x;
+  o.r = (R*)c->k_r;
+  o.r2 = (R*)c->k_r2;
+  o.q = (R*)c->k_q;
+  o.d0 = (R*)c->k_d0;
+  o.d1 = (R*)c->k_d1;
+  o.z = (R*)c->k_z;
+  o.y = (R*)c->k_y;
+  o.pA = part(c, kPartA);
+  o.pB = part(c, kPartB);
+  o.G = G;
+  // multigrid: z = B r is stored by the V-cycle (which also writes the r.z, r.r
+  // partials); the stencil kernel then forms d from z instead of Dinv r
+  // (or by the fast diagonalisation, on grids that have a plan and for operators it accepts)
+  const size_t es = sizeof(R);
+  const bool reuse = c->pcg_same_op && c->pcg_op_src == (const void*)Pf && c->pcg_op_es == (int)es;
+  if (!reuse) {
+    c->pcg_op_src = nullptr;   // invalid until the setup below is enqueued
+    c->pcg_op_pre = 0;
+    c->pcg_op_reject = false;
+    c->pcg_op_copied = false;
+  }
+  o.fdm = precond == PISO_PRECOND_MG && c->fdm.on && !c->pcg_op_reject;
+  o.mg = precond == PISO_PRECOND_MG && !c->mg.empty() && !o.fdm;
+  o.z_op = o.mg || o.fdm;
+  const int pre = o.fdm ? kPreFdm : (o.mg ? kPreMg : kPreJacobi);
+  o.quad = c->quad;   // the context's buffers are 256-byte aligned
+  o.line = o.mg && c->mg_line_axis != 0;
+  o.Gz = o.fdm ? fdm_groups<R>(c)
+               : (o.line ? line_groups(c) : (o.mg && o.quad && zm_use(c, sizeof(R)) ? zm_groups(c) : G));
+  const bool small = o.fdm && c->cg_grid == 0 && small_pcg_use<R>(c);   // the whole solve in one launch
+  if (!small && !c->pcg_op_copied) {
+    PISO_HIP(c, hipMemcpyAsync((void*)o.Pf, Pf, es * (size_t)c->dim * N, hipMemcpyDeviceToDevice, s));
+    PISO_HIP(c, hipMemcpyAsync((void*)o.Dinv, Dinv, es * (size_t)N, hipMemcpyDeviceToDevice, s));
+    c->pcg_op_copied = true;
+  }
+  if (!(c->pcg_op_pre >> pre & 1)) {
+    if (o.fdm) {
+      if (int rc = fdm_setup<R>(c, s, Pf)) return rc;
+    } else if (o.mg) {
+      if (int rc = mg_setup<R>(c, s, o.Pf)) return rc;
+    }
+    c->pcg_op_src = Pf;
+    c->pcg_op_es = (int)es;
+    c->pcg_op_pre |= 1 << pre;
+  }
+  // the fast diagonalisation gains one to five digits an iteration, so it ends anywhere below
+  // the tolerance where the V-cycle's small steps end close to a digit below it on average:
+  // plain solves ask for 0.2 of it, which leaves the solutions as near as the V-cycle's did
+  // (MIXED checks its own residual)
+  const double tol2 = rtol * rtol * (o.fdm && hint_slot == 0 ? 0.04 : 1.0);
+  if (small) {
+    if (int rc = small_pcg<R>(c, s, Pf, b, mean, sign, x, gauged != nullptr, tol2, max_iter)) return rc;
+  } else {
+    if (int rc = pcg_launched<R, BT>(c, s, o, b, mean, sign, x, max_iter, check_every, tol2, pre, hint_slot))
+      return rc;
+  }
   const CgState& h = *c->h_cg;
   if (h.status == kFdmRejected) {   // not an iteration was run: the same solve with multigrid
     const bool same_op = c->pcg_same_op;
     c->pcg_op_reject = c->pcg_same_op = true;
     const int rc = pcg_run<R, BT>(c, s, Pf, Dinv, b, mean, sign, x, rtol, max_iter, check_every, precond, iters_out,
-                                  rel_out, status_out, hint_slot);
+                                  rel_out, status_out, hint_slot, nullptr);
     c->pcg_same_op = same_op;
     return rc;
   }
-  PISO_HIP(c, hipMemcpyAsync(x, o.x, es * (size_t)N, hipMemcpyDeviceToDevice, s));
-  if (h.status == 0) hint = h.iters;
+  if (small && gauged) *gauged = true;
   *iters_out += h.iters;
   *rel_out = h.bb > 0 ? std::sqrt(h.rr / h.bb) : 0.0;
   const bool met = h.status == PISO_NOT_CONVERGED && h.rr <= rtol * rtol * h.bb;
@@ -1274,13 +1287,14 @@ int pressure_solve(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const
     return fail(c, PISO_E_ARG, "pressure solve: unknown preconditioner");
   int iters = 0, status = 0;
   double rel = 0.0;
+  bool gauged = false;
   int rc = pcg_run<R, BT>(c, s, Pf, Dinv, rhs, mean, -1.0, x, o->rtol, o->max_iter, o->check_every,
-                          o->precond, &iters, &rel, &status);
+                          o->precond, &iters, &rel, &status, 0, &gauged);
   if (rc) return rc;
   // zero-mean gauge
-  rc = launch_sum<R, double>(c, s, x, c->N, 1.0 / c->N, c->mean + 1);
+  if (!gauged) rc = launch_sum<R, double>(c, s, x, c->N, 1.0 / c->N, c->mean + 1);
   if (rc) return rc;
-  rc = launch_sub_mean<R, R>(c, s, x, c->mean + 1, x, c->N);
+  if (!gauged) rc = launch_sub_mean<R, R>(c, s, x, c->mean + 1, x, c->N);
   if (rc) return rc;
   if (info) {
     info->status = status;
@@ -1351,7 +1365,7 @@ int pressure_solve_mixed(piso_ctx* c, hipStream_t s, const double* Pf, const dou
     c->pcg_same_op = same || sweeps > 0;   // later sweeps and correctors: same operator
     int rc = pcg_run<float, float>(c, s, Pf32, Dinv32, r32, nullptr, 1.0, e32, tol_in, o->max_iter,
                                    o->check_every, o->precond, &iters, &rel_in, &st_in,
-                                   1 + std::min(sweeps, 2));
+                                   1 + std::min(sweeps, 2), nullptr);
     c->pcg_same_op = same_in;
     if (rc) return rc;
     if (st_in < 0) {
@@ -1475,51 +1489,55 @@ static int bicgstab_run(piso_ctx* c, hipStream_t s, bool trans, const R* A, cons
       else k_bii_spmv<R, 3, false, 3 * NVM><<<G, kWG, 0, s>>>(c->grid, A, C, X, H1, Y, st, PART);          \
     }                                                                                                      \
   } while (0)
-  if (ilu) {
-    if (D == 2) k_ilu_setup<R, 2><<<grid_cells(N), kWG, 0, s>>>(c->grid, A, C, sinv);
-    else k_ilu_setup<R, 3><<<grid_cells(N), kWG, 0, s>>>(c->grid, A, C, sinv);
+  if (!ilu && small_bi_use(c)) {   // the whole solve in one launch
+    if (int rc = small_bicgstab<R>(c, s, trans, A, C, b, x, st, tol2, o->max_iter)) return rc;
   } else {
-    k_bi_recip<R><<<grid_cells(N), kWG, 0, s>>>(N, A, iA);
-  }
-  BI_LAUNCH(k_bi_init, c->grid, A, C, b, x, r, rh, pb[0], vb[0], p3);
-  BI_CHECK(1, 0);
-  // zero right-hand sides are handled on the device (no read-back before the iterations)
-  if (D == 2) k_bi_zero_if<R, 2><<<grid_cells(N), kWG, 0, s>>>(N, st, x);
-  else k_bi_zero_if<R, 3><<<grid_cells(N), kWG, 0, s>>>(N, st, x);
-  if (int rc = check(c, "k_bi_init")) return rc;
-  c->h_bi->all_done = 0;
-  int it = 0;
-  const int ce = o->check_every < 1 ? 4 : o->check_every;
-  while (!c->h_bi->all_done && it < o->max_iter) {
-    const int n = std::min(ce, o->max_iter - it);
-    for (int k = 0; k < n; ++k, ++it) {
-      R* po = pb[it & 1];
-      R* pn = pb[(it + 1) & 1];
-      R* vo = vb[it & 1];
-      R* vn = vb[(it + 1) & 1];
-      if (ilu) {
-        // p, M^-1 p, v = C M^-1 p; s, M^-1 s, t = C M^-1 s; x, r
-        if (D == 2) k_bii_p<R, 2><<<G, kWG, 0, s>>>(N, r, po, vo, pn, st, p3, G, it);
-        else k_bii_p<R, 3><<<G, kWG, 0, s>>>(N, r, po, vo, pn, st, p3, G, it);
-        ILU_SWEEPS(pn, ph);
-        BII_SPMV(1, ph, rh, vn, p1);
-        if (D == 2) k_bii_s<R, 2><<<G, kWG, 0, s>>>(N, r, vn, sb, st, p1, G, it);
-        else k_bii_s<R, 3><<<G, kWG, 0, s>>>(N, r, vn, sb, st, p1, G, it);
-        ILU_SWEEPS(sb, sh);
-        BII_SPMV(2, sh, sb, tb, p2);
-        if (D == 2) k_bii_x<R, 2><<<G, kWG, 0, s>>>(N, x, r, rh, ph, sh, sb, tb, st, p2, p3, G, it);
-        else k_bii_x<R, 3><<<G, kWG, 0, s>>>(N, x, r, rh, ph, sh, sb, tb, st, p2, p3, G, it);
-        continue;
-      }
-      BI_LAUNCH(k_bi_1, c->grid, iA, C, r, rh, po, vo, pn, vn, st, p3, p1, G, it);
-      BI_LAUNCH(k_bi_2, c->grid, iA, C, r, vn, sb, tb, st, p1, p2, G, it);
-      if (D == 2) k_bi_3<R, 2><<<G, kWG, 0, s>>>(N, iA, x, r, rh, pn, sb, tb, st, p2, p3, G, it);
-      else k_bi_3<R, 3><<<G, kWG, 0, s>>>(N, iA, x, r, rh, pn, sb, tb, st, p2, p3, G, it);
+    if (ilu) {
+      if (D == 2) k_ilu_setup<R, 2><<<grid_cells(N), kWG, 0, s>>>(c->grid, A, C, sinv);
+      else k_ilu_setup<R, 3><<<grid_cells(N), kWG, 0, s>>>(c->grid, A, C, sinv);
+    } else {
+      k_bi_recip<R><<<grid_cells(N), kWG, 0, s>>>(N, A, iA);
     }
-    BI_CHECK(0, it);
-    if (int rc = check(c, "k_bi iteration")) return rc;
-    PISO_HIP(c, hipMemcpyAsync(c->h_bi, st, sizeof(BiState), hipMemcpyDeviceToHost, s));
-    PISO_HIP(c, hipStreamSynchronize(s));
+    BI_LAUNCH(k_bi_init, c->grid, A, C, b, x, r, rh, pb[0], vb[0], p3);
+    BI_CHECK(1, 0);
+    // zero right-hand sides are handled on the device (no read-back before the iterations)
+    if (D == 2) k_bi_zero_if<R, 2><<<grid_cells(N), kWG, 0, s>>>(N, st, x);
+    else k_bi_zero_if<R, 3><<<grid_cells(N), kWG, 0, s>>>(N, st, x);
+    if (int rc = check(c, "k_bi_init")) return rc;
+    c->h_bi->all_done = 0;
+    int it = 0;
+    const int ce = o->check_every < 1 ? 4 : o->check_every;
+    while (!c->h_bi->all_done && it < o->max_iter) {
+      const int n = std::min(ce, o->max_iter - it);
+      for (int k = 0; k < n; ++k, ++it) {
+        R* po = pb[it & 1];
+        R* pn = pb[(it + 1) & 1];
+        R* vo = vb[it & 1];
+        R* vn = vb[(it + 1) & 1];
+        if (ilu) {
+          // p, M^-1 p, v = C M^-1 p; s, M^-1 s, t = C M^-1 s; x, r
+          if (D == 2) k_bii_p<R, 2><<<G, kWG, 0, s>>>(N, r, po, vo, pn, st, p3, G, it);
+          else k_bii_p<R, 3><<<G, kWG, 0, s>>>(N, r, po, vo, pn, st, p3, G, it);
+          ILU_SWEEPS(pn, ph);
+          BII_SPMV(1, ph, rh, vn, p1);
+          if (D == 2) k_bii_s<R, 2><<<G, kWG, 0, s>>>(N, r, vn, sb, st, p1, G, it);
+          else k_bii_s<R, 3><<<G, kWG, 0, s>>>(N, r, vn, sb, st, p1, G, it);
+          ILU_SWEEPS(sb, sh);
+          BII_SPMV(2, sh, sb, tb, p2);
+          if (D == 2) k_bii_x<R, 2><<<G, kWG, 0, s>>>(N, x, r, rh, ph, sh, sb, tb, st, p2, p3, G, it);
+          else k_bii_x<R, 3><<<G, kWG, 0, s>>>(N, x, r, rh, ph, sh, sb, tb, st, p2, p3, G, it);
+          continue;
+        }
+        BI_LAUNCH(k_bi_1, c->grid, iA, C, r, rh, po, vo, pn, vn, st, p3, p1, G, it);
+        BI_LAUNCH(k_bi_2, c->grid, iA, C, r, vn, sb, tb, st, p1, p2, G, it);
+        if (D == 2) k_bi_3<R, 2><<<G, kWG, 0, s>>>(N, iA, x, r, rh, pn, sb, tb, st, p2, p3, G, it);
+        else k_bi_3<R, 3><<<G, kWG, 0, s>>>(N, iA, x, r, rh, pn, sb, tb, st, p2, p3, G, it);
+      }
+      BI_CHECK(0, it);
+      if (int rc = check(c, "k_bi iteration")) return rc;
+      PISO_HIP(c, hipMemcpyAsync(c->h_bi, st, sizeof(BiState), hipMemcpyDeviceToHost, s));
+      PISO_HIP(c, hipStreamSynchronize(s));
+    }
   }
 #undef BI_LAUNCH
 #undef BI_CHECK
