@@ -243,6 +243,9 @@ struct piso_ctx {
   // solve, then the first, second and later MIXED refinement sweeps
   int pcg_hint[3][5][4] = {};
   int pcg_kind = 4;               // kind of the next pressure solves (set around them)
+  // the same of the Jacobi BiCGStab: [transposed][plain, first, later MIXED sweeps]
+  int bi_hint[2][3] = {};
+  int bi_slot = 0;                // slot of the next velocity solves
   // The PCG copies P_f and D^-1 into g_Pf / g_Dinv and builds the coarse operators from
   // them.  A caller that knows the operator has not changed since the last solve (the
   // second corrector of a step, the second adjoint solve, later MIXED sweeps) sets
@@ -518,13 +521,13 @@ const int* fdm_rejected(const piso_ctx* c);   // device flag
 template <typename R>
 bool small_pcg_use(const piso_ctx* c);
 template <typename R>
-int small_pcg(piso_ctx* c, hipStream_t s, const R* Pf, const R* b, const double* mean, double sign, R* x, bool gauge,
-              double tol2, int max_iter);
+int small_pcg(piso_ctx* c, hipStream_t s, const R* Pf, const R* b, const double* mean, double sign, const R* x0, R* x,
+              bool gauge, double tol2, int max_iter);
 // ... and the Jacobi BiCGStab.
 bool small_bi_use(const piso_ctx* c);
 template <typename R>
-int small_bicgstab(piso_ctx* c, hipStream_t s, bool trans, const R* A, const R* C, const R* b, R* x, BiState* st,
-                   double tol2, int max_iter);
+int small_bicgstab(piso_ctx* c, hipStream_t s, bool trans, const R* A, const R* C, const R* b, R* x, bool from_zero,
+                   BiState* st, double tol2, int max_iter);
 // Work-groups whose r.z, r.r partial sums the products leave.
 template <typename R>
 int fdm_groups(const piso_ctx* c);
@@ -619,7 +622,7 @@ struct BiWork {
 BiWork bi_work_ctx(piso_ctx* c);   // the context's own workspaces
 template <typename R>
 int velocity_solve_ws(piso_ctx* c, hipStream_t s, bool trans, const R* A, const R* C, const R* b, R* x,
-                      const piso_solve_opts* o, piso_solve_info* info, const BiWork& w);
+                      const piso_solve_opts* o, piso_solve_info* info, const BiWork& w, bool from_zero);
 // The fixed device array of the allocation-free entry point on the context's device
 // (piso_noalloc.hip): its address, looked up once per device at context creation.
 int noalloc_bind(piso_ctx* c);

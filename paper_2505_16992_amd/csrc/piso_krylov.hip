@@ -29,8 +29,8 @@ __device__ __forceinline__ bool lead() { return blockIdx.x == 0 && threadIdx.x =
 template <typename R, typename BT, int D>
 __global__ void __launch_bounds__(kWG)
 k_cg_init(Grid g, const R* __restrict__ Pf, const R* __restrict__ Dinv, const BT* __restrict__ bsrc,
-          const double* __restrict__ mean, double sign, const R* __restrict__ x, R* __restrict__ r,
-          R* __restrict__ dold, double* __restrict__ partB) {
+          const double* __restrict__ mean, double sign, const R* __restrict__ x, R* __restrict__ xo,
+          R* __restrict__ r, R* __restrict__ dold, double* __restrict__ partB) {
   const int N = g.N;
   int beg, end;
   chunk_range(N, beg, end);
@@ -40,14 +40,17 @@ k_cg_init(Grid g, const R* __restrict__ Pf, const R* __restrict__ Dinv, const BT
     int Fp[D], Fm[D];
     faces_of<D>(g, P, Fp, Fm);
     const R b = (R)(sign * ((double)bsrc[P] - mu));
-    const R xP = x[P];
+    const R xP = x ? x[P] : R(0);   // null: from zero
+    xo[P] = xP;
     R Mx = R(0);
     // a face without a neighbour cell reads the cell itself: its term is exactly zero
+    if (x) {
 #pragma unroll
-    for (int j = 0; j < D; ++j) {
-      const int Fpj = Fp[j] >= 0 ? Fp[j] : P, Fmj = Fm[j] >= 0 ? Fm[j] : P;
-      Mx += Pf[(size_t)j * N + P] * (xP - x[Fpj]);
-      Mx += Pf[(size_t)j * N + Fmj] * (xP - x[Fmj]);
+      for (int j = 0; j < D; ++j) {
+        const int Fpj = Fp[j] >= 0 ? Fp[j] : P, Fmj = Fm[j] >= 0 ? Fm[j] : P;
+        Mx += Pf[(size_t)j * N + P] * (xP - x[Fpj]);
+        Mx += Pf[(size_t)j * N + Fmj] * (xP - x[Fmj]);
+      }
     }
     const R rv = b - Mx;
     r[P] = rv;
@@ -61,10 +64,11 @@ k_cg_init(Grid g, const R* __restrict__ Pf, const R* __restrict__ Dinv, const BT
 
 // One work-group: publishes the state after init (first: also resets the iteration
 // index and sets its limit; rejected: flag of the fast diagonalisation, or null) or after a
-// chunk of iterations (convergence of the latest residual).
+// chunk of iterations (convergence of the latest residual; host: the pinned copy that the
+// host reads after the wait, one launch less than copying the state).
 __global__ void __launch_bounds__(kWG)
 k_cg_check(const double* __restrict__ partB, int G, int first, int max_k, double tol2, CgState* st,
-           const int* __restrict__ rejected) {
+           const int* __restrict__ rejected, CgState* host) {
   double t[3];
   reduce_partials<3>(partB, G, t);
   if (threadIdx.x != 0) return;
@@ -78,18 +82,20 @@ k_cg_check(const double* __restrict__ partB, int G, int first, int max_k, double
     st->max_k = max_k;
     st->zero_rhs = t[2] == 0.0 ? 1 : 0;
   }
-  if (st->done) return;
-  st->rr = t[1];
-  st->iters = st->k;
-  if (!std::isfinite(t[0]) || !std::isfinite(t[1]) || !std::isfinite(st->bb)) {
-    st->status = PISO_E_NAN;
-    st->done = 1;
-  } else if (st->bb == 0.0 || t[1] <= st->tol2 * st->bb) {
-    st->done = 1;
-  } else if (rejected && *rejected) {   // the host runs the solve with multigrid
-    st->status = kFdmRejected;
-    st->done = 1;
+  if (!st->done) {
+    st->rr = t[1];
+    st->iters = st->k;
+    if (!std::isfinite(t[0]) || !std::isfinite(t[1]) || !std::isfinite(st->bb)) {
+      st->status = PISO_E_NAN;
+      st->done = 1;
+    } else if (st->bb == 0.0 || t[1] <= st->tol2 * st->bb) {
+      st->done = 1;
+    } else if (rejected && *rejected) {   // the host runs the solve with multigrid
+      st->status = kFdmRejected;
+      st->done = 1;
+    }
   }
+  if (host) *host = *st;
 }
 
 template <typename R, int D, bool ZOP = false>
@@ -337,25 +343,6 @@ k_finalize(const double* __restrict__ partials, int G, double* __restrict__ out)
   }
 }
 
-// x = 0 when the right-hand side is zero (set by k_cg_check), decided on the device so
-// that the host need not wait for the initial state.
-template <typename R>
-__global__ void __launch_bounds__(kWG) k_cg_zero_if(int N, const CgState* st, R* __restrict__ x) {
-  if (!st->zero_rhs) return;
-  const int P = cell_of_thread(N);
-  if (P >= 0) x[P] = R(0);
-}
-
-// x_c = 0 for the components whose right-hand side is zero (set by k_bi_check).
-template <typename R, int D>
-__global__ void __launch_bounds__(kWG) k_bi_zero_if(int N, const BiState* st, R* __restrict__ x) {
-  const int P = cell_of_thread(N);
-  if (P < 0) return;
-#pragma unroll
-  for (int c = 0; c < D; ++c)
-    if (st->bb[c] == 0.0) x[(size_t)c * N + P] = R(0);
-}
-
 // x64 += e over n elements (the refinement update of both MIXED solves).
 __global__ void __launch_bounds__(kWG) k_mix_add(int n, double* __restrict__ x64, const float* __restrict__ e) {
   const int P = cell_of_thread(n);
@@ -390,7 +377,7 @@ __global__ void __launch_bounds__(kWG) k_bi_recip(int N, const R* __restrict__ A
 template <typename R, int D, bool TRANS>
 __global__ void __launch_bounds__(kWG)
 k_bi_init(Grid g, const R* __restrict__ A, const R* __restrict__ C, const R* __restrict__ b,
-          const R* __restrict__ x, R* __restrict__ r, R* __restrict__ rh, R* __restrict__ p0,
+          R* __restrict__ x, int from_zero, R* __restrict__ r, R* __restrict__ rh, R* __restrict__ p0,
           R* __restrict__ v0, double* __restrict__ part3) {
   const int N = g.N;
   int beg, end;
@@ -415,12 +402,17 @@ k_bi_init(Grid g, const R* __restrict__ A, const R* __restrict__ C, const R* __r
     const R AP = A[P];
 #pragma unroll
     for (int c = 0; c < D; ++c) {
-      const R* xc = x + (size_t)c * N;
-      R Cx = AP * xc[P];
+      R* xc = x + (size_t)c * N;
+      R Cx = R(0);
+      if (from_zero) {
+        xc[P] = R(0);
+      } else {
+        Cx = AP * xc[P];
 #pragma unroll
-      for (int j = 0; j < D; ++j) {
-        Cx += cp[j] * xc[Fp[j]];
-        Cx += cm[j] * xc[Fm[j]];
+        for (int j = 0; j < D; ++j) {
+          Cx += cp[j] * xc[Fp[j]];
+          Cx += cm[j] * xc[Fm[j]];
+        }
       }
       const R bv = b[(size_t)c * N + P];
       const R rv = bv - Cx;
@@ -483,7 +475,7 @@ k_bi_mix_resid(Grid g, const double* __restrict__ A, const double* __restrict__ 
 
 template <int D>
 __global__ void __launch_bounds__(kWG)
-k_bi_check(const double* __restrict__ part3, int G, int first, int k_total, double tol2, BiState* st) {
+k_bi_check(const double* __restrict__ part3, int G, int first, int k_total, double tol2, BiState* st, BiState* host) {
   double t[3 * D];
   if (first) {
     reduce_partials<3 * D>(part3, G, t);
@@ -521,6 +513,7 @@ k_bi_check(const double* __restrict__ part3, int G, int first, int k_total, doub
     all &= st->done[c];
   }
   st->all_done = all;
+  if (host) *host = *st;   // pinned: what the host reads after the wait
 }
 
 template <typename R, int D, bool TRANS>
@@ -1121,19 +1114,18 @@ static int pcg_groups(const piso_ctx* c) {
   return solver_groups(c->quad ? (long)c->N / 4 : (long)c->N);
 }
 
-// The solve by launches over the chip: from x (out: the iterate), its end state in c->h_cg.
+// The solve by launches over the chip: from x (null: from zero), its end state in c->h_cg, the
+// iterate in o.x.
 template <typename R, typename BT>
 static int pcg_launched(piso_ctx* c, hipStream_t s, const PcgOps<R>& o, const BT* b, const double* mean, double sign,
-                        R* x, int max_iter, int check_every, double tol2, int pre, int hint_slot) {
-  const int N = c->N, G = o.G;
-  const size_t es = sizeof(R);
+                        const R* x, int max_iter, int check_every, double tol2, int pre, int hint_slot) {
+  const int G = o.G;
   CgState* st = c->cg;
-  PISO_HIP(c, hipMemcpyAsync(o.x, x, es * (size_t)N, hipMemcpyDeviceToDevice, s));
   if (c->dim == 2)
-    k_cg_init<R, BT, 2><<<G, kWG, 0, s>>>(c->grid, o.Pf, o.Dinv, b, mean, sign, o.x, o.r, o.d0, o.pB);
+    k_cg_init<R, BT, 2><<<G, kWG, 0, s>>>(c->grid, o.Pf, o.Dinv, b, mean, sign, x, o.x, o.r, o.d0, o.pB);
   else
-    k_cg_init<R, BT, 3><<<G, kWG, 0, s>>>(c->grid, o.Pf, o.Dinv, b, mean, sign, o.x, o.r, o.d0, o.pB);
-  k_cg_check<<<1, kWG, 0, s>>>(o.pB, G, 1, max_iter, tol2, st, o.fdm ? fdm_rejected(c) : nullptr);
+    k_cg_init<R, BT, 3><<<G, kWG, 0, s>>>(c->grid, o.Pf, o.Dinv, b, mean, sign, x, o.x, o.r, o.d0, o.pB);
+  k_cg_check<<<1, kWG, 0, s>>>(o.pB, G, 1, max_iter, tol2, st, o.fdm ? fdm_rejected(c) : nullptr, nullptr);
   if (int rc = check(c, "k_cg_init")) return rc;
   if (o.fdm) {
     if (int rc = fdm_apply<R>(c, s, (const R*)o.r, o.z, st, o.pB)) return rc;
@@ -1147,10 +1139,8 @@ static int pcg_launched(piso_ctx* c, hipStream_t s, const PcgOps<R>& o, const BT
     }
     if (int rc = mg_apply<R>(c, s, o.Pf, o.Dinv, (const R*)o.r, (const R*)o.y, o.z, st, o.pB, G)) return rc;
   }
-  // no read-back here: a zero right-hand side is handled on the device, and iterations
-  // launched after convergence return at once
-  k_cg_zero_if<R><<<grid_cells(N), kWG, 0, s>>>(N, st, o.x);
-  c->h_cg->done = 0;
+  // no read-back here: iterations launched after convergence return at once
+  c->h_cg->done = c->h_cg->zero_rhs = 0;
   // chunks of an even number of iterations: the recorded pair keeps the slot parity
   if (check_every < 2) check_every = 2;
   check_every += check_every & 1;
@@ -1160,14 +1150,17 @@ static int pcg_launched(piso_ctx* c, hipStream_t s, const PcgOps<R>& o, const BT
   if (use_graph && !*gx) {
     if (int rc = pcg_graph<R>(c, o, gx)) return rc;
   }
-  // the first chunk covers the iterations of the previous solve of the same kind less two
-  // (solves of one kind in consecutive steps take similar counts, different kinds do
-  // not; an iteration launched after convergence costs about as much as a read-back),
-  // later chunks check_every
+  // the first chunk covers the iterations of the previous solve of the same kind (solves of one
+  // kind in consecutive steps take similar counts, different kinds do not; a pair launched
+  // after convergence costs about as much as a read-back), later chunks check_every
   const int kind = c->pcg_kind >= 0 && c->pcg_kind <= kPcgOther ? c->pcg_kind : kPcgOther;
   int& hint = c->pcg_hint[pre][kind][hint_slot];
-  int chunk = std::max(check_every, (hint - 2) & ~1);
+  int chunk = std::max(check_every, (hint + 1) & ~1);
   int launched = 0;
+  if (max_iter <= 0) {   // no iterations: the initial state alone
+    k_cg_check<<<1, kWG, 0, s>>>(o.pB, G, 0, max_iter, tol2, st, nullptr, c->h_cg);
+    PISO_HIP(c, hipStreamSynchronize(s));
+  }
   while (!c->h_cg->done && launched < max_iter) {
     const int n = std::min(chunk, max_iter - launched + 1);
     chunk = check_every;
@@ -1180,27 +1173,26 @@ static int pcg_launched(piso_ctx* c, hipStream_t s, const PcgOps<R>& o, const BT
       }
     }
     launched += n + (n & 1);
-    k_cg_check<<<1, kWG, 0, s>>>(o.pB, o.Gz, 0, max_iter, tol2, st, nullptr);
+    k_cg_check<<<1, kWG, 0, s>>>(o.pB, o.Gz, 0, max_iter, tol2, st, nullptr, c->h_cg);
     if (int rc = check(c, "k_cg iteration")) return rc;
-    PISO_HIP(c, hipMemcpyAsync(c->h_cg, st, sizeof(CgState), hipMemcpyDeviceToHost, s));
     PISO_HIP(c, hipStreamSynchronize(s));
     timing_collect(c);
   }
-  if (c->h_cg->status == kFdmRejected) return PISO_OK;
-  PISO_HIP(c, hipMemcpyAsync(x, o.x, es * (size_t)N, hipMemcpyDeviceToDevice, s));
   if (c->h_cg->status == 0) hint = c->h_cg->iters;
   return PISO_OK;
 }
 
-// gauged (or null): the caller frees x of its mean unless *gauged is set.
+// The solve from x0 (null: from zero); the iterate in *res: xs, or a buffer of the context.
+// gauged (or null): *res still has its mean unless *gauged is set.
 template <typename R, typename BT>
 static int pcg_run(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const BT* b,
-                   const double* mean, double sign, R* x, double rtol, int max_iter, int check_every,
+                   const double* mean, double sign, const R* x0, R* xs, const R** res, double rtol, int max_iter, int check_every,
                    int precond, int* iters_out, double* rel_out, int* status_out, int hint_slot, bool* gauged) {
   const int N = c->N, G = pcg_groups(c);
   PcgOps<R> o;
-  o.Pf = (const R*)c->g_Pf;
-  o.Dinv = (const R*)c->g_Dinv;
+  const bool own = sizeof(R) == 4 && c->prec == PISO_MIXED;   // the context's own buffers already
+  o.Pf = own ? Pf : (const R*)c->g_Pf;
+  o.Dinv = own ? Dinv : (const R*)c->g_Dinv;
   o.x = (R*)c->g_x;
   o.r = (R*)c->k_r;
   o.r2 = (R*)c->k_r2;
@@ -1232,7 +1224,7 @@ static int pcg_run(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const
   o.Gz = o.fdm ? fdm_groups<R>(c)
                : (o.line ? line_groups(c) : (o.mg && o.quad && zm_use(c, sizeof(R)) ? zm_groups(c) : G));
   const bool small = o.fdm && c->cg_grid == 0 && small_pcg_use<R>(c);   // the whole solve in one launch
-  if (!small && !c->pcg_op_copied) {
+  if (!small && !own && !c->pcg_op_copied) {
     PISO_HIP(c, hipMemcpyAsync((void*)o.Pf, Pf, es * (size_t)c->dim * N, hipMemcpyDeviceToDevice, s));
     PISO_HIP(c, hipMemcpyAsync((void*)o.Dinv, Dinv, es * (size_t)N, hipMemcpyDeviceToDevice, s));
     c->pcg_op_copied = true;
@@ -1253,17 +1245,19 @@ static int pcg_run(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const
   // (MIXED checks its own residual)
   const double tol2 = rtol * rtol * (o.fdm && hint_slot == 0 ? 0.04 : 1.0);
   if (small) {
-    if (int rc = small_pcg<R>(c, s, Pf, b, mean, sign, x, gauged != nullptr, tol2, max_iter)) return rc;
+    if (int rc = small_pcg<R>(c, s, Pf, b, mean, sign, x0, xs, gauged != nullptr, tol2, max_iter)) return rc;
+    *res = xs;
   } else {
-    if (int rc = pcg_launched<R, BT>(c, s, o, b, mean, sign, x, max_iter, check_every, tol2, pre, hint_slot))
+    if (int rc = pcg_launched<R, BT>(c, s, o, b, mean, sign, x0, max_iter, check_every, tol2, pre, hint_slot))
       return rc;
+    *res = o.x;
   }
   const CgState& h = *c->h_cg;
   if (h.status == kFdmRejected) {   // not an iteration was run: the same solve with multigrid
     const bool same_op = c->pcg_same_op;
     c->pcg_op_reject = c->pcg_same_op = true;
-    const int rc = pcg_run<R, BT>(c, s, Pf, Dinv, b, mean, sign, x, rtol, max_iter, check_every, precond, iters_out,
-                                  rel_out, status_out, hint_slot, nullptr);
+    const int rc = pcg_run<R, BT>(c, s, Pf, Dinv, b, mean, sign, x0, xs, res, rtol, max_iter, check_every, precond,
+                                  iters_out, rel_out, status_out, hint_slot, nullptr);
     c->pcg_same_op = same_op;
     return rc;
   }
@@ -1288,14 +1282,18 @@ int pressure_solve(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const
   int iters = 0, status = 0;
   double rel = 0.0;
   bool gauged = false;
-  int rc = pcg_run<R, BT>(c, s, Pf, Dinv, rhs, mean, -1.0, x, o->rtol, o->max_iter, o->check_every,
+  const R* res = nullptr;
+  int rc = pcg_run<R, BT>(c, s, Pf, Dinv, rhs, mean, -1.0, x, x, &res, o->rtol, o->max_iter, o->check_every,
                           o->precond, &iters, &rel, &status, 0, &gauged);
   if (rc) return rc;
-  // zero-mean gauge
-  if (!gauged) rc = launch_sum<R, double>(c, s, x, c->N, 1.0 / c->N, c->mean + 1);
-  if (rc) return rc;
-  if (!gauged) rc = launch_sub_mean<R, R>(c, s, x, c->mean + 1, x, c->N);
-  if (rc) return rc;
+  if (!gauged) {   // zero-mean gauge
+    if (c->h_cg->zero_rhs) {
+      PISO_HIP(c, hipMemsetAsync(x, 0, sizeof(R) * (size_t)c->N, s));
+    } else {
+      if ((rc = launch_sum<R, double>(c, s, res, c->N, 1.0 / c->N, c->mean + 1))) return rc;
+      if ((rc = launch_sub_mean<R, R>(c, s, res, c->mean + 1, x, c->N))) return rc;
+    }
+  }
   if (info) {
     info->status = status;
     info->iters = iters;
@@ -1334,9 +1332,8 @@ int pressure_solve_mixed(piso_ctx* c, hipStream_t s, const double* Pf, const dou
       k_mix_resid<2><<<G, kWG, 0, s>>>(c->grid, Pf, rhs64, mean, x64, r32, pS);
     else
       k_mix_resid<3><<<G, kWG, 0, s>>>(c->grid, Pf, rhs64, mean, x64, r32, pS);
-    k_finalize<2><<<1, kWG, 0, s>>>(pS, G, c->mean + 2);
+    k_finalize<2><<<1, kWG, 0, s>>>(pS, G, c->h_scal);   // pinned
     if (int rc = check(c, "k_mix_resid")) return rc;
-    PISO_HIP(c, hipMemcpyAsync(c->h_scal, c->mean + 2, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
     PISO_HIP(c, hipStreamSynchronize(s));
     const double rr = c->h_scal[0], bb = c->h_scal[1];
     if (!std::isfinite(rr) || !std::isfinite(bb)) {
@@ -1354,7 +1351,7 @@ int pressure_solve_mixed(piso_ctx* c, hipStream_t s, const double* Pf, const dou
       status = PISO_NOT_CONVERGED;
       break;
     }
-    PISO_HIP(c, hipMemsetAsync(e32, 0, sizeof(float) * (size_t)N, s));
+    const float* e = nullptr;
     int st_in = 0;
     double rel_in = 0.0;
     // ask the inner solve only for the reduction still missing, rtol / rel (the check of
@@ -1363,7 +1360,7 @@ int pressure_solve_mixed(piso_ctx* c, hipStream_t s, const double* Pf, const dou
     const double tol_in = std::min(0.5, std::max(o->inner_rtol, o->rtol / rel));
     const bool same_in = c->pcg_same_op;
     c->pcg_same_op = same || sweeps > 0;   // later sweeps and correctors: same operator
-    int rc = pcg_run<float, float>(c, s, Pf32, Dinv32, r32, nullptr, 1.0, e32, tol_in, o->max_iter,
+    int rc = pcg_run<float, float>(c, s, Pf32, Dinv32, r32, nullptr, 1.0, nullptr, e32, &e, tol_in, o->max_iter,
                                    o->check_every, o->precond, &iters, &rel_in, &st_in,
                                    1 + std::min(sweeps, 2), nullptr);
     c->pcg_same_op = same_in;
@@ -1372,7 +1369,7 @@ int pressure_solve_mixed(piso_ctx* c, hipStream_t s, const double* Pf, const dou
       status = st_in;
       break;
     }
-    k_mix_add<<<grid_cells(N), kWG, 0, s>>>(N, x64, e32);
+    if (!c->h_cg->zero_rhs) k_mix_add<<<grid_cells(N), kWG, 0, s>>>(N, x64, e);
     if (int rc2 = check(c, "k_mix_add")) return rc2;
     ++sweeps;
   }
@@ -1398,7 +1395,7 @@ int velocity_solve(piso_ctx* c, hipStream_t s, bool trans, const R* A, const R* 
   if constexpr (std::is_same<R, double>::value) {
     if (c->prec == PISO_MIXED) return velocity_solve_mixed(c, s, trans, A, C, b, x, o, info);
   }
-  return velocity_solve_ws<R>(c, s, trans, A, C, b, x, o, info, bi_work_ctx(c));
+  return velocity_solve_ws<R>(c, s, trans, A, C, b, x, o, info, bi_work_ctx(c), false);
 }
 
 BiWork bi_work_ctx(piso_ctx* c) {
@@ -1427,7 +1424,7 @@ BiWork bi_work_ctx(piso_ctx* c) {
 // info->status.
 template <typename R>
 static int bicgstab_run(piso_ctx* c, hipStream_t s, bool trans, const R* A, const R* C, const R* b, R* x,
-                        const piso_solve_opts* o, piso_solve_info* info, const BiWork& w, bool ilu) {
+                        const piso_solve_opts* o, piso_solve_info* info, const BiWork& w, bool ilu, bool from_zero) {
   const int N = c->N, G = solver_groups(N), D = c->dim;   // cell-per-thread kernels
   R* r = (R*)w.r;
   R* rh = (R*)w.rh;
@@ -1452,8 +1449,9 @@ static int bicgstab_run(piso_ctx* c, hipStream_t s, bool trans, const R* A, cons
   } while (0)
 #define BI_CHECK(FIRST, KT)                                                       \
   do {                                                                            \
-    if (D == 2) k_bi_check<2><<<1, kWG, 0, s>>>(p3, G, FIRST, KT, tol2, st);      \
-    else k_bi_check<3><<<1, kWG, 0, s>>>(p3, G, FIRST, KT, tol2, st);             \
+    BiState* host = FIRST ? nullptr : c->h_bi;                                    \
+    if (D == 2) k_bi_check<2><<<1, kWG, 0, s>>>(p3, G, FIRST, KT, tol2, st, host); \
+    else k_bi_check<3><<<1, kWG, 0, s>>>(p3, G, FIRST, KT, tol2, st, host);       \
   } while (0)
   R* iA = (R*)w.iA;
   R* ph = (R*)w.ph;
@@ -1490,7 +1488,7 @@ static int bicgstab_run(piso_ctx* c, hipStream_t s, bool trans, const R* A, cons
     }                                                                                                      \
   } while (0)
   if (!ilu && small_bi_use(c)) {   // the whole solve in one launch
-    if (int rc = small_bicgstab<R>(c, s, trans, A, C, b, x, st, tol2, o->max_iter)) return rc;
+    if (int rc = small_bicgstab<R>(c, s, trans, A, C, b, x, from_zero, st, tol2, o->max_iter)) return rc;
   } else {
     if (ilu) {
       if (D == 2) k_ilu_setup<R, 2><<<grid_cells(N), kWG, 0, s>>>(c->grid, A, C, sinv);
@@ -1498,17 +1496,22 @@ static int bicgstab_run(piso_ctx* c, hipStream_t s, bool trans, const R* A, cons
     } else {
       k_bi_recip<R><<<grid_cells(N), kWG, 0, s>>>(N, A, iA);
     }
-    BI_LAUNCH(k_bi_init, c->grid, A, C, b, x, r, rh, pb[0], vb[0], p3);
+    BI_LAUNCH(k_bi_init, c->grid, A, C, b, x, from_zero ? 1 : 0, r, rh, pb[0], vb[0], p3);
     BI_CHECK(1, 0);
-    // zero right-hand sides are handled on the device (no read-back before the iterations)
-    if (D == 2) k_bi_zero_if<R, 2><<<grid_cells(N), kWG, 0, s>>>(N, st, x);
-    else k_bi_zero_if<R, 3><<<grid_cells(N), kWG, 0, s>>>(N, st, x);
     if (int rc = check(c, "k_bi_init")) return rc;
     c->h_bi->all_done = 0;
     int it = 0;
     const int ce = o->check_every < 1 ? 4 : o->check_every;
+    // the first read-back where the last solve of the kind ended (as in pcg_launched)
+    int& hint = c->bi_hint[trans ? 1 : 0][c->bi_slot];
+    int chunk = ilu ? ce : std::max(ce, hint);
+    if (o->max_iter <= 0) {   // no iterations: the initial state alone
+      BI_CHECK(0, 0);
+      PISO_HIP(c, hipStreamSynchronize(s));
+    }
     while (!c->h_bi->all_done && it < o->max_iter) {
-      const int n = std::min(ce, o->max_iter - it);
+      const int n = std::min(chunk, o->max_iter - it);
+      chunk = ce;
       for (int k = 0; k < n; ++k, ++it) {
         R* po = pb[it & 1];
         R* pn = pb[(it + 1) & 1];
@@ -1535,9 +1538,16 @@ static int bicgstab_run(piso_ctx* c, hipStream_t s, bool trans, const R* A, cons
       }
       BI_CHECK(0, it);
       if (int rc = check(c, "k_bi iteration")) return rc;
-      PISO_HIP(c, hipMemcpyAsync(c->h_bi, st, sizeof(BiState), hipMemcpyDeviceToHost, s));
       PISO_HIP(c, hipStreamSynchronize(s));
     }
+    if (!ilu) {
+      hint = 0;
+      for (int q = 0; q < D; ++q) hint = std::max(hint, c->h_bi->status[q] ? 0 : c->h_bi->iters[q]);
+    }
+    // a component whose right-hand side is zero, untouched by the iterations
+    for (int q = 0; q < D; ++q)
+      if (c->h_bi->bb[q] == 0.0)
+        PISO_HIP(c, hipMemsetAsync(x + (size_t)q * N, 0, sizeof(R) * (size_t)N, s));
   }
 #undef BI_LAUNCH
 #undef BI_CHECK
@@ -1562,7 +1572,7 @@ static int bicgstab_run(piso_ctx* c, hipStream_t s, bool trans, const R* A, cons
 
 template <typename R>
 int velocity_solve_ws(piso_ctx* c, hipStream_t s, bool trans, const R* A, const R* C, const R* b, R* x,
-                      const piso_solve_opts* o, piso_solve_info* info, const BiWork& w) {
+                      const piso_solve_opts* o, piso_solve_info* info, const BiWork& w, bool from_zero) {
   const int pc = o->precond;
   if (pc != PISO_PRECOND_JACOBI && pc != PISO_PRECOND_ILU0 && pc != PISO_PRECOND_JACOBI_ILU0)
     return fail(c, PISO_E_ARG, "velocity solve: preconditioner must be Jacobi, ILU(0) or Jacobi with ILU(0) restart");
@@ -1570,7 +1580,7 @@ int velocity_solve_ws(piso_ctx* c, hipStream_t s, bool trans, const R* A, const 
     return fail(c, PISO_E_ARG, "velocity solve: ILU(0) needs a grid two colours tile (even periodic extents)");
   piso_solve_info tmp{};
   piso_solve_info* inf = info ? info : &tmp;
-  int rc = bicgstab_run<R>(c, s, trans, A, C, b, x, o, inf, w, pc == PISO_PRECOND_ILU0);
+  int rc = bicgstab_run<R>(c, s, trans, A, C, b, x, o, inf, w, pc == PISO_PRECOND_ILU0, from_zero);
   if (rc < 0) return rc;
   if (pc == PISO_PRECOND_JACOBI_ILU0 && inf->status != PISO_OK && c->ilu_ok) {
     // the Jacobi solve failed: restart with ILU(0) from its last iterate, or from zero
@@ -1578,7 +1588,7 @@ int velocity_solve_ws(piso_ctx* c, hipStream_t s, bool trans, const R* A, const 
     if (inf->status == PISO_E_NAN)
       PISO_HIP(c, hipMemsetAsync(x, 0, sizeof(R) * (size_t)c->dim * c->N, s));
     const int first = inf->iters;
-    rc = bicgstab_run<R>(c, s, trans, A, C, b, x, o, inf, w, true);
+    rc = bicgstab_run<R>(c, s, trans, A, C, b, x, o, inf, w, true, false);
     if (rc < 0) return rc;
     inf->iters += first;
     inf->fallback = 1;
@@ -1609,14 +1619,13 @@ static int velocity_solve_mixed(piso_ctx* c, hipStream_t s, bool trans, const do
     if (D == 2) {
       if (trans) k_bi_mix_resid<2, true><<<G, kWG, 0, s>>>(c->grid, A, C, b, x, r32, p3);
       else k_bi_mix_resid<2, false><<<G, kWG, 0, s>>>(c->grid, A, C, b, x, r32, p3);
-      k_finalize<4><<<1, kWG, 0, s>>>(p3, G, c->mix_scal);
+      k_finalize<4><<<1, kWG, 0, s>>>(p3, G, c->h_scal);   // pinned
     } else {
       if (trans) k_bi_mix_resid<3, true><<<G, kWG, 0, s>>>(c->grid, A, C, b, x, r32, p3);
       else k_bi_mix_resid<3, false><<<G, kWG, 0, s>>>(c->grid, A, C, b, x, r32, p3);
-      k_finalize<6><<<1, kWG, 0, s>>>(p3, G, c->mix_scal);
+      k_finalize<6><<<1, kWG, 0, s>>>(p3, G, c->h_scal);
     }
     if (int rc = check(c, "k_bi_mix_resid")) return rc;
-    PISO_HIP(c, hipMemcpyAsync(c->h_scal, c->mix_scal, 2 * D * sizeof(double), hipMemcpyDeviceToHost, s));
     PISO_HIP(c, hipStreamSynchronize(s));
     rel = 0.0;
     bool bad = false;
@@ -1640,11 +1649,12 @@ static int velocity_solve_mixed(piso_ctx* c, hipStream_t s, bool trans, const do
       status = PISO_NOT_CONVERGED;
       break;
     }
-    PISO_HIP(c, hipMemsetAsync(e32, 0, sizeof(float) * (size_t)D * N, s));
     piso_solve_opts in = *o;
     in.rtol = std::min(0.5, std::max(o->inner_rtol, 0.5 * o->rtol / rel));
     piso_solve_info ii{};
-    int rc = velocity_solve<float>(c, s, trans, A32, C32, r32, e32, &in, &ii);
+    c->bi_slot = 1 + std::min(sweeps, 1);
+    int rc = velocity_solve_ws<float>(c, s, trans, A32, C32, r32, e32, &in, &ii, bi_work_ctx(c), true);
+    c->bi_slot = 0;
     if (rc < 0) {
       status = rc;
       break;
@@ -1671,10 +1681,10 @@ template int pressure_solve<double, double>(piso_ctx*, hipStream_t, const double
                                             const double*, const double*, double*, const piso_solve_opts*,
                                             piso_solve_info*);
 template int velocity_solve_ws<float>(piso_ctx*, hipStream_t, bool, const float*, const float*, const float*,
-                                      float*, const piso_solve_opts*, piso_solve_info*, const BiWork&);
+                                      float*, const piso_solve_opts*, piso_solve_info*, const BiWork&, bool);
 template int velocity_solve_ws<double>(piso_ctx*, hipStream_t, bool, const double*, const double*,
                                        const double*, double*, const piso_solve_opts*, piso_solve_info*,
-                                       const BiWork&);
+                                       const BiWork&, bool);
 template int velocity_solve<float>(piso_ctx*, hipStream_t, bool, const float*, const float*, const float*,
                                    float*, const piso_solve_opts*, piso_solve_info*);
 template int velocity_solve<double>(piso_ctx*, hipStream_t, bool, const double*, const double*,

@@ -80,9 +80,9 @@ extern "C" int piso_solve_velocity_noalloc(piso_ctx* c, void* stream, const piso
   piso_solve_info tmp{};
   const int rc = c->esz == 8
                      ? velocity_solve_ws<double>(c, s, false, (const double*)sys->A, (const double*)sys->C,
-                                                 (const double*)sys->b, (double*)u_star, o, &tmp, w)
+                                                 (const double*)sys->b, (double*)u_star, o, &tmp, w, false)
                      : velocity_solve_ws<float>(c, s, false, (const float*)sys->A, (const float*)sys->C,
-                                                (const float*)sys->b, (float*)u_star, o, &tmp, w);
+                                                (const float*)sys->b, (float*)u_star, o, &tmp, w, false);
   if (info) *info = tmp;
   return rc < 0 ? rc : tmp.status;
 }

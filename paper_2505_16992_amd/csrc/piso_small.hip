@@ -106,7 +106,7 @@ struct SmallSum {
 template <typename R, int D, bool TRANS, int CPT>
 __global__ void __launch_bounds__(kBiWG)
 k_bi_small(Grid g, const R* __restrict__ A, const R* __restrict__ C, const R* __restrict__ b, R* __restrict__ x,
-           BiState* st, BiState* host, double tol2, int max_iter) {
+           int from_zero, BiState* st, BiState* host, double tol2, int max_iter) {
   extern __shared__ __align__(32) char smem[];
   __shared__ double red[2 * 8 * kBiWG / 16];
   double* op = (double*)smem;   // [D][N]
@@ -140,10 +140,12 @@ k_bi_small(Grid g, const R* __restrict__ A, const R* __restrict__ C, const R* __
 #pragma unroll
     for (int c = 0; c < D; ++c) {
       const R* xc = x + (size_t)c * N;
-      xv[u][c] = on ? (double)xc[P] : 0.0;
+      xv[u][c] = on && !from_zero ? (double)xc[P] : 0.0;
       double Cx = AP * xv[u][c];
+      if (!from_zero) {
 #pragma unroll
-      for (int f = 0; f < 2 * D; ++f) Cx += a[u][f] * (double)xc[F[u][f]];
+        for (int f = 0; f < 2 * D; ++f) Cx += a[u][f] * (double)xc[F[u][f]];
+      }
       const double bv = on ? (double)b[(size_t)c * N + P] : 0.0;
       const double rv = on ? bv - Cx : 0.0;
       r[u][c] = rh[u][c] = rv;
@@ -394,7 +396,7 @@ __device__ __forceinline__ void small_product(const SmallFdm<R>& a, const R* V, 
 template <typename R, int CPT, bool STAGE>
 __global__ void __launch_bounds__(kPcgWG)
 k_pcg_small(Grid g, SmallFdm<R> a, const R* __restrict__ Pf, const R* __restrict__ bsrc,
-            const double* __restrict__ mean, double sign, R* __restrict__ x, int gauge, double tol2, int max_k,
+            const double* __restrict__ mean, double sign, const R* x0, R* x, int gauge, double tol2, int max_k,
             CgState* st, CgState* host) {
   using V4 = typename Vec4<R>::T;
   extern __shared__ __align__(32) char smem[];
@@ -460,7 +462,7 @@ k_pcg_small(Grid g, SmallFdm<R> a, const R* __restrict__ Pf, const R* __restrict
       }
     }
     const Cell cl = locate(g, P);
-    xv[u] = on ? (double)x[P] : 0.0;
+    xv[u] = on && x0 ? (double)x0[P] : 0.0;   // null: from zero
     double Mx = 0.0;
 #pragma unroll
     for (int f = 0; f < 4; ++f) {
@@ -468,7 +470,7 @@ k_pcg_small(Grid g, SmallFdm<R> a, const R* __restrict__ Pf, const R* __restrict
       const double pf = Pf[(size_t)j * N + ((f & 1) ? P : Qc)];
       F[u][f] = Qc;
       c[u][f] = on && Q >= 0 ? pf : 0.0;
-      Mx += c[u][f] * (xv[u] - (double)x[Qc]);
+      if (x0) Mx += c[u][f] * (xv[u] - (double)x0[Qc]);
     }
     const double bv = on ? sign * ((double)bsrc[P] - mu) : 0.0;
     r[u] = bv - Mx;
@@ -723,15 +725,15 @@ bool small_pcg_use(const piso_ctx* c) {
 }
 
 template <typename R>
-int small_pcg(piso_ctx* c, hipStream_t s, const R* Pf, const R* b, const double* mean, double sign, R* x, bool gauge,
-              double tol2, int max_iter) {
+int small_pcg(piso_ctx* c, hipStream_t s, const R* Pf, const R* b, const double* mean, double sign, const R* x0, R* x,
+              bool gauge, double tol2, int max_iter) {
   const SmallFdm<R> a = small_fdm<R>(c);
   const bool stage = small_fdm_lds<R>(a, c->N, true) <= kSmallLds;
   const size_t lds = small_fdm_lds<R>(a, c->N, stage);
   const int wg = small_threads(c->N, kPcgWG), cpt = (c->N + wg - 1) / wg;
 #define SMALL_PCG(CPT, STAGE)                                                                                     \
-  k_pcg_small<R, CPT, STAGE><<<1, wg, lds, s>>>(c->grid, a, Pf, b, mean, sign, x, gauge ? 1 : 0, tol2, max_iter, \
-                                                c->cg, c->h_cg)
+  k_pcg_small<R, CPT, STAGE><<<1, wg, lds, s>>>(c->grid, a, Pf, b, mean, sign, x0, x, gauge ? 1 : 0, tol2,     \
+                                                max_iter, c->cg, c->h_cg)
 #define SMALL_PCG_C(CPT)             \
   do {                               \
     if (stage) SMALL_PCG(CPT, true); \
@@ -750,12 +752,13 @@ bool small_bi_use(const piso_ctx* c) {
 }
 
 template <typename R>
-int small_bicgstab(piso_ctx* c, hipStream_t s, bool trans, const R* A, const R* C, const R* b, R* x, BiState* st,
-                   double tol2, int max_iter) {
+int small_bicgstab(piso_ctx* c, hipStream_t s, bool trans, const R* A, const R* C, const R* b, R* x, bool from_zero,
+                   BiState* st, double tol2, int max_iter) {
   const size_t lds = (size_t)c->dim * c->N * sizeof(double);
   const int wg = small_threads(c->N, kBiWG), cpt = (c->N + wg - 1) / wg;
 #define SMALL_BI(D, T, CPT) \
-  k_bi_small<R, D, T, CPT><<<1, wg, lds, s>>>(c->grid, A, C, b, x, st, c->h_bi, tol2, max_iter)
+  k_bi_small<R, D, T, CPT><<<1, wg, lds, s>>>(c->grid, A, C, b, x, from_zero ? 1 : 0, st, c->h_bi, tol2, \
+                                              max_iter)
 #define SMALL_BI_C(D, T)                  \
   do {                                    \
     if (cpt == 1) SMALL_BI(D, T, 1);      \
@@ -777,10 +780,10 @@ int small_bicgstab(piso_ctx* c, hipStream_t s, bool trans, const R* A, const R* 
 
 #define INST(R)                                                                                                    \
   template bool small_pcg_use<R>(const piso_ctx*);                                                                 \
-  template int small_pcg<R>(piso_ctx*, hipStream_t, const R*, const R*, const double*, double, R*, bool, double,  \
-                            int);                                                                                  \
-  template int small_bicgstab<R>(piso_ctx*, hipStream_t, bool, const R*, const R*, const R*, R*, BiState*, double, \
-                                 int);
+  template int small_pcg<R>(piso_ctx*, hipStream_t, const R*, const R*, const double*, double, const R*, R*, bool, \
+                            double, int);                                                                                  \
+  template int small_bicgstab<R>(piso_ctx*, hipStream_t, bool, const R*, const R*, const R*, R*, bool, BiState*,    \
+                                 double, int);
 INST(float)
 INST(double)
 #undef INST
