@@ -128,9 +128,7 @@ int alloc_workspaces(piso_ctx* c) {
       {&c->b_r, D * N * e}, {&c->b_rh, D * N * e}, {&c->b_p0, D * N * e}, {&c->b_p1, D * N * e},
       {&c->b_v0, D * N * e}, {&c->b_v1, D * N * e}, {&c->b_s, D * N * e}, {&c->b_t, D * N * e},
       {&c->b_iA, N * e}, {&c->b_ph, D * N * e}, {&c->b_sh, D * N * e}, {&c->b_sinv, N * e},
-      {&c->a_g, D * N * e}, {&c->a_uin, D * N * e}, {&c->a_lam, N * e}, {&c->a_pbar, N * e},
-      {&c->a_mu, D * N * e}, {&c->a_dh, D * N * e}, {&c->a_dA, N * e}, {&c->a_dC, 2 * D * N * e},
-      {&c->a_dbu, D * N * e}, {&c->a_db, D * N * e}, {&c->a_dp1, N * e}, {&c->a_dnu, N * e},
+      {&c->a_g, D * N * e}, {&c->a_lam, N * 8}, {&c->a_pbar, N * e}, {&c->a_db, D * N * e},
       {&c->a_ybar, D * N * e}, {&c->a_cbar, D * D * N * e}, {&c->a_lam_hist[0], N * 8}, {&c->a_lam_hist[1], N * 8},
       {&c->a_lam_hist2[0], N * 8}, {&c->a_lam_hist2[1], N * 8}, {&c->w_zb, D * (size_t)std::max(c->NB, 1) * e},
       {(void**)&c->partials, (size_t)kPartRegions * kRedGrid * sizeof(double)},
@@ -138,6 +136,19 @@ int alloc_workspaces(piso_ctx* c) {
   };
   for (auto& l : L)
     if (int rc = dev_alloc(c, l.p, l.bytes)) return rc;
+  // what a backward step accumulates into, in one allocation that one fill clears
+  struct { void** p; size_t bytes; } Z[] = {
+      {&c->a_dA, N * e}, {&c->a_dC, 2 * D * N * e}, {&c->a_dbu, D * N * e}, {&c->a_dp1, N * e}, {&c->a_uin, D * N * e},
+      {&c->a_dh, D * N * e}, {&c->a_mu, D * N * e}, {&c->a_dnu, N * e},
+  };
+  c->a_zero_bytes = 0;
+  for (auto& z : Z) c->a_zero_bytes += (z.bytes + 255) / 256 * 256;
+  if (int rc = dev_alloc(c, &c->a_zero, c->a_zero_bytes)) return rc;
+  size_t at = 0;
+  for (auto& z : Z) {
+    *z.p = (char*)c->a_zero + at;
+    at += (z.bytes + 255) / 256 * 256;
+  }
   PISO_HIP(c, hipMemset(c->w_zb, 0, D * (size_t)std::max(c->NB, 1) * e));
   PISO_HIP(c, hipMemset(c->cg, 0, sizeof(CgState)));
   PISO_HIP(c, hipMemset(c->bi, 0, sizeof(BiState)));
@@ -223,11 +234,11 @@ int do_pressure_adjoint(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, 
   const int rc = pressure_solve<R, R>(c, s, Pf, Dinv, g, c->mean, lam, o, inf);
   if (rc < 0) return rc;
   if (hist >= 0 && inf->status >= 0) {
-    if (c->lam_hist_valid[hist]) {
-      PISO_HIP(c, hipMemcpyAsync(c->a_lam_hist2[hist], c->a_lam_hist[hist], sizeof(R) * N, hipMemcpyDeviceToDevice, s));
-      c->lam_hist_valid2[hist] = true;
-    }
-    PISO_HIP(c, hipMemcpyAsync(c->a_lam_hist[hist], lam, sizeof(R) * N, hipMemcpyDeviceToDevice, s));
+    // lam, the last and the one before change places (lam stays valid for the caller until
+    // the next adjoint solve)
+    c->lam_hist_valid2[hist] = c->lam_hist_valid[hist];
+    std::swap(c->a_lam_hist[hist], c->a_lam_hist2[hist]);
+    std::swap(c->a_lam_hist[hist], c->a_lam);
     c->lam_hist_valid[hist] = true;
   }
   return rc;
@@ -383,10 +394,10 @@ int do_corrector_bwd(piso_ctx* c, hipStream_t s, const R* A, const R* C, const R
 // already holds db = mu and the h contributions) and the p^n gradient of -grad p^n.
 template <typename R>
 int do_assemble_bwd(piso_ctx* c, hipStream_t s, const R* u_n, const R* nu, int nu_field, const R* ub, double dt,
-                    const R* dA, const R* dC, const R* dbu, R* du_n, R* dS, R* dnu, R* dub) {
+                    const R* dA, const R* dC, const R* dbu, R* du_n, R* dS, R* dnu, R* dub, bool cleared = false) {
   const int N = c->N, D = c->dim;
   R* dnu_cell = dnu ? (R*)c->a_dnu : nullptr;
-  if (dnu_cell) PISO_HIP(c, hipMemsetAsync(dnu_cell, 0, sizeof(R) * N, s));
+  if (dnu_cell && !cleared) PISO_HIP(c, hipMemsetAsync(dnu_cell, 0, sizeof(R) * N, s));
   if (int rc = launch_assemble_bwd<R>(c, s, u_n, nu, nu_field, ub, dt, dA, dC, dbu, du_n, dS, dnu_cell, dub)) return rc;
   if (c->nonorth) {
     R* ybar = (R*)c->a_ybar;
@@ -418,31 +429,22 @@ int do_step_backward(piso_ctx* c, hipStream_t s, const void* tape, const R* u_n,
   R* dp1 = (R*)c->a_dp1;
   R* uin = (R*)c->a_uin;
   R* duc = (R*)c->a_dh;
-  PISO_HIP(c, hipMemsetAsync(dA, 0, sizeof(R) * N, s));
-  PISO_HIP(c, hipMemsetAsync(dC, 0, sizeof(R) * 2 * D * N, s));
-  PISO_HIP(c, hipMemsetAsync(dbu, 0, sizeof(R) * D * N, s));
-  PISO_HIP(c, hipMemsetAsync(dp1, 0, sizeof(R) * N, s));
-  if (du_np1) PISO_HIP(c, hipMemcpyAsync(duc, du_np1, sizeof(R) * D * N, hipMemcpyDeviceToDevice, s));
-  else PISO_HIP(c, hipMemsetAsync(duc, 0, sizeof(R) * D * N, s));
+  PISO_HIP(c, hipMemsetAsync(c->a_zero, 0, c->a_zero_bytes, s));   // dA, dC, dbu, dp1, uin, duc, mu, dnu
   if (dp_np1) PISO_HIP(c, hipMemcpyAsync(pbar, dp_np1, sizeof(R) * N, hipMemcpyDeviceToDevice, s));
   else PISO_HIP(c, hipMemsetAsync(pbar, 0, sizeof(R) * N, s));
   const bool skipP = (o->grad_path_flags & 2) != 0, skipV = (o->grad_path_flags & 1) != 0;
   piso_solve_info pi[2]{}, vi{};
   // corrector 2: output u***, p**; inputs u**, lag p*
-  PISO_HIP(c, hipMemsetAsync(uin, 0, sizeof(R) * D * N, s));
   const int warm = o->adjoint_warm_start ? 1 : 0;
   c->pcg_kind = kPcgAdj1 + 1;
-  int rc = do_corrector_bwd<R>(c, s, t.A, t.C, t.Pf, t.Dinv, t.h2, t.u1, t.p1, t.p2, duc, pbar, uin, dp1, dA, dC, dbu,
-                               dub, skipP, &o->pres, &pi[1], warm ? 1 : -1);
+  int rc = do_corrector_bwd<R>(c, s, t.A, t.C, t.Pf, t.Dinv, t.h2, t.u1, t.p1, t.p2, du_np1 ? du_np1 : duc, pbar, uin, dp1,
+                               dA, dC, dbu, dub, skipP, &o->pres, &pi[1], warm ? 1 : -1);
   c->pcg_kind = kPcgOther;
   if (rc < 0) return rc;
   // corrector 1: output u**, p*; inputs u*, lag p^n
-  PISO_HIP(c, hipMemcpyAsync(duc, uin, sizeof(R) * D * N, hipMemcpyDeviceToDevice, s));
-  PISO_HIP(c, hipMemcpyAsync(pbar, dp1, sizeof(R) * N, hipMemcpyDeviceToDevice, s));
-  PISO_HIP(c, hipMemsetAsync(uin, 0, sizeof(R) * D * N, s));
   c->pcg_kind = kPcgAdj1;
   c->pcg_same_op = !skipP;   // the second adjoint solve of the step: the same tape P_f
-  rc = do_corrector_bwd<R>(c, s, t.A, t.C, t.Pf, t.Dinv, t.h1, t.us, p_n, t.p1, duc, pbar, uin, dp_n, dA, dC, dbu, dub,
+  rc = do_corrector_bwd<R>(c, s, t.A, t.C, t.Pf, t.Dinv, t.h1, t.us, p_n, t.p1, uin, dp1, duc, dp_n, dA, dC, dbu, dub,
                            skipP, &o->pres, &pi[0], warm ? 0 : -1);
   c->pcg_kind = kPcgOther;
   c->pcg_same_op = false;
@@ -450,15 +452,14 @@ int do_step_backward(piso_ctx* c, hipStream_t s, const void* tape, const R* u_n,
   // velocity solve: mu = C^-T du*, db = mu, dC -= mu (x) u*
   if (!skipV) {
     R* mu = (R*)c->a_mu;
-    PISO_HIP(c, hipMemsetAsync(mu, 0, sizeof(R) * D * N, s));
-    rc = velocity_solve<R>(c, s, true, t.A, t.C, uin, mu, &o->vel, &vi);
+    rc = velocity_solve<R>(c, s, true, t.A, t.C, duc, mu, &o->vel, &vi);
     if (rc < 0) return rc;
     if ((rc = launch_outer_bwd<R>(c, s, t.C, mu, t.us, nullptr, dC, dA))) return rc;
     if ((rc = launch_axpy<R>(c, s, D * N, R(1), mu, dbu))) return rc;
     if (dp_n && o->grad_p_in_predictor)
       if ((rc = launch_gradT<R>(c, s, mu, nullptr, R(-1), dp_n))) return rc;
   }
-  rc = do_assemble_bwd<R>(c, s, u_n, nu, nu_field, ub, dt, dA, dC, dbu, du_n, dS, dnu, dub);
+  rc = do_assemble_bwd<R>(c, s, u_n, nu, nu_field, ub, dt, dA, dC, dbu, du_n, dS, dnu, dub, true);
   if (rc) return rc;
   if (info) {
     info->vel = vi;

@@ -224,6 +224,8 @@ struct piso_ctx {
   double* mix_scal = nullptr;         // [8] device scalars of the refinement residuals
   void *k_r = nullptr, *k_q = nullptr, *k_d0 = nullptr, *k_d1 = nullptr;   // PCG [N]
   void* k_r2 = nullptr;           // second residual buffer of the multigrid PCG [N]
+  void* a_zero = nullptr;         // the accumulators of piso_step_backward (dA .. dnu) in one block
+  size_t a_zero_bytes = 0;
   // adjoint pressure solutions of the last piso_step_backward per corrector (8 bytes per
   // cell), the warm start of the next call
   void* a_lam_hist[2] = {nullptr, nullptr};
