@@ -654,8 +654,9 @@ struct FdmStats {
   size_t N;
   const int* map;
   int rowfast;
-  const R* wt[3][3];   // [j][m]: [rung][n_m]
+  const R* wt[3][3];   // [j][m]: [rung][n_m], reciprocals of the weights' factors
 };
+constexpr int kFdmMaxSplits = 4;        // work-groups a plane
 constexpr int kFdmStatValues = 3 * 3;   // per rung: term, then smallest, largest, sum
 
 // Smallest, largest and sum of the ratios of the operator's face weights to each rung's over
@@ -689,9 +690,9 @@ __global__ void __launch_bounds__(kWG) k_fdm_stats(FdmStats<R> a, const R* __res
 #pragma unroll
       for (int q = 0; q < kFdmRungs; ++q) {
         if (q >= a.rungs) continue;
-        R m = a.wt[j][0][q * nx + i] * a.wt[j][a.pa][q * a.n[a.pa] + plane];
+        R m = a.wt[j][0][q * nx + i] * a.wt[j][a.pa][q * a.n[a.pa] + plane];   // 1 / weight
         if (a.dim == 3) m *= a.wt[j][a.oa][q * rows + o];
-        const float v = (float)(p / m);
+        const float v = (float)(p * m);
         const bool ok = v > 0.f && std::isfinite(v);
         lo[q][j] = ok ? fminf(lo[q][j], v) : 0.f;
         hi[q][j] = ok ? fmaxf(hi[q][j], v) : INFINITY;
@@ -728,73 +729,84 @@ __global__ void __launch_bounds__(kWG) k_fdm_stats(FdmStats<R> a, const R* __res
 
 // Rung of the smallest spread over all faces (relative to the plane means along a line axis),
 // and the means as that rung's profiles: prof[0] couplings along the line, prof[1] weights of
-// the x term, prof[2] weights of the third term.  One work-group.
-__global__ void __launch_bounds__(kWG)
+// the x term, prof[2] weights of the third term.  One work-group, a wave per rung, every load
+// of a plane's statistics in flight at once (one rung after the other, load by load, six rungs
+// took 13 us).
+constexpr int kFdmSelectWG = 512;
+static_assert(kFdmRungs <= kFdmSelectWG / 64, "a wave per rung");
+__global__ void __launch_bounds__(kFdmSelectWG)
 k_fdm_select(const float* __restrict__ st, int planes, int splits, int rungs, int dim, int pa, int line,
              int3 faces, int last_open, float limit, double* __restrict__ prof, FdmSel* sel) {
-  __shared__ float slo[kFdmRungs][kWaves], shi[kFdmRungs][kWaves];
-  __shared__ int best;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  __shared__ float spread[kFdmRungs];
+  const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
   const size_t G = (size_t)planes * splits;
-  auto of = [&](int q, int j, int v, int pl) {
-    const float* p = st + (size_t)(q * kFdmStatValues + 3 * j + v) * G + (size_t)pl * splits;
-    float t = p[0];
-    for (int s = 1; s < splits; ++s) t = v == 0 ? fminf(t, p[s]) : (v == 1 ? fmaxf(t, p[s]) : t + p[s]);
-    return t;
+  constexpr int S = kFdmMaxSplits;
+  // the three statistics of direction j on plane pl
+  auto stat = [&](int rung, int j, int pl, float (&v)[3]) {
+    float t[3][S];
+#pragma unroll
+    for (int k = 0; k < 3; ++k)
+#pragma unroll
+      for (int s = 0; s < S; ++s)
+        t[k][s] = st[(size_t)(rung * kFdmStatValues + 3 * j + k) * G + (size_t)pl * splits + min(s, splits - 1)];
+    v[0] = t[0][0];
+    v[1] = t[1][0];
+    v[2] = t[2][0];
+#pragma unroll
+    for (int s = 1; s < S; ++s) {   // a repeated split changes neither extreme
+      v[0] = fminf(v[0], t[0][s]);
+      v[1] = fmaxf(v[1], t[1][s]);
+      v[2] += s < splits ? t[2][s] : 0.f;
+    }
   };
   auto count = [&](int j, int pl) {
     if (j == pa && last_open && pl + 1 == planes) return 0;
     return j == 0 ? faces.x : (j == 1 ? faces.y : faces.z);
   };
-  for (int q = 0; q < rungs; ++q) {
+  if (q < rungs) {
     float lo = INFINITY, hi = 0.f;
-    for (int pl = threadIdx.x; pl < planes; pl += kWG)
-      for (int j = 0; j < dim; ++j) {
-        const int cnt = count(j, pl);
+    for (int pl = lane; pl < planes; pl += 64) {
+      float v[3][3];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) stat(q, min(j, dim - 1), pl, v[j]);
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        const int cnt = j < dim ? count(j, pl) : 0;
         if (cnt == 0) continue;
-        const float mean = line ? of(q, j, 2, pl) / (float)cnt : 1.f;
-        const float l = of(q, j, 0, pl) / mean, h = of(q, j, 1, pl) / mean;
+        const float mean = line ? v[j][2] / (float)cnt : 1.f;
+        const float l = v[j][0] / mean, h = v[j][1] / mean;
         lo = l > 0.f ? fminf(lo, l) : 0.f;     // also 0 where the mean is infinite or NaN
         hi = h > 0.f ? fmaxf(hi, h) : INFINITY;
       }
+    }
 #pragma unroll
     for (int s = 32; s > 0; s >>= 1) {
       lo = fminf(lo, __shfl_xor(lo, s, 64));
       hi = fmaxf(hi, __shfl_xor(hi, s, 64));
     }
-    if (lane == 0) {
-      slo[q][wave] = lo;
-      shi[q][wave] = hi;
-    }
+    if (lane == 0) spread[q] = lo > 0.f ? hi / lo : INFINITY;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    float top = INFINITY;
-    int bq = 0;
-    for (int q = 0; q < rungs; ++q) {
-      float lo = slo[q][0], hi = shi[q][0];
-      for (int w = 1; w < kWaves; ++w) {
-        lo = fminf(lo, slo[q][w]);
-        hi = fmaxf(hi, shi[q][w]);
-      }
-      const float spread = lo > 0.f ? hi / lo : INFINITY;
-      if (spread < top) {
-        top = spread;
-        bq = q;
-      }
+  float top = INFINITY;
+  int best = 0;
+  for (int k = 0; k < rungs; ++k)
+    if (spread[k] < top) {
+      top = spread[k];
+      best = k;
     }
-    sel->q = best = bq;
+  if (threadIdx.x == 0) {
+    sel->q = best;
     sel->kappa = top;
     sel->bad = top <= limit ? 0 : 1;
   }
-  __syncthreads();
   if (!line) return;
-  for (int pl = threadIdx.x; pl < planes; pl += kWG)
-    for (int j = 0; j < dim; ++j) {
-      const int cnt = count(j, pl);
-      const int slot = j == pa ? 0 : (j == 0 ? 1 : 2);
-      prof[(size_t)slot * planes + pl] = cnt ? (double)of(best, j, 2, pl) / cnt : 0.0;
-    }
+  for (int e = threadIdx.x; e < planes * dim; e += kFdmSelectWG) {
+    const int j = e / planes, pl = e - j * planes, cnt = count(j, pl);
+    float v[3];
+    stat(best, j, pl, v);
+    const int slot = j == pa ? 0 : (j == 0 ? 1 : 2);
+    prof[(size_t)slot * planes + pl] = cnt ? (double)v[2] / cnt : 0.0;
+  }
 }
 
 // ------------------------------------------------------------------------- host side
@@ -825,6 +837,11 @@ std::vector<R> narrow(const std::vector<double>& v) {
   return std::vector<R>(v.begin(), v.end());
 }
 
+std::vector<double> reciprocal(std::vector<double> v) {
+  for (double& x : v) x = 1.0 / x;
+  return v;
+}
+
 template <typename R>
 int upload_plan(piso_ctx* c, const FdmPlan& p) {
   FdmState& f = c->fdm;
@@ -835,7 +852,7 @@ int upload_plan(piso_ctx* c, const FdmPlan& p) {
       if (int rc = upload(c, &f.lam[m], narrow<R>(p.lam[m]))) return rc;
     }
     for (int j = 0; j < p.dim; ++j)
-      if (int rc = upload(c, &f.wt[j][m], narrow<R>(p.wt[j][m]))) return rc;
+      if (int rc = upload(c, &f.wt[j][m], narrow<R>(reciprocal(p.wt[j][m])))) return rc;
   }
   std::vector<double> ones(p.rungs, 1.0 / c->N);
   for (int m = 0; m < p.dim; ++m)
@@ -1112,7 +1129,7 @@ int fdm_build(piso_ctx* c, const piso_domain_desc* desc, const Topology& topo) {
     const int pa = f.line == 2 ? 2 : 1, oa = pa == 1 ? 2 : 1;
     f.planes = f.n[pa];
     const int units = f.n[oa] * ((f.n[0] + 63) / 64);
-    f.splits = std::max(1, std::min({4, 512 / f.planes, (units + kWaves - 1) / kWaves}));
+    f.splits = std::max(1, std::min({kFdmMaxSplits, 512 / f.planes, (units + kWaves - 1) / kWaves}));
     if (int rc = dev_alloc(c, (void**)&f.stats,
                            sizeof(float) * kFdmRungs * kFdmStatValues * (size_t)f.planes * f.splits))
       return rc;
@@ -1157,7 +1174,7 @@ int fdm_setup(piso_ctx* c, hipStream_t s, const R* Pf) {
     *nf[m] = m == a.pa || f.wrap[m] ? cells : cells / f.n[m] * (f.n[m] - 1);
   }
   k_fdm_stats<R><<<f.planes * f.splits, kWG, 0, s>>>(a, Pf, f.stats);
-  k_fdm_select<<<1, kWG, 0, s>>>(f.stats, f.planes, f.splits, f.rungs, c->dim, a.pa, f.line >= 0 ? 1 : 0, faces,
+  k_fdm_select<<<1, kFdmSelectWG, 0, s>>>(f.stats, f.planes, f.splits, f.rungs, c->dim, a.pa, f.line >= 0 ? 1 : 0, faces,
                                  f.wrap[a.pa] ? 0 : 1, kFdmMaxSpread, f.prof, f.sel);
   if (f.line >= 0) {
     const FdmLine<R> l = line_args<R>(c);
