@@ -67,7 +67,7 @@ constexpr int kFdmPad = 4;   // LDS row padding: the 16 rows (row tiles) or the 
 
 template <typename R>
 struct FdmRow {
-  int n, rows, kc, mt, splits, mper, ntiles, ld;   // mper: output tiles per split
+  int n, rows, kc, mt, splits, mper, ks, ntiles, ld;   // mper: output tiles per split, ks: waves sharing one
   uint32_t div_lo, div_hi;                         // division by n (or n / 4)
   int div_sh, quad;
   const int* map;
@@ -242,21 +242,39 @@ __global__ void __launch_bounds__(64 * kFdmMaxWaves) k_fdm_row(FdmRow<R> a) {
     for (int e = tid; e < (16 * NT - rows) * a.n; e += nth) X[(rows + e / a.n) * a.ld + e % a.n] = R(0);
     __syncthreads();
     const int mend = min(a.mt, (sp + 1) * a.mper);
-    for (int mt = sp * a.mper + wave; mt < mend; mt += nth >> 6) {
+    // with ks > 1 each wave has one output tile and a part of its sum (mper * ks waves)
+    const int wk = wave % a.ks, wm = wave / a.ks, k0 = a.kc * wk / a.ks, k1 = a.kc * (wk + 1) / a.ks;
+    for (int m = wm; m < a.mper; m += (nth >> 6) / a.ks) {
+      const int mt = sp * a.mper + m;
       V4 acc[NT];
 #pragma unroll
       for (int t = 0; t < NT; ++t) acc[t] = V4{R(0), R(0), R(0), R(0)};
-      const R* vp = Vq + ((size_t)mt * a.kc * 64 + lane) * 4;
+      if (mt < mend) {
+        const R* vp = Vq + ((size_t)mt * a.kc * 64 + lane) * 4;
 #pragma unroll 4
-      for (int k = 0; k < a.kc; ++k) {
-        const V4 av = *reinterpret_cast<const V4*>(vp + (size_t)k * 256);
+        for (int k = k0; k < k1; ++k) {
+          const V4 av = *reinterpret_cast<const V4*>(vp + (size_t)k * 256);
 #pragma unroll
-        for (int t = 0; t < NT; ++t) {
-          const V4 bv = lds4<R>(X + (t * 16 + nl) * a.ld + k * 16 + 4 * g);
+          for (int t = 0; t < NT; ++t) {
+            const V4 bv = lds4<R>(X + (t * 16 + nl) * a.ld + k * 16 + 4 * g);
 #pragma unroll
-          for (int u = 0; u < 4; ++u) acc[t] = mma(av[u], bv[u], acc[t]);
+            for (int u = 0; u < 4; ++u) acc[t] = mma(av[u], bv[u], acc[t]);
+          }
         }
       }
+      if (a.ks > 1) {   // every wave is here once
+        R* part = X + (size_t)16 * NT * a.ld + ((size_t)wm * a.ks * 64 + lane) * 4 * NT;
+        if (wk > 0) {
+#pragma unroll
+          for (int t = 0; t < NT; ++t) sts4<R>(part + (size_t)wk * 256 * NT + 4 * t, acc[t]);
+        }
+        __syncthreads();
+        if (wk > 0) continue;
+        for (int w = 1; w < a.ks; ++w)
+#pragma unroll
+          for (int t = 0; t < NT; ++t) acc[t] += lds4<R>(part + (size_t)w * 256 * NT + 4 * t);
+      }
+      if (mt >= mend) continue;
       const int col = mt * 16 + 4 * g;
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
@@ -676,27 +694,44 @@ __global__ void __launch_bounds__(kWG) k_fdm_stats(FdmStats<R> a, const R* __res
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int lg = xcd_logical_group(), plane = lg / a.splits, sp = lg % a.splits;
   const int nx = a.n[0], segs = (nx + 63) / 64, rows = a.n[a.oa];
-  for (int w = sp * kWaves + wave; w < rows * segs; w += a.splits * kWaves) {
-    const int o = w / segs, i = (w - o * segs) * 64 + lane;
-    if (i >= nx) continue;
-    size_t P = (size_t)plane * a.stride[a.pa] + (size_t)o * a.stride[a.oa] + i;
-    if (a.map) P = a.map[a.rowfast ? (size_t)i * (a.N / nx) + P / nx : P];
+  constexpr int U = 4;   // row segments whose loads are in flight together
+  const int step = a.splits * kWaves;
+  for (int w0 = sp * kWaves + wave; w0 < rows * segs; w0 += U * step) {
+    R p[U][3];
+    int oo[U], ii[U];
+    bool on[U];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
-      if (j >= a.dim) continue;
-      const int pos = j == 0 ? i : (j == a.pa ? plane : o);
-      if (pos + 1 >= a.n[j] && !a.wrap[j]) continue;
-      const R p = Pf[(size_t)a.perm[j] * a.N + P];
+    for (int u = 0; u < U; ++u) {
+      const int w = min(w0 + u * step, rows * segs - 1);
+      oo[u] = w / segs;
+      ii[u] = (w - oo[u] * segs) * 64 + lane;
+      on[u] = w0 + u * step < rows * segs && ii[u] < nx;
+      const int i = min(ii[u], nx - 1);
+      size_t P = (size_t)plane * a.stride[a.pa] + (size_t)oo[u] * a.stride[a.oa] + i;
+      if (a.map) P = a.map[a.rowfast ? (size_t)i * (a.N / nx) + P / nx : P];
 #pragma unroll
-      for (int q = 0; q < kFdmRungs; ++q) {
-        if (q >= a.rungs) continue;
-        R m = a.wt[j][0][q * nx + i] * a.wt[j][a.pa][q * a.n[a.pa] + plane];   // 1 / weight
-        if (a.dim == 3) m *= a.wt[j][a.oa][q * rows + o];
-        const float v = (float)(p * m);
-        const bool ok = v > 0.f && std::isfinite(v);
-        lo[q][j] = ok ? fminf(lo[q][j], v) : 0.f;
-        hi[q][j] = ok ? fmaxf(hi[q][j], v) : INFINITY;
-        sum[q][j] += v;
+      for (int j = 0; j < 3; ++j) p[u][j] = j < a.dim ? Pf[(size_t)a.perm[j] * a.N + P] : R(0);
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (!on[u]) continue;
+      const int i = ii[u], o = oo[u];
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        if (j >= a.dim) continue;
+        const int pos = j == 0 ? i : (j == a.pa ? plane : o);
+        if (pos + 1 >= a.n[j] && !a.wrap[j]) continue;
+#pragma unroll
+        for (int q = 0; q < kFdmRungs; ++q) {
+          if (q >= a.rungs) continue;
+          R m = a.wt[j][0][q * nx + i] * a.wt[j][a.pa][q * a.n[a.pa] + plane];   // 1 / weight
+          if (a.dim == 3) m *= a.wt[j][a.oa][q * rows + o];
+          const float v = (float)(p[u][j] * m);
+          const bool ok = v > 0.f && std::isfinite(v);
+          lo[q][j] = ok ? fminf(lo[q][j], v) : 0.f;
+          hi[q][j] = ok ? fmaxf(hi[q][j], v) : INFINITY;
+          sum[q][j] += v;
+        }
       }
     }
   }
@@ -867,7 +902,7 @@ int upload_plan(piso_ctx* c, const FdmPlan& p) {
 // axis of mt output tiles and `units` columns or rows.  Wide tiles reuse a basis operand for
 // several instructions; narrow ones and splits keep about two work-groups per CU in flight.
 struct Shape {
-  int nt, splits, mper, waves;
+  int nt, splits, mper, waves, ks;
 };
 Shape shape_for(long units, int mt, int max_nt, bool may_split) {
   Shape s;
@@ -882,6 +917,7 @@ Shape shape_for(long units, int mt, int max_nt, bool may_split) {
   // as many waves as divide the output tiles evenly, at least 4 for the loads
   const int trips = (s.mper + kFdmMaxWaves - 1) / kFdmMaxWaves;
   s.waves = std::max(4, (s.mper + trips - 1) / trips);
+  s.ks = 1;
   return s;
 }
 
@@ -897,7 +933,7 @@ void launch_row(piso_ctx* c, hipStream_t s, int kind, FdmRow<R> a, const Shape& 
   const bool gather = MODE != 2 && (!a.quad || a.map);
   const bool qin = a.quad && !gather;   // as in the kernel
   div_magic((uint32_t)(qin ? a.n / 4 : a.n), a.div_lo, a.div_hi, a.div_sh);
-  const size_t lds = (size_t)16 * sh.nt * a.ld * sizeof(R);
+  const size_t lds = ((size_t)16 * sh.nt * a.ld + (sh.ks > 1 ? (size_t)sh.waves * 256 * sh.nt : 0)) * sizeof(R);
   const int wg = 64 * sh.waves;
   auto launch = [&](auto nt) {
     constexpr int NT = decltype(nt)::value;
@@ -931,7 +967,20 @@ template <typename R>
 Shape row_shape(const piso_ctx* c) {
   const int nx = c->fdm.n[0];
   const int max_nt = nx * sizeof(R) <= 1024 ? 4 : 2;   // tile within half the LDS
-  return shape_for((long)c->N / nx, (nx + 15) / 16, max_nt, true);
+  const int kc = (nx + 15) / 16;
+  Shape s = shape_for((long)c->N / nx, kc, max_nt, true);
+  // output rows split over work-groups leave one or two tiles to each: its waves then share a
+  // tile's sum, at least two 16-cell chunks each (256^2 FP32: 6.7 us for the update and 6.5 for
+  // the inverse with one of four waves at work on 16 chunks, 5.6 with eight on two each)
+  if (s.splits > 1) {
+    int ks = 1;
+    while (2 * ks * s.mper <= kFdmMaxWaves && kc >= 4 * ks) ks *= 2;
+    if (ks > 1) {
+      s.ks = ks;
+      s.waves = s.mper * ks;
+    }
+  }
+  return s;
 }
 
 template <typename R>
@@ -955,6 +1004,7 @@ FdmRow<R> row_args(piso_ctx* c, const Shape& sh, CgState* st) {
   a.kc = a.mt = (a.n + 15) / 16;
   a.splits = sh.splits;
   a.mper = sh.mper;
+  a.ks = sh.ks;
   a.ntiles = (a.rows + 16 * sh.nt - 1) / (16 * sh.nt);
   a.ld = a.kc * 16 + kFdmPad;
   a.quad = a.n % 4 == 0;
