@@ -848,22 +848,23 @@ k_fdm_select(const float* __restrict__ st, int planes, int splits, int rungs, in
 
 namespace {
 
-// V (or its transpose) of every rung in operand order, zero-padded to multiples of 16.
+// V (or its transpose) of every rung in operand order, zero-padded to multiples of 16.  Read in
+// memory order, each element to its place: lane 16 (k / 4) + (place of the output row), step
+// k % 4 of its 16 x 16 block.
 template <typename R>
 std::vector<R> pack(const FdmPlan& p, int m, bool fwd) {
   const int n = p.n[m], T = (n + 15) / 16;
   std::vector<R> out((size_t)p.rungs * T * T * 256, R(0));
+  int place[16];
+  for (int l = 0; l < 16; ++l) place[packed_row<R>(l)] = l;
+  const double* v = p.V[m].data();
   for (int q = 0; q < p.rungs; ++q)
-    for (int mt = 0; mt < T; ++mt)
-      for (int kc = 0; kc < T; ++kc)
-        for (int lane = 0; lane < 64; ++lane)
-          for (int t = 0; t < 4; ++t) {
-            const int o = mt * 16 + packed_row<R>(lane % 16), k = kc * 16 + 4 * (lane / 16) + t;
-            if (o >= n || k >= n) continue;
-            const size_t row = fwd ? k : o, col = fwd ? o : k;
-            out[((((size_t)q * T + mt) * T + kc) * 64 + lane) * 4 + t] =
-                (R)p.V[m][((size_t)q * n + row) * n + col];
-          }
+    for (int row = 0; row < n; ++row)
+      for (int col = 0; col < n; ++col, ++v) {
+        const int k = fwd ? row : col, o = fwd ? col : row;
+        const size_t block = ((size_t)q * T + o / 16) * T + k / 16;
+        out[(block * 64 + 16 * (k % 16 / 4) + place[o % 16]) * 4 + k % 4] = (R)*v;
+      }
   return out;
 }
 
