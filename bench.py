@@ -33,7 +33,7 @@ if ROOT not in sys.path:
 HBM_PEAK_GBPS = 8000.0
 CSRC = os.path.join(ROOT, "paper_2505_16992_amd", "csrc")
 DIGEST_SOURCES = ["piso_common.h", "piso_quad.h", "piso_krylov.hip", "piso_mg.hip", "piso_line.hip",
-                  "piso_zmarch.hip"]
+                  "piso_zmarch.hip", "piso_mma.h", "piso_fdm.hip"]
 
 
 def kernel_digest():
@@ -161,6 +161,15 @@ def time_extras(ctx, case, precision, u0, S):
     return out
 
 
+def fast_diagonalisation(ctx, dom):
+    """Whether the pressure PCG of these workloads (tensor-product boxes and the O-H cylinder,
+    whose operators it accepts) runs with the fast diagonalisation: the size rules of the
+    library, and no multigrid form asked for by name."""
+    if os.environ.get("PISO_MG_LINE") or os.environ.get("PISO_ZMARCH"):
+        return False
+    return max(max(b) for b in dom.blocks) <= 512 and (ctx.dim == 2 or ctx.N >= 1 << 14)
+
+
 def pcg_roofline(ctx, dom, opts, tm, workload, precision):
     """(roofline, pressure_cg) records from per-class kernel times tm = {class: (ms,
     launches)}: algorithmic bytes per launch of each fine-grid kernel class (each stream
@@ -186,6 +195,15 @@ def pcg_roofline(ctx, dom, opts, tm, workload, precision):
         # y, r, Dinv, Pf (d), level-1 correction -> z
         "mg_up0": ("k_mg_up0_q" if quad else "k_mg_up0", N * (d + 4) * es + (N // nch) * es),
     }
+    fdm = mg and fast_diagonalisation(ctx, dom)
+    if fdm:
+        line = zm = False
+        model["cg_update_restrict"] = ("k_fdm_row_update", N * 7 * es)   # x, r, d_new, q -> x, r', hat
+        model["mg_down0"] = ("k_fdm_row_forward", N * 2 * es)            # r -> hat
+        model["mg_up0"] = ("k_fdm_row_inverse", N * 3 * es)              # hat, r -> z
+        # between them, per launch: the products along the third axis (hat -> hat) and the line
+        # systems (hat, pivots -> hat), or the fused product of an axis without lines
+        model["mg_coarse"] = ("k_fdm_col, k_fdm_line", N * 7 * es // 3 if d == 3 else N * 3 * es)
     if zm:
         for k, name in (("cg_stencil", "k_zm_spmv"), ("cg_update_restrict", "k_zm_down"), ("mg_up0", "k_zm_up")):
             model[k] = (name, model[k][1])
@@ -209,7 +227,7 @@ def pcg_roofline(ctx, dom, opts, tm, workload, precision):
     fine = [k for k in model if k in per]
     if not fine:
         return None, None
-    dom_k = max(fine, key=lambda k: per[k]["total_ms"])
+    dom_k = max((k for k in fine if k != "mg_coarse"), key=lambda k: per[k]["total_ms"])   # of one kernel
     kname, kbytes = model[dom_k]
     avg = tm[dom_k][0] / tm[dom_k][1]
     ach = kbytes / (avg * 1e-3) / 1e9
@@ -221,9 +239,10 @@ def pcg_roofline(ctx, dom, opts, tm, workload, precision):
     iters = tm["cg_stencil"][1]
     it_ms = sum(ms for ms, _ in tm.values()) / max(iters, 1)
     it_bytes = sum(model[k][1] * tm[k][1] for k in fine) / max(iters, 1)
-    pcg = {"preconditioner": "multigrid" if mg else "jacobi",
-           "fine_smoother": ("lines along %s" % "xyz"[ctx.mg_line_axis]) if mg and ctx.mg_line_axis else "point",
-           "mg_levels": [n for n, _ in ctx.mg_levels] if mg else [],
+    pcg = {"preconditioner": "fast diagonalisation" if fdm else ("multigrid" if mg else "jacobi"),
+           "fine_smoother": None if fdm else (("lines along %s" % "xyz"[ctx.mg_line_axis])
+                                              if mg and ctx.mg_line_axis else "point"),
+           "mg_levels": [n for n, _ in ctx.mg_levels] if mg and not fdm else [],
            "iteration_us": round(1e3 * it_ms, 3),
            "fine_bytes_per_iteration": int(it_bytes),
            "GBps": round(it_bytes / (it_ms * 1e-3) / 1e9, 1),
@@ -245,6 +264,8 @@ def pcg_micro(ctx, case, precision, workload, iters, precond):
     ctx.assemble(sys_, u0, p0, nu, S, ub, case.dt)
     us = u0.clone()
     ctx.solve_velocity(sys_, us, opts.vel)
+    if precond == 1 and bool(ctx.mg_levels) and fast_diagonalisation(ctx, case.domain):
+        iters = min(iters, 6)   # a few digits each: the residual is exhausted soon after
     fixed = type(opts.pres)()
     fixed.rtol, fixed.max_iter, fixed.check_every, fixed.precond = 1e-30, iters, iters, precond
     fixed.inner_rtol, fixed.max_refine = 1e-30, 0

@@ -766,7 +766,7 @@ __global__ void __launch_bounds__(kWG) k_fdm_stats(FdmStats<R> a, const R* __res
 // and the means as that rung's profiles: prof[0] couplings along the line, prof[1] weights of
 // the x term, prof[2] weights of the third term.  One work-group, a wave per rung, every load
 // of a plane's statistics in flight at once (one rung after the other, load by load, six rungs
-// took 13 us).
+// took 13 - 14 us; now 5 - 7).
 constexpr int kFdmSelectWG = 512;
 static_assert(kFdmRungs <= kFdmSelectWG / 64, "a wave per rung");
 __global__ void __launch_bounds__(kFdmSelectWG)

@@ -43,7 +43,9 @@ constexpr int kPart3 = 13;       // BiCGStab: rh.r, r.r (+ b.b)    (9)
 constexpr int kPartS = 22;       // one-shot sums                  (2)
 constexpr int kPartRegions = 24;
 
-// Kernel classes of the solver timing (piso_get_timing).
+// Kernel classes of the solver timing (piso_get_timing).  With the fast diagonalisation the
+// multigrid's classes are the products along x at the start of a solve (Down0), fused with the
+// update (CgUpdateMg) and back (Up0), and the products and line systems between them (Coarse).
 // Kinds of pressure solve, for the iteration-count estimates of the host read-backs:
 // forward correctors 1 and 2, adjoint correctors 1 and 2, everything else.
 constexpr int kPcgFwd1 = 0, kPcgAdj1 = 2, kPcgOther = 4;
