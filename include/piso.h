@@ -525,6 +525,8 @@ typedef enum {
   PISO_TIME_MG_COARSE = 4,   /* multigrid kernels on the coarse levels */
   PISO_TIME_CG_UPDATE_MG = 5, /* multigrid PCG: x, r update fused with the fine-grid
                                  pre-smoothing (point smoothing: and the restriction) */
+  /* with the fast diagonalisation: DOWN0, CG_UPDATE_MG and UP0 are its products along x (first of
+     a solve, fused with the update, back), COARSE what lies between them */
   PISO_TIME_MG_SMOOTH0 = 6,  /* line smoothing: first pre-smoothing of a solve on the fine grid */
   PISO_TIME_KINDS = 7
 } piso_time_kind;

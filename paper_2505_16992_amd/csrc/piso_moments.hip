@@ -147,6 +147,7 @@ k_mom_acc(const R* __restrict__ x, int N, int nx, int ny, int ms, int axis, MomT
           double* __restrict__ state) {
   constexpr MomTuples T = mom_tuples<M, K>();
   constexpr int NA = T.n, REC = 1 + M + NA, W = kMomWG / 64, U = 4;
+  static_assert(W == 16, "a row of lanes per value");
   __shared__ double lds[(NA > M ? NA : M) * W];
   __shared__ double mu[M], sb[NA], old[REC], powA[M][K + 1], powB[M][K + 1];
   const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -161,10 +162,10 @@ k_mom_acc(const R* __restrict__ x, int N, int nx, int ny, int ms, int axis, MomT
       if (lane == 0) lds[q * W + wave] = t;
     }
     __syncthreads();
-    if (tid < NV) {
-      double t = 0.0;
-      for (int w = 0; w < W; ++w) t += lds[tid * W + w];
-      out[tid] = t;
+    for (int q0 = 4 * wave; q0 < NV; q0 += 4 * W) {   // a row of 16 lanes per value
+      const double t = row_sum(q0 * W + lane < NV * W ? lds[q0 * W + lane] : 0.0);
+      const int q = q0 + (lane >> 4);
+      if ((lane & 15) == 0 && q < NV) out[q] = t;
     }
     __syncthreads();
   };

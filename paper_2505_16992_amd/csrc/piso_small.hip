@@ -29,36 +29,6 @@ namespace {
 // PCG: two, whose products hide each other's latencies.
 constexpr int kBiWG = 256, kPcgWG = 512;
 
-// v of the lane that a row-wise pattern names (0xB1, 0x4E: quad permutations by xor 1 and 2,
-// 0x141, 0x140: mirrors of 8 and 16 lanes)
-template <int CTRL>
-__device__ __forceinline__ double dpp(double v) {
-  union {
-    double d;
-    int i[2];
-  } a, b;
-  a.d = v;
-  b.i[0] = __builtin_amdgcn_update_dpp(0, a.i[0], CTRL, 0xf, 0xf, false);
-  b.i[1] = __builtin_amdgcn_update_dpp(0, a.i[1], CTRL, 0xf, 0xf, false);
-  return b.d;
-}
-__device__ __forceinline__ double row_sum(double v) {   // over each 16 lanes
-  v += dpp<0xB1>(v);
-  v += dpp<0x4E>(v);
-  v += dpp<0x141>(v);
-  return v + dpp<0x140>(v);
-}
-__device__ __forceinline__ double lane_value(double v, int lane) {
-  union {
-    double d;
-    int i[2];
-  } a;
-  a.d = v;
-  a.i[0] = __builtin_amdgcn_readlane(a.i[0], lane);
-  a.i[1] = __builtin_amdgcn_readlane(a.i[1], lane);
-  return a.d;
-}
-
 // Sums of NV <= 8 values over a work-group of at most WG threads, the same in every thread, in
 // a fixed order: rows of 16 lanes, then the rows' sums of several values at a time.  One
 // barrier a call: successive calls alternate between the two halves of red, zeroed where the
@@ -512,10 +482,6 @@ k_pcg_small(Grid g, SmallFdm<R> a, const R* __restrict__ Pf, const R* __restrict
       // to the middle row; the null mode (column 0) without its means
       const int n = a.n1, m = n / 2, lane = threadIdx.x & 63, half = lane >> 5;
       const int steps = half ? n - 1 - m : m;
-      auto wave_total = [&](double t) {
-        t = row_sum(t);
-        return (lane_value(t, 0) + lane_value(t, 16)) + (lane_value(t, 32) + lane_value(t, 48));
-      };
       for (int c0 = (int)(threadIdx.x >> 6) * 32; c0 < a.n0; c0 += nth >> 1) {
         const bool on = c0 + (lane & 31) < a.n0;
         const int cc = on ? c0 + (lane & 31) : a.n0 - 1;
@@ -525,7 +491,7 @@ k_pcg_small(Grid g, SmallFdm<R> a, const R* __restrict__ Pf, const R* __restrict
         if (c0 == 0) {
           double t = 0.0;
           for (int j = lane; j < n; j += 64) t += (double)Y[j * a.ld];
-          t = wave_total(t);
+          t = wave_sum(t);
           if (lane == 0) rmean = t * ones;
           off = (lane & 31) == 0 ? (R)(t / n) : R(0);
         }

@@ -38,7 +38,6 @@ template <int NV, int WGS>
 __device__ __forceinline__ void zm_sum_all(double (&v)[NV]) {
   constexpr int NW = WGS / 64;
   __shared__ double lds[NV][NW];
-  __shared__ double res[NV];
 #pragma unroll
   for (int q = 0; q < NV; ++q) v[q] = wave_sum(v[q]);
   if ((threadIdx.x & 63) == 0) {
@@ -46,17 +45,13 @@ __device__ __forceinline__ void zm_sum_all(double (&v)[NV]) {
     for (int q = 0; q < NV; ++q) lds[q][threadIdx.x >> 6] = v[q];
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
 #pragma unroll
-    for (int q = 0; q < NV; ++q) {
-      double s = 0.0;
-      for (int w = 0; w < NW; ++w) s += lds[q][w];
-      res[q] = s;
-    }
+  for (int q = 0; q < NV; ++q) {
+    double s = 0.0;
+#pragma unroll
+    for (int w = 0; w < NW; ++w) s += lds[q][w];
+    v[q] = s;
   }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < NV; ++q) v[q] = res[q];
   __syncthreads();
 }
 
