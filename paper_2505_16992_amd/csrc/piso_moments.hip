@@ -137,8 +137,8 @@ constexpr MomTuples mom_tuples() {
 // few CUs that have a plane, and the merge, which one thread did over all pairs of
 // multi-indices with a table in memory.  Now a thread per multi-index merges, the products
 // are unrolled from constants, and each thread has four samples' loads in flight: on 96
-// planes of 96^2 FP64 samples three variables to order 4 take 40 us (181 before), to order 2
-// 17 us (181), six variables to order 2 43 us (246).
+// planes of 96^2 FP64 samples three variables to order 4 take 31 us (181 before), to order 2
+// 15 us (181), six variables to order 2 36 us (246).
 constexpr int kMomWG = 1024;
 
 template <typename R, int M, int K>
@@ -262,16 +262,17 @@ k_mom_acc(const R* __restrict__ x, int N, int nx, int ny, int ms, int axis, MomT
   if (q == 0) rec[0] = n;
 }
 
+// A thread per value of a plane's record (one per plane took 11 us for 96 planes of 34 values, now
+// 4).
 __global__ void __launch_bounds__(kWG)
 k_mom_final(int n_planes, int M, int NA, const double* __restrict__ state, double* __restrict__ mean,
             double* __restrict__ mom) {
-  const int p = blockIdx.x * kWG + threadIdx.x;
+  const int e = blockIdx.x * kWG + threadIdx.x, p = e / (M + NA), v = e - p * (M + NA);
   if (p >= n_planes) return;
-  const int REC = 1 + M + NA;
-  const double* rec = state + (size_t)p * REC;
-  const double n = rec[0];
-  for (int i = 0; i < M; ++i) mean[p * M + i] = rec[1 + i];
-  for (int q = 0; q < NA; ++q) mom[(size_t)p * NA + q] = n > 0 ? rec[1 + M + q] / n : 0.0;
+  const double* rec = state + (size_t)p * (1 + M + NA);
+  const double n = rec[0], x = rec[1 + v];
+  if (v < M) mean[p * M + v] = x;
+  else mom[(size_t)p * NA + v - M] = n > 0 ? x / n : 0.0;
 }
 
 template <typename R, int M>
@@ -358,25 +359,28 @@ k_field_grad(Grid g, const R* __restrict__ JT, const R* __restrict__ invJ, const
   }
 }
 
-// Budget terms from the accumulated states, one thread per plane and pair (one per plane
-// took 65 us for 96 planes, a chain of table searches; now 20): su (m = d, order >= 3, table tu),
-// sg[k] (m = d, order 2; k = 0 .. d-1, each REC_g long per plane), sup (m = 2d, order 2,
-// table tp).  Planes normal to axis a; tmet[p] = T_aa and jm[p] = J of the plane.
-// out[term][p][pair], terms P, eps, T, D, Pi.
-__device__ __forceinline__ int mom_find3(const MomTab& t, int i, int j, int k) {   // k < 0: a pair
-  int x = i < j ? i : j, y = i < j ? j : i, z = k;
-  if (z >= 0) {   // sorted
-    if (z < x) { const int w = x; x = z; z = y; y = w; }
-    else if (z < y) { const int w = y; y = z; z = w; }
-  }
-  for (int q = 0; q < t.n; ++q)
-    if (t.tup[q][0] == x && t.tup[q][1] == y && t.tup[q][2] == z && t.tup[q][3] < 0) return q;
-  return 0;   // not reached: every pair and (order >= 3) triple is in the table
+// Places of the sorted pair (i, j) and triple among the multi-indices of M variables.
+__device__ __forceinline__ int mom_pair(int M, int i, int j) {
+  const int x = min(i, j), y = max(i, j);
+  return x * M - x * (x - 1) / 2 + y - x;
+}
+__device__ __forceinline__ int mom_triple(int M, int i, int j, int k) {
+  const int x = min(min(i, j), k), z = max(max(i, j), k), y = i + j + k - x - z;
+  int at = M * (M + 1) / 2;   // behind the pairs
+  for (int a = 0; a < x; ++a) at += (M - a) * (M - a + 1) / 2;
+  for (int b = x; b < y; ++b) at += M - b;
+  return at + z - y;
 }
 
+// Budget terms from the accumulated states, one thread per plane and pair (one per plane that
+// searched the tables took 65 us for 96 planes, one per pair 20, with places by formula
+// 4): su
+// (m = d, order >= 3, nu multi-indices), sg[k] (m = d, order 2; k = 0 .. d-1, each REC_g long
+// per plane), sup (m = 2d, order 2).  Planes normal to axis a; tmet[p] = T_aa and jm[p] = J of
+// the plane.  out[term][p][pair], terms P, eps, T, D, Pi.
 template <int D>
 __global__ void __launch_bounds__(kWG)
-k_budget(int np, int a, int periodic, MomTab tu, MomTab tg, MomTab tp, const double* __restrict__ su,
+k_budget(int np, int a, int periodic, int nu, const double* __restrict__ su,
          const double* __restrict__ sg, const double* __restrict__ sup, const double* __restrict__ tmet,
          const double* __restrict__ jm, double wl0, double wl1, double wl2, double wh0, double wh1, double wh2,
          double* __restrict__ out) {
@@ -390,7 +394,7 @@ k_budget(int np, int a, int periodic, MomTab tu, MomTab tg, MomTab tp, const dou
     ++i;
   }
   j += i;
-  const int RU = 1 + D + tu.n, RG = 1 + D + tg.n, RP = 1 + 2 * D + tp.n;
+  const int RU = 1 + D + nu, RG = 1 + D + NP, RP = 1 + 2 * D + D * (2 * D + 1);
   auto at3 = [](int k, double v0, double v1, double v2) { return k == 0 ? v0 : (k == 1 ? v1 : v2); };
   const int pp = p + 1 < np ? p + 1 : (periodic ? 0 : -1);
   const int pm = p > 0 ? p - 1 : (periodic ? np - 1 : -1);
@@ -414,17 +418,16 @@ k_budget(int np, int a, int periodic, MomTab tu, MomTab tg, MomTab tp, const dou
   auto dU = [&](int v) {
     return d1([&](int pl) { return su[(size_t)pl * RU + 1 + v]; }, at3(v, wl0, wl1, wl2), at3(v, wh0, wh1, wh2));
   };
-  const int ij = mom_find3(tu, i, j, -1), ija = mom_find3(tu, i, j, a);
+  const int ij = mom_pair(D, i, j), ija = mom_triple(D, i, j, a);
   double eps = 0.0;
-  const int gij = mom_find3(tg, i, j, -1);
   for (int k = 0; k < D; ++k) {
     const double* r = sg + ((size_t)k * np + p) * RG;
-    eps += r[1 + D + gij] / r[0];
+    eps += r[1 + D + ij] / r[0];
   }
   const double* r = sup + (size_t)p * RP;
-  const double xij = r[1 + 2 * D + mom_find3(tp, i, D + j, -1)], xji = r[1 + 2 * D + mom_find3(tp, j, D + i, -1)];
+  const double xij = r[1 + 2 * D + mom_pair(2 * D, i, D + j)], xji = r[1 + 2 * D + mom_pair(2 * D, j, D + i)];
   out[((size_t)0 * np + p) * NP + q] =
-      -(Mu(p, mom_find3(tu, i, a, -1)) * dU(j) + Mu(p, mom_find3(tu, j, a, -1)) * dU(i));
+      -(Mu(p, mom_pair(D, i, a)) * dU(j) + Mu(p, mom_pair(D, j, a)) * dU(i));
   out[((size_t)1 * np + p) * NP + q] = eps * 2.0;
   out[((size_t)2 * np + p) * NP + q] = -d1([&](int pl) { return Mu(pl, ija); }, 0.0, 0.0);
   out[((size_t)3 * np + p) * NP + q] = d2([&](int pl) { return Mu(pl, ij); });
@@ -498,7 +501,7 @@ int moments_finalize(piso_ctx* c, hipStream_t s, int m, int order, int axis, con
                      double* mom) {
   int np, ms, na;
   if (moments_layout(c, axis, m, order, &np, &ms, &na)) return fail(c, PISO_E_ARG, "moments: bad layout");
-  k_mom_final<<<grid_cells(np), kWG, 0, s>>>(np, m, na, state, mean, mom);
+  k_mom_final<<<grid_cells(np * (m + na)), kWG, 0, s>>>(np, m, na, state, mean, mom);
   return mom_check(c, "k_mom_final");
 }
 
@@ -543,10 +546,6 @@ int budget(piso_ctx* c, hipStream_t s, int axis, int order_u, const double* su, 
   if (moments_layout(c, axis, D, order_u, &np, &ms, &nu) || order_u < 3 ||
       moments_layout(c, axis, D, 2, &np, &ms, &ng) || moments_layout(c, axis, 2 * D, 2, &np, &ms, &npp))
     return fail(c, PISO_E_ARG, "budget: single-block grid, axis < d, u moments of order >= 3");
-  MomTab tu, tg, tp;
-  momtab(D, order_u, tu);
-  momtab(D, 2, tg);
-  momtab(2 * D, 2, tp);
   const int* tb = &c->h_tab[0];
   const int periodic = (tb[kTabWrap] >> (2 * axis)) & 1;
   const int nx = tb[1], ny = tb[2];
@@ -566,10 +565,10 @@ int budget(piso_ctx* c, hipStream_t s, int axis, int order_u, const double* su, 
   const double wl[3] = {w[0], w[1], D == 3 ? w[2] : 0.0};
   const double wh[3] = {w[D], w[D + 1], D == 3 ? w[D + 2] : 0.0};
   if (D == 2)
-    k_budget<2><<<grid_cells(3 * np), kWG, 0, s>>>(np, axis, periodic, tu, tg, tp, su, sg, sup, tmet, jm, wl[0], wl[1], wl[2], wh[0],
+    k_budget<2><<<grid_cells(3 * np), kWG, 0, s>>>(np, axis, periodic, nu, su, sg, sup, tmet, jm, wl[0], wl[1], wl[2], wh[0],
                                   wh[1], wh[2], out);
   else
-    k_budget<3><<<grid_cells(6 * np), kWG, 0, s>>>(np, axis, periodic, tu, tg, tp, su, sg, sup, tmet, jm, wl[0], wl[1], wl[2], wh[0],
+    k_budget<3><<<grid_cells(6 * np), kWG, 0, s>>>(np, axis, periodic, nu, su, sg, sup, tmet, jm, wl[0], wl[1], wl[2], wh[0],
                                   wh[1], wh[2], out);
   return mom_check(c, "k_budget");
 }
