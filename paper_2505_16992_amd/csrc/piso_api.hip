@@ -153,9 +153,12 @@ int alloc_workspaces(piso_ctx* c) {
   PISO_HIP(c, hipMemset(c->cg, 0, sizeof(CgState)));
   PISO_HIP(c, hipMemset(c->bi, 0, sizeof(BiState)));
   PISO_HIP(c, hipMemset(c->partials, 0, (size_t)kPartRegions * kRedGrid * sizeof(double)));
-  PISO_HIP(c, hipHostMalloc((void**)&c->h_cg, sizeof(CgState), hipHostMallocDefault));
-  PISO_HIP(c, hipHostMalloc((void**)&c->h_bi, sizeof(BiState), hipHostMallocDefault));
-  PISO_HIP(c, hipHostMalloc((void**)&c->h_scal, 8 * sizeof(double), hipHostMallocDefault));
+  PISO_HIP(c, hipHostMalloc((void**)&c->h_cg, sizeof(CgState), hipHostMallocCoherent));
+  PISO_HIP(c, hipHostMalloc((void**)&c->h_bi, sizeof(BiState), hipHostMallocCoherent));
+  PISO_HIP(c, hipHostMalloc((void**)&c->h_scal, 9 * sizeof(double), hipHostMallocCoherent));
+  *c->h_cg = CgState{};
+  *c->h_bi = BiState{};
+  for (int q = 0; q < 9; ++q) c->h_scal[q] = 0.0;
   return PISO_OK;
 }
 

@@ -245,4 +245,9 @@ __device__ __forceinline__ int cell_of_thread(int N) {
   return P < N ? P : -1;
 }
 
+// Publishes the values that this thread has written to pinned memory (see wait_pinned).
+__device__ __forceinline__ void publish(unsigned long long* seq, unsigned long long n) {
+  __hip_atomic_store(seq, n, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 }  // namespace piso

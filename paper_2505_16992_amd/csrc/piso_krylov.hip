@@ -68,7 +68,7 @@ k_cg_init(Grid g, const R* __restrict__ Pf, const R* __restrict__ Dinv, const BT
 // host reads after the wait, one launch less than copying the state).
 __global__ void __launch_bounds__(kWG)
 k_cg_check(const double* __restrict__ partB, int G, int first, int max_k, double tol2, CgState* st,
-           const int* __restrict__ rejected, CgState* host) {
+           const int* __restrict__ rejected, CgState* host, unsigned long long seq) {
   double t[3];
   reduce_partials<3>(partB, G, t);
   if (threadIdx.x != 0) return;
@@ -95,7 +95,12 @@ k_cg_check(const double* __restrict__ partB, int G, int first, int max_k, double
       st->done = 1;
     }
   }
-  if (host) *host = *st;
+  if (host) {
+    CgState o = *st;
+    o.seq = seq - 1;
+    *host = o;
+    publish(&host->seq, seq);
+  }
 }
 
 template <typename R, int D, bool ZOP = false>
@@ -334,12 +339,13 @@ k_mix_resid(Grid g, const double* __restrict__ Pf, const double* __restrict__ rh
 
 template <int NV>
 __global__ void __launch_bounds__(kWG)
-k_finalize(const double* __restrict__ partials, int G, double* __restrict__ out) {
+k_finalize(const double* __restrict__ partials, int G, double* __restrict__ out, unsigned long long seq) {
   double t[NV];
   reduce_partials<NV>(partials, G, t);
   if (threadIdx.x == 0) {
 #pragma unroll
     for (int q = 0; q < NV; ++q) out[q] = t[q];
+    publish((unsigned long long*)(out + 8), seq);   // pinned
   }
 }
 
@@ -475,7 +481,8 @@ k_bi_mix_resid(Grid g, const double* __restrict__ A, const double* __restrict__ 
 
 template <int D>
 __global__ void __launch_bounds__(kWG)
-k_bi_check(const double* __restrict__ part3, int G, int first, int k_total, double tol2, BiState* st, BiState* host) {
+k_bi_check(const double* __restrict__ part3, int G, int first, int k_total, double tol2, BiState* st, BiState* host,
+           unsigned long long seq) {
   double t[3 * D];
   if (first) {
     reduce_partials<3 * D>(part3, G, t);
@@ -513,7 +520,12 @@ k_bi_check(const double* __restrict__ part3, int G, int first, int k_total, doub
     all &= st->done[c];
   }
   st->all_done = all;
-  if (host) *host = *st;   // pinned: what the host reads after the wait
+  if (host) {   // pinned: what the host reads after the wait
+    BiState o = *st;
+    o.seq = seq - 1;
+    *host = o;
+    publish(&host->seq, seq);
+  }
 }
 
 template <typename R, int D, bool TRANS>
@@ -998,6 +1010,23 @@ static int check(piso_ctx* c, const char* what) {
   return PISO_OK;
 }
 
+int wait_pinned(piso_ctx* c, hipStream_t s, const unsigned long long* seq, const char* what) {
+  const unsigned long long n = c->wait_seq;
+  for (unsigned spin = 1;; ++spin) {
+    if (__atomic_load_n(seq, __ATOMIC_ACQUIRE) == n) return PISO_OK;
+    __builtin_ia32_pause();
+    if (spin % 16384) continue;
+    if (hipStreamQuery(s) == hipErrorNotReady) {
+      (void)hipGetLastError();
+      continue;
+    }
+    const hipError_t e = hipStreamSynchronize(s);
+    if (e != hipSuccess) return fail(c, PISO_E_HIP, std::string(what) + ": " + hipGetErrorString(e));
+    if (__atomic_load_n(seq, __ATOMIC_ACQUIRE) == n) return PISO_OK;
+    return fail(c, PISO_E_HIP, std::string(what) + ": no state");
+  }
+}
+
 // Operands of the PCG iterations.  The solver copies the caller's coefficients and
 // iterate into context-owned buffers, so that every pointer an iteration uses belongs
 // to the context and a recorded iteration stays valid for the context's lifetime.
@@ -1125,7 +1154,7 @@ static int pcg_launched(piso_ctx* c, hipStream_t s, const PcgOps<R>& o, const BT
     k_cg_init<R, BT, 2><<<G, kWG, 0, s>>>(c->grid, o.Pf, o.Dinv, b, mean, sign, x, o.x, o.r, o.d0, o.pB);
   else
     k_cg_init<R, BT, 3><<<G, kWG, 0, s>>>(c->grid, o.Pf, o.Dinv, b, mean, sign, x, o.x, o.r, o.d0, o.pB);
-  k_cg_check<<<1, kWG, 0, s>>>(o.pB, G, 1, max_iter, tol2, st, o.fdm ? fdm_rejected(c) : nullptr, nullptr);
+  k_cg_check<<<1, kWG, 0, s>>>(o.pB, G, 1, max_iter, tol2, st, o.fdm ? fdm_rejected(c) : nullptr, nullptr, 0);
   if (int rc = check(c, "k_cg_init")) return rc;
   if (o.fdm) {
     if (int rc = fdm_apply<R>(c, s, (const R*)o.r, o.z, st, o.pB)) return rc;
@@ -1158,8 +1187,8 @@ static int pcg_launched(piso_ctx* c, hipStream_t s, const PcgOps<R>& o, const BT
   int chunk = std::max(check_every, (hint + 1) & ~1);
   int launched = 0;
   if (max_iter <= 0) {   // no iterations: the initial state alone
-    k_cg_check<<<1, kWG, 0, s>>>(o.pB, G, 0, max_iter, tol2, st, nullptr, c->h_cg);
-    PISO_HIP(c, hipStreamSynchronize(s));
+    k_cg_check<<<1, kWG, 0, s>>>(o.pB, G, 0, max_iter, tol2, st, nullptr, c->h_cg, ++c->wait_seq);
+    if (int rc = wait_pinned(c, s, &c->h_cg->seq, "k_cg_check")) return rc;
   }
   while (!c->h_cg->done && launched < max_iter) {
     const int n = std::min(chunk, max_iter - launched + 1);
@@ -1173,9 +1202,10 @@ static int pcg_launched(piso_ctx* c, hipStream_t s, const PcgOps<R>& o, const BT
       }
     }
     launched += n + (n & 1);
-    k_cg_check<<<1, kWG, 0, s>>>(o.pB, o.Gz, 0, max_iter, tol2, st, nullptr, c->h_cg);
+    k_cg_check<<<1, kWG, 0, s>>>(o.pB, o.Gz, 0, max_iter, tol2, st, nullptr, c->h_cg, ++c->wait_seq);
     if (int rc = check(c, "k_cg iteration")) return rc;
-    PISO_HIP(c, hipStreamSynchronize(s));
+    if (c->timing.enabled) PISO_HIP(c, hipStreamSynchronize(s));
+    else if (int rc = wait_pinned(c, s, &c->h_cg->seq, "k_cg iteration")) return rc;
     timing_collect(c);
   }
   if (c->h_cg->status == 0) hint = c->h_cg->iters;
@@ -1332,9 +1362,9 @@ int pressure_solve_mixed(piso_ctx* c, hipStream_t s, const double* Pf, const dou
       k_mix_resid<2><<<G, kWG, 0, s>>>(c->grid, Pf, rhs64, mean, x64, r32, pS);
     else
       k_mix_resid<3><<<G, kWG, 0, s>>>(c->grid, Pf, rhs64, mean, x64, r32, pS);
-    k_finalize<2><<<1, kWG, 0, s>>>(pS, G, c->h_scal);   // pinned
+    k_finalize<2><<<1, kWG, 0, s>>>(pS, G, c->h_scal, ++c->wait_seq);   // pinned
     if (int rc = check(c, "k_mix_resid")) return rc;
-    PISO_HIP(c, hipStreamSynchronize(s));
+    if (int rc = wait_pinned(c, s, (const unsigned long long*)(c->h_scal + 8), "k_mix_resid")) return rc;
     const double rr = c->h_scal[0], bb = c->h_scal[1];
     if (!std::isfinite(rr) || !std::isfinite(bb)) {
       status = PISO_E_NAN;
@@ -1450,8 +1480,9 @@ static int bicgstab_run(piso_ctx* c, hipStream_t s, bool trans, const R* A, cons
 #define BI_CHECK(FIRST, KT)                                                       \
   do {                                                                            \
     BiState* host = FIRST ? nullptr : c->h_bi;                                    \
-    if (D == 2) k_bi_check<2><<<1, kWG, 0, s>>>(p3, G, FIRST, KT, tol2, st, host); \
-    else k_bi_check<3><<<1, kWG, 0, s>>>(p3, G, FIRST, KT, tol2, st, host);       \
+    if (host) ++c->wait_seq;                                                      \
+    if (D == 2) k_bi_check<2><<<1, kWG, 0, s>>>(p3, G, FIRST, KT, tol2, st, host, c->wait_seq); \
+    else k_bi_check<3><<<1, kWG, 0, s>>>(p3, G, FIRST, KT, tol2, st, host, c->wait_seq);       \
   } while (0)
   R* iA = (R*)w.iA;
   R* ph = (R*)w.ph;
@@ -1507,7 +1538,7 @@ static int bicgstab_run(piso_ctx* c, hipStream_t s, bool trans, const R* A, cons
     int chunk = ilu ? ce : std::max(ce, hint);
     if (o->max_iter <= 0) {   // no iterations: the initial state alone
       BI_CHECK(0, 0);
-      PISO_HIP(c, hipStreamSynchronize(s));
+      if (int rc = wait_pinned(c, s, &c->h_bi->seq, "k_bi_check")) return rc;
     }
     while (!c->h_bi->all_done && it < o->max_iter) {
       const int n = std::min(chunk, o->max_iter - it);
@@ -1538,7 +1569,7 @@ static int bicgstab_run(piso_ctx* c, hipStream_t s, bool trans, const R* A, cons
       }
       BI_CHECK(0, it);
       if (int rc = check(c, "k_bi iteration")) return rc;
-      PISO_HIP(c, hipStreamSynchronize(s));
+      if (int rc = wait_pinned(c, s, &c->h_bi->seq, "k_bi iteration")) return rc;
     }
     if (!ilu) {
       hint = 0;
@@ -1619,14 +1650,14 @@ static int velocity_solve_mixed(piso_ctx* c, hipStream_t s, bool trans, const do
     if (D == 2) {
       if (trans) k_bi_mix_resid<2, true><<<G, kWG, 0, s>>>(c->grid, A, C, b, x, r32, p3);
       else k_bi_mix_resid<2, false><<<G, kWG, 0, s>>>(c->grid, A, C, b, x, r32, p3);
-      k_finalize<4><<<1, kWG, 0, s>>>(p3, G, c->h_scal);   // pinned
+      k_finalize<4><<<1, kWG, 0, s>>>(p3, G, c->h_scal, ++c->wait_seq);   // pinned
     } else {
       if (trans) k_bi_mix_resid<3, true><<<G, kWG, 0, s>>>(c->grid, A, C, b, x, r32, p3);
       else k_bi_mix_resid<3, false><<<G, kWG, 0, s>>>(c->grid, A, C, b, x, r32, p3);
-      k_finalize<6><<<1, kWG, 0, s>>>(p3, G, c->h_scal);
+      k_finalize<6><<<1, kWG, 0, s>>>(p3, G, c->h_scal, ++c->wait_seq);
     }
     if (int rc = check(c, "k_bi_mix_resid")) return rc;
-    PISO_HIP(c, hipStreamSynchronize(s));
+    if (int rc = wait_pinned(c, s, (const unsigned long long*)(c->h_scal + 8), "k_bi_mix_resid")) return rc;
     rel = 0.0;
     bool bad = false;
     for (int q = 0; q < D; ++q) {

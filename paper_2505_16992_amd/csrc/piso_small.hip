@@ -76,7 +76,7 @@ struct SmallSum {
 template <typename R, int D, bool TRANS, int CPT>
 __global__ void __launch_bounds__(kBiWG)
 k_bi_small(Grid g, const R* __restrict__ A, const R* __restrict__ C, const R* __restrict__ b, R* __restrict__ x,
-           int from_zero, BiState* st, BiState* host, double tol2, int max_iter) {
+           int from_zero, BiState* st, BiState* host, unsigned long long seq, double tol2, int max_iter) {
   extern __shared__ __align__(32) char smem[];
   __shared__ double red[2 * 8 * kBiWG / 16];
   double* op = (double*)smem;   // [D][N]
@@ -293,7 +293,9 @@ k_bi_small(Grid g, const R* __restrict__ A, const R* __restrict__ C, const R* __
       o.all_done &= done[c];
     }
     *st = o;
+    o.seq = seq - 1;
     *host = o;
+    publish(&host->seq, seq);
   }
 }
 
@@ -367,7 +369,7 @@ template <typename R, int CPT, bool STAGE>
 __global__ void __launch_bounds__(kPcgWG)
 k_pcg_small(Grid g, SmallFdm<R> a, const R* __restrict__ Pf, const R* __restrict__ bsrc,
             const double* __restrict__ mean, double sign, const R* x0, R* x, int gauge, double tol2, int max_k,
-            CgState* st, CgState* host) {
+            CgState* st, CgState* host, unsigned long long seq) {
   using V4 = typename Vec4<R>::T;
   extern __shared__ __align__(32) char smem[];
   __shared__ double red[2 * 8 * kPcgWG / 16];
@@ -632,7 +634,9 @@ k_pcg_small(Grid g, SmallFdm<R> a, const R* __restrict__ Pf, const R* __restrict
     o.status = status;
     o.zero_rhs = bb == 0.0 ? 1 : 0;
     *st = o;
+    o.seq = seq - 1;
     *host = o;
+    publish(&host->seq, seq);
   }
 }
 
@@ -640,11 +644,10 @@ k_pcg_small(Grid g, SmallFdm<R> a, const R* __restrict__ Pf, const R* __restrict
 
 namespace {
 
-int small_check(piso_ctx* c, hipStream_t s, const char* what) {
-  hipError_t e = hipGetLastError();
-  if (e == hipSuccess) e = hipStreamSynchronize(s);
+int small_check(piso_ctx* c, hipStream_t s, const unsigned long long* seq, const char* what) {
+  const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(c, PISO_E_HIP, std::string(what) + ": " + hipGetErrorString(e));
-  return PISO_OK;
+  return wait_pinned(c, s, seq, what);
 }
 
 int small_threads(int N, int wg) { return std::min(wg, (N + 63) / 64 * 64); }
@@ -694,12 +697,13 @@ template <typename R>
 int small_pcg(piso_ctx* c, hipStream_t s, const R* Pf, const R* b, const double* mean, double sign, const R* x0, R* x,
               bool gauge, double tol2, int max_iter) {
   const SmallFdm<R> a = small_fdm<R>(c);
+  const unsigned long long seq = ++c->wait_seq;
   const bool stage = small_fdm_lds<R>(a, c->N, true) <= kSmallLds;
   const size_t lds = small_fdm_lds<R>(a, c->N, stage);
   const int wg = small_threads(c->N, kPcgWG), cpt = (c->N + wg - 1) / wg;
 #define SMALL_PCG(CPT, STAGE)                                                                                     \
   k_pcg_small<R, CPT, STAGE><<<1, wg, lds, s>>>(c->grid, a, Pf, b, mean, sign, x0, x, gauge ? 1 : 0, tol2,     \
-                                                max_iter, c->cg, c->h_cg)
+                                                max_iter, c->cg, c->h_cg, seq)
 #define SMALL_PCG_C(CPT)             \
   do {                               \
     if (stage) SMALL_PCG(CPT, true); \
@@ -710,7 +714,7 @@ int small_pcg(piso_ctx* c, hipStream_t s, const R* Pf, const R* b, const double*
   else SMALL_PCG_C(4);
 #undef SMALL_PCG
 #undef SMALL_PCG_C
-  return small_check(c, s, "k_pcg_small");
+  return small_check(c, s, &c->h_cg->seq, "k_pcg_small");
 }
 
 bool small_bi_use(const piso_ctx* c) {
@@ -720,10 +724,11 @@ bool small_bi_use(const piso_ctx* c) {
 template <typename R>
 int small_bicgstab(piso_ctx* c, hipStream_t s, bool trans, const R* A, const R* C, const R* b, R* x, bool from_zero,
                    BiState* st, double tol2, int max_iter) {
+  const unsigned long long seq = ++c->wait_seq;
   const size_t lds = (size_t)c->dim * c->N * sizeof(double);
   const int wg = small_threads(c->N, kBiWG), cpt = (c->N + wg - 1) / wg;
 #define SMALL_BI(D, T, CPT) \
-  k_bi_small<R, D, T, CPT><<<1, wg, lds, s>>>(c->grid, A, C, b, x, from_zero ? 1 : 0, st, c->h_bi, tol2, \
+  k_bi_small<R, D, T, CPT><<<1, wg, lds, s>>>(c->grid, A, C, b, x, from_zero ? 1 : 0, st, c->h_bi, seq, tol2, \
                                               max_iter)
 #define SMALL_BI_C(D, T)                  \
   do {                                    \
@@ -741,7 +746,7 @@ int small_bicgstab(piso_ctx* c, hipStream_t s, bool trans, const R* A, const R* 
   }
 #undef SMALL_BI
 #undef SMALL_BI_C
-  return small_check(c, s, "k_bi_small");
+  return small_check(c, s, &c->h_bi->seq, "k_bi_small");
 }
 
 #define INST(R)                                                                                                    \
