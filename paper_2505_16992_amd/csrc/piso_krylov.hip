@@ -1184,6 +1184,9 @@ static int pcg_launched(piso_ctx* c, hipStream_t s, const PcgOps<R>& o, const BT
   // after convergence costs about as much as a read-back), later chunks check_every
   const int kind = c->pcg_kind >= 0 && c->pcg_kind <= kPcgOther ? c->pcg_kind : kPcgOther;
   int& hint = c->pcg_hint[pre][kind][hint_slot];
+  // (the fast diagonalisation's inner solves end after one to three iterations, fewer than a
+  // check_every of 4: it goes by the hint alone, and by pairs behind it)
+  if (o.fdm && hint > 0) check_every = 2;
   int chunk = std::max(check_every, (hint + 1) & ~1);
   int launched = 0;
   if (max_iter <= 0) {   // no iterations: the initial state alone
@@ -1208,7 +1211,7 @@ static int pcg_launched(piso_ctx* c, hipStream_t s, const PcgOps<R>& o, const BT
     else if (int rc = wait_pinned(c, s, &c->h_cg->seq, "k_cg iteration")) return rc;
     timing_collect(c);
   }
-  if (c->h_cg->status == 0) hint = c->h_cg->iters;
+  if (c->h_cg->status == 0) hint = std::max(c->h_cg->iters, 1);
   return PISO_OK;
 }
 
