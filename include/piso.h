@@ -38,7 +38,8 @@
  *
  * Streams: work is enqueued on the given stream (hipStream_t, may be 0).  The Krylov
  * solves read their convergence state back to the host every check_every iterations,
- * which synchronises that stream; everything else is asynchronous.
+ * which waits for the kernels enqueued before (u_star of piso_solve_velocity is complete when
+ * the call returns); everything else is asynchronous.
  *
  * Errors: a negative return is a hard error (outputs unspecified, message from
  * piso_last_error); a positive return is a soft status (outputs written; see the

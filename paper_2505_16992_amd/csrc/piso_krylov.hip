@@ -1578,10 +1578,15 @@ static int bicgstab_run(piso_ctx* c, hipStream_t s, bool trans, const R* A, cons
       hint = 0;
       for (int q = 0; q < D; ++q) hint = std::max(hint, c->h_bi->status[q] ? 0 : c->h_bi->iters[q]);
     }
-    // a component whose right-hand side is zero, untouched by the iterations
-    for (int q = 0; q < D; ++q)
-      if (c->h_bi->bb[q] == 0.0)
+    // a component whose right-hand side is zero, untouched by the iterations (from zero: it is
+    // zero); x is complete when the solve returns
+    bool zeroed = false;
+    for (int q = 0; q < D && !from_zero; ++q)
+      if (c->h_bi->bb[q] == 0.0) {
         PISO_HIP(c, hipMemsetAsync(x + (size_t)q * N, 0, sizeof(R) * (size_t)N, s));
+        zeroed = true;
+      }
+    if (zeroed) PISO_HIP(c, hipStreamSynchronize(s));
   }
 #undef BI_LAUNCH
 #undef BI_CHECK

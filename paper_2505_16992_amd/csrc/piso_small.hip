@@ -278,6 +278,8 @@ k_bi_small(Grid g, const R* __restrict__ A, const R* __restrict__ C, const R* __
 #pragma unroll
       for (int c = 0; c < D; ++c) x[(size_t)c * N + cell[u]] = (R)xv[u][c];
     }
+  __threadfence();
+  __syncthreads();   // every wave's part of x is in memory before the host sees the state
   if (threadIdx.x == 0) {
     BiState o{};
     o.tol2 = tol2;
