@@ -21,9 +21,12 @@ namespace piso {
 // The iteration index k lives here too: the update kernel's lead thread advances it,
 // and kernels take only its parity (slot) as an argument, so that a recorded sequence
 // of two iterations can be replayed as a graph.
+// A solve aims at tol2; where the caller's own tolerance met2 is wider (tol2 tightened for the
+// fast diagonalisation), one whose residual meets met2 and no longer falls ends there (FP32 near
+// the type's smallest numbers: it would go on to max_iter).
 struct CgState {
-  double rz[2];
-  double rr, bb, tol2, pad0;
+  double rz[2], rrp[2];
+  double rr, bb, tol2, met2;
   int done, iters, status, zero_rhs;
   int k, max_k, pad1, pad2;
   unsigned long long seq;   // pinned copy: number of the wait that this state answers
@@ -536,7 +539,7 @@ template <typename R>
 bool small_pcg_use(const piso_ctx* c);
 template <typename R>
 int small_pcg(piso_ctx* c, hipStream_t s, const R* Pf, const R* b, const double* mean, double sign, const R* x0, R* x,
-              bool gauge, double tol2, int max_iter);
+              bool gauge, double tol2, double met2, int max_iter);
 // ... and the Jacobi BiCGStab.
 bool small_bi_use(const piso_ctx* c);
 template <typename R>

@@ -67,7 +67,7 @@ k_cg_init(Grid g, const R* __restrict__ Pf, const R* __restrict__ Dinv, const BT
 // chunk of iterations (convergence of the latest residual; host: the pinned copy that the
 // host reads after the wait, one launch less than copying the state).
 __global__ void __launch_bounds__(kWG)
-k_cg_check(const double* __restrict__ partB, int G, int first, int max_k, double tol2, CgState* st,
+k_cg_check(const double* __restrict__ partB, int G, int first, int max_k, double tol2, double met2, CgState* st,
            const int* __restrict__ rejected, CgState* host, unsigned long long seq) {
   double t[3];
   reduce_partials<3>(partB, G, t);
@@ -75,6 +75,7 @@ k_cg_check(const double* __restrict__ partB, int G, int first, int max_k, double
   if (first) {
     st->bb = t[2];
     st->tol2 = tol2;
+    st->met2 = met2;
     st->status = 0;
     st->done = 0;
     st->iters = 0;
@@ -110,17 +111,19 @@ k_cg_spmv(Grid g, const R* __restrict__ Pf, const R* __restrict__ Dinv, const R*
           const double* __restrict__ partB, double* __restrict__ partA, int Gp, int par) {
   // the state and the partials are loaded together, before the first wait
   const int done = st->done, kd = st->k, max_k = st->max_k;
-  const double tol2bb = st->tol2 * st->bb, rz_old = st->rz[par ^ 1];
+  const double tol2bb = st->tol2 * st->bb, met2bb = st->met2 * st->bb;
+  const double rz_old = st->rz[par ^ 1], rr_old = st->rrp[par ^ 1];
   double t[2];
   reduce_partials<2>(partB, Gp, t);
   if (done) return;
   const double rz = t[0], rr = t[1];
-  if (!std::isfinite(rz) || !std::isfinite(rr) || rr <= tol2bb || kd >= max_k) {
+  const bool met = rr <= tol2bb || (kd > 0 && rr <= met2bb && rr >= rr_old);
+  if (!std::isfinite(rz) || !std::isfinite(rr) || met || kd >= max_k) {
     if (lead()) {
       st->rr = rr;
       st->iters = kd;
       if (!std::isfinite(rz) || !std::isfinite(rr)) st->status = PISO_E_NAN;
-      else if (!(rr <= tol2bb)) st->status = PISO_NOT_CONVERGED;
+      else if (!met) st->status = PISO_NOT_CONVERGED;
       st->done = 1;
     }
     return;
@@ -128,7 +131,7 @@ k_cg_spmv(Grid g, const R* __restrict__ Pf, const R* __restrict__ Dinv, const R*
   const R beta = kd == 0 ? R(0) : (R)(rz / rz_old);
   if (lead()) {
     st->rz[par] = rz;
-    st->rr = rr;
+    st->rr = st->rrp[par] = rr;
   }
   const int N = g.N;
   int beg, end;
@@ -198,7 +201,8 @@ k_cg_spmv_q(Grid g, const R* __restrict__ Pf, const R* __restrict__ Dinv, const 
   // loaded together, before the first wait (at one trip per thread the prologue's
   // latency then overlaps the main loads)
   const int done = st->done, kd = st->k, max_k = st->max_k;
-  const double tol2bb = st->tol2 * st->bb, rz_old = st->rz[par ^ 1];
+  const double tol2bb = st->tol2 * st->bb, met2bb = st->met2 * st->bb;
+  const double rz_old = st->rz[par ^ 1], rr_old = st->rrp[par ^ 1];
   int qd0, end, stride;
   quad_sweep(g.N >> 2, qd0, end, stride);
   const int P00 = qd0 < end ? qd0 << 2 : 0;   // unconditional (clamped) loads: no branch to wait at
@@ -209,12 +213,13 @@ k_cg_spmv_q(Grid g, const R* __restrict__ Pf, const R* __restrict__ Dinv, const 
   reduce_partials<2>(partB, Gp, t);
   if (done) return;
   const double rz = t[0], rr = t[1];
-  if (!std::isfinite(rz) || !std::isfinite(rr) || rr <= tol2bb || kd >= max_k) {
+  const bool met = rr <= tol2bb || (kd > 0 && rr <= met2bb && rr >= rr_old);
+  if (!std::isfinite(rz) || !std::isfinite(rr) || met || kd >= max_k) {
     if (lead()) {
       st->rr = rr;
       st->iters = kd;
       if (!std::isfinite(rz) || !std::isfinite(rr)) st->status = PISO_E_NAN;
-      else if (!(rr <= tol2bb)) st->status = PISO_NOT_CONVERGED;
+      else if (!met) st->status = PISO_NOT_CONVERGED;
       st->done = 1;
     }
     return;
@@ -222,7 +227,7 @@ k_cg_spmv_q(Grid g, const R* __restrict__ Pf, const R* __restrict__ Dinv, const 
   const R beta = kd == 0 ? R(0) : (R)(rz / rz_old);
   if (lead()) {
     st->rz[par] = rz;
-    st->rr = rr;
+    st->rr = st->rrp[par] = rr;
   }
   auto dq = [&](int P, int, int) {
     const Q4<R> b = ldq(r, P), c = ldq(dold, P);
@@ -1147,14 +1152,15 @@ static int pcg_groups(const piso_ctx* c) {
 // iterate in o.x.
 template <typename R, typename BT>
 static int pcg_launched(piso_ctx* c, hipStream_t s, const PcgOps<R>& o, const BT* b, const double* mean, double sign,
-                        const R* x, int max_iter, int check_every, double tol2, int pre, int hint_slot) {
+                        const R* x, int max_iter, int check_every, double tol2, double met2, int pre,
+                        int hint_slot) {
   const int G = o.G;
   CgState* st = c->cg;
   if (c->dim == 2)
     k_cg_init<R, BT, 2><<<G, kWG, 0, s>>>(c->grid, o.Pf, o.Dinv, b, mean, sign, x, o.x, o.r, o.d0, o.pB);
   else
     k_cg_init<R, BT, 3><<<G, kWG, 0, s>>>(c->grid, o.Pf, o.Dinv, b, mean, sign, x, o.x, o.r, o.d0, o.pB);
-  k_cg_check<<<1, kWG, 0, s>>>(o.pB, G, 1, max_iter, tol2, st, o.fdm ? fdm_rejected(c) : nullptr, nullptr, 0);
+  k_cg_check<<<1, kWG, 0, s>>>(o.pB, G, 1, max_iter, tol2, met2, st, o.fdm ? fdm_rejected(c) : nullptr, nullptr, 0);
   if (int rc = check(c, "k_cg_init")) return rc;
   if (o.fdm) {
     if (int rc = fdm_apply<R>(c, s, (const R*)o.r, o.z, st, o.pB)) return rc;
@@ -1190,7 +1196,7 @@ static int pcg_launched(piso_ctx* c, hipStream_t s, const PcgOps<R>& o, const BT
   int chunk = std::max(check_every, (hint + 1) & ~1);
   int launched = 0;
   if (max_iter <= 0) {   // no iterations: the initial state alone
-    k_cg_check<<<1, kWG, 0, s>>>(o.pB, G, 0, max_iter, tol2, st, nullptr, c->h_cg, ++c->wait_seq);
+    k_cg_check<<<1, kWG, 0, s>>>(o.pB, G, 0, max_iter, tol2, met2, st, nullptr, c->h_cg, ++c->wait_seq);
     if (int rc = wait_pinned(c, s, &c->h_cg->seq, "k_cg_check")) return rc;
   }
   while (!c->h_cg->done && launched < max_iter) {
@@ -1205,7 +1211,7 @@ static int pcg_launched(piso_ctx* c, hipStream_t s, const PcgOps<R>& o, const BT
       }
     }
     launched += n + (n & 1);
-    k_cg_check<<<1, kWG, 0, s>>>(o.pB, o.Gz, 0, max_iter, tol2, st, nullptr, c->h_cg, ++c->wait_seq);
+    k_cg_check<<<1, kWG, 0, s>>>(o.pB, o.Gz, 0, max_iter, tol2, met2, st, nullptr, c->h_cg, ++c->wait_seq);
     if (int rc = check(c, "k_cg iteration")) return rc;
     if (c->timing.enabled) PISO_HIP(c, hipStreamSynchronize(s));
     else if (int rc = wait_pinned(c, s, &c->h_cg->seq, "k_cg iteration")) return rc;
@@ -1276,12 +1282,14 @@ static int pcg_run(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const
   // the tolerance where the V-cycle's small steps end close to a digit below it on average:
   // plain solves ask for 0.2 of it, which leaves the solutions as near as the V-cycle's did
   // (MIXED checks its own residual)
-  const double tol2 = rtol * rtol * (o.fdm && hint_slot == 0 ? 0.04 : 1.0);
+  const double met2 = rtol * rtol, tol2 = met2 * (o.fdm && hint_slot == 0 ? 0.04 : 1.0);
   if (small) {
-    if (int rc = small_pcg<R>(c, s, Pf, b, mean, sign, x0, xs, gauged != nullptr, tol2, max_iter)) return rc;
+    if (int rc = small_pcg<R>(c, s, Pf, b, mean, sign, x0, xs, gauged != nullptr, tol2, met2, max_iter))
+      return rc;
     *res = xs;
   } else {
-    if (int rc = pcg_launched<R, BT>(c, s, o, b, mean, sign, x0, max_iter, check_every, tol2, pre, hint_slot))
+    if (int rc = pcg_launched<R, BT>(c, s, o, b, mean, sign, x0, max_iter, check_every, tol2, met2, pre,
+                                     hint_slot))
       return rc;
     *res = o.x;
   }
@@ -1297,10 +1305,11 @@ static int pcg_run(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const
   if (small && gauged) *gauged = true;
   *iters_out += h.iters;
   *rel_out = h.bb > 0 ? std::sqrt(h.rr / h.bb) : 0.0;
-  const bool met = h.status == PISO_NOT_CONVERGED && h.rr <= rtol * rtol * h.bb;
-  if (h.status < 0) *status_out = h.status;
-  else if (h.status > 0 && !met) *status_out = std::max(*status_out, h.status);
-  else if (!h.done) *status_out = std::max(*status_out, (int)PISO_NOT_CONVERGED);
+  // whichever way it ended (limit of iterations, breakdown), a residual within the caller's
+  // tolerance is a solution
+  const int ended = h.status ? h.status : (h.done ? PISO_OK : PISO_NOT_CONVERGED);
+  if (ended < 0) *status_out = ended;
+  else if (ended > 0 && !(h.rr <= met2 * h.bb)) *status_out = std::max(*status_out, ended);
   return PISO_OK;
 }
 

@@ -370,8 +370,8 @@ __device__ __forceinline__ void small_product(const SmallFdm<R>& a, const R* V, 
 template <typename R, int CPT, bool STAGE>
 __global__ void __launch_bounds__(kPcgWG)
 k_pcg_small(Grid g, SmallFdm<R> a, const R* __restrict__ Pf, const R* __restrict__ bsrc,
-            const double* __restrict__ mean, double sign, const R* x0, R* x, int gauge, double tol2, int max_k,
-            CgState* st, CgState* host, unsigned long long seq) {
+            const double* __restrict__ mean, double sign, const R* x0, R* x, int gauge, double tol2, double met2,
+            int max_k, CgState* st, CgState* host, unsigned long long seq) {
   using V4 = typename Vec4<R>::T;
   extern __shared__ __align__(32) char smem[];
   __shared__ double red[2 * 8 * kPcgWG / 16];
@@ -453,7 +453,7 @@ k_pcg_small(Grid g, SmallFdm<R> a, const R* __restrict__ Pf, const R* __restrict
     t2[1] += bv * bv;
   }
   sum(t2);
-  double rr = t2[0], rz = 0.0, rz_old = 1.0;
+  double rr = t2[0], rr_old = rr, rz = 0.0, rz_old = 1.0;
   const double bb = t2[1];
   int k = 0, status = 0;
   bool done = false;
@@ -577,7 +577,8 @@ k_pcg_small(Grid g, SmallFdm<R> a, const R* __restrict__ Pf, const R* __restrict
       status = PISO_E_NAN;
       break;
     }
-    if (rr <= tol2 * bb) break;
+    if (rr <= tol2 * bb || (k > 0 && rr <= met2 * bb && rr >= rr_old)) break;
+    rr_old = rr;
     if (k >= max_k) {
       status = PISO_NOT_CONVERGED;
       break;
@@ -630,6 +631,7 @@ k_pcg_small(Grid g, SmallFdm<R> a, const R* __restrict__ Pf, const R* __restrict
     o.rr = rr;
     o.bb = bb;
     o.tol2 = tol2;
+    o.met2 = met2;
     o.done = 1;
     o.iters = o.k = k;
     o.max_k = max_k;
@@ -697,14 +699,14 @@ bool small_pcg_use(const piso_ctx* c) {
 
 template <typename R>
 int small_pcg(piso_ctx* c, hipStream_t s, const R* Pf, const R* b, const double* mean, double sign, const R* x0, R* x,
-              bool gauge, double tol2, int max_iter) {
+              bool gauge, double tol2, double met2, int max_iter) {
   const SmallFdm<R> a = small_fdm<R>(c);
   const unsigned long long seq = ++c->wait_seq;
   const bool stage = small_fdm_lds<R>(a, c->N, true) <= kSmallLds;
   const size_t lds = small_fdm_lds<R>(a, c->N, stage);
   const int wg = small_threads(c->N, kPcgWG), cpt = (c->N + wg - 1) / wg;
 #define SMALL_PCG(CPT, STAGE)                                                                                     \
-  k_pcg_small<R, CPT, STAGE><<<1, wg, lds, s>>>(c->grid, a, Pf, b, mean, sign, x0, x, gauge ? 1 : 0, tol2,     \
+  k_pcg_small<R, CPT, STAGE><<<1, wg, lds, s>>>(c->grid, a, Pf, b, mean, sign, x0, x, gauge ? 1 : 0, tol2, met2, \
                                                 max_iter, c->cg, c->h_cg, seq)
 #define SMALL_PCG_C(CPT)             \
   do {                               \
@@ -754,7 +756,7 @@ int small_bicgstab(piso_ctx* c, hipStream_t s, bool trans, const R* A, const R* 
 #define INST(R)                                                                                                    \
   template bool small_pcg_use<R>(const piso_ctx*);                                                                 \
   template int small_pcg<R>(piso_ctx*, hipStream_t, const R*, const R*, const double*, double, const R*, R*, bool, \
-                            double, int);                                                                                  \
+                            double, double, int);                                                                  \
   template int small_bicgstab<R>(piso_ctx*, hipStream_t, bool, const R*, const R*, const R*, R*, bool, BiState*,    \
                                  double, int);
 INST(float)

@@ -510,7 +510,8 @@ k_zm_spmv(Grid g, ZmTiles tl, const R* __restrict__ Pf, const R* __restrict__ zi
   __shared__ R lpx[2][WGS];      // x-face coefficient at cell 3
   __shared__ Q4<R> lpy[2][WGS];  // P_y of the row (the face the row above crosses)
   const int done = st->done, kd = st->k, max_k = st->max_k;
-  const double tol2bb = st->tol2 * st->bb, rz_old = st->rz[par ^ 1];
+  const double tol2bb = st->tol2 * st->bb, met2bb = st->met2 * st->bb;
+  const double rz_old = st->rz[par ^ 1], rr_old = st->rrp[par ^ 1];
   const ZmPos p = zm_pos(g, tl);
   const int N = g.N, S = p.nx * p.ny;
   const R* __restrict__ Py = Pf + (size_t)N;
@@ -550,12 +551,13 @@ k_zm_spmv(Grid g, ZmTiles tl, const R* __restrict__ Pf, const R* __restrict__ zi
   if (done) return;
   const double rz = t[0], rr = t[1];
   const bool lead = blockIdx.x == 0 && threadIdx.x == 0;
-  if (!std::isfinite(rz) || !std::isfinite(rr) || rr <= tol2bb || kd >= max_k) {
+  const bool met = rr <= tol2bb || (kd > 0 && rr <= met2bb && rr >= rr_old);
+  if (!std::isfinite(rz) || !std::isfinite(rr) || met || kd >= max_k) {
     if (lead) {
       st->rr = rr;
       st->iters = kd;
       if (!std::isfinite(rz) || !std::isfinite(rr)) st->status = PISO_E_NAN;
-      else if (!(rr <= tol2bb)) st->status = PISO_NOT_CONVERGED;
+      else if (!met) st->status = PISO_NOT_CONVERGED;
       st->done = 1;
     }
     return;
@@ -563,7 +565,7 @@ k_zm_spmv(Grid g, ZmTiles tl, const R* __restrict__ Pf, const R* __restrict__ zi
   const R beta = kd == 0 ? R(0) : (R)(rz / rz_old);
   if (lead) {
     st->rz[par] = rz;
-    st->rr = rr;
+    st->rr = st->rrp[par] = rr;
   }
   auto d1 = [&](int F) __attribute__((always_inline)) { return zin[F] + beta * dold[F]; };
   auto dv = [&](const Q4<R>& a, const Q4<R>& b) __attribute__((always_inline)) {

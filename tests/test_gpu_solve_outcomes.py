@@ -42,3 +42,29 @@ def test_velocity_is_complete_at_return(dims):
         torch.cuda.synchronize()
         assert info["status"] == 0 and torch.equal(x, y), (dims, k)
         assert bool(x[-1].any()) == bool(k % 2)
+
+
+def _pressure(ctx, sys, u, p, ub, scale, rtol, max_iter):
+    s = dict(sys, b_u=sys["b_u"] * scale)
+    o = ctx.default_opts().pres
+    o.rtol, o.max_iter = rtol, max_iter
+    x = torch.zeros_like(p)
+    return ctx.solve_pressure(s, u * scale, ub * scale, torch.zeros_like(p), x, o)
+
+
+@pytest.mark.parametrize("dims,periodic", [((64, 60), (0,)), ((35, 70), ()), ((18, 16), (0, 1)), ((48, 40, 32), (0, 2))])
+def test_residual_within_the_tolerance_is_a_solution(dims, periodic):
+    """Whichever way a pressure solve ends: stopped by its limit of iterations below the
+    tolerance, or (right-hand sides near FP32's smallest numbers, whose residuals stop falling)
+    soon after it has met the tolerance instead of running on to the limit."""
+    api = _api()
+    case = _case(dims, periodic)
+    ctx = api.Context(case.domain, "f32")
+    sys, u, p, ub = _system(ctx, case, random_state(case, seed=5))
+    for scale, limit in ((1.0, 4), (1e-36, 200)):
+        end = _pressure(ctx, sys, u, p, ub, scale, 1e-30, limit)
+        got = _pressure(ctx, sys, u, p, ub, scale, 2 * end["rel_residual"], limit)
+        say(dims, scale, end, got)
+        assert end["status"] == 1 and end["iters"] == limit
+        assert got["status"] == 0 and got["rel_residual"] <= 2 * end["rel_residual"]
+        assert got["iters"] <= min(limit, 40)
