@@ -470,11 +470,14 @@ k_pcg_small(Grid g, SmallFdm<R> a, const R* __restrict__ Pf, const R* __restrict
 #pragma unroll
     for (int u = 0; u < CPT; ++u) xv[u] = 0.0;
   }
-  // z = B r, the residual freed of its mean, and r.z, r.r.  B works in R.
+  // z = B r, the residual freed of its mean, and r.z, r.r.  B works in R, on r times a power of
+  // two that brings its norm to about one (B is linear; in FP32 the transforms of residuals below
+  // 1e-37 would lose their digits: 18 x 16 cells, right-hand sides of 2e-38, stayed at 2.7e-7).
   auto precondition = [&]() {
+    const double up = ldexp(1.0, -(ilogb(rr) / 2)), down = 1.0 / up;
 #pragma unroll
     for (int u = 0; u < CPT; ++u)
-      if (cell[u] >= 0) X[at[u]] = (R)(r[u]);
+      if (cell[u] >= 0) X[at[u]] = (R)(r[u] * up);
     __syncthreads();
     auto store_row = [&](R* D) {
       return [&, D](int col, int row, V4 v) { sts4<R>(D + row * a.ld + col, v); };
@@ -557,12 +560,12 @@ k_pcg_small(Grid g, SmallFdm<R> a, const R* __restrict__ Pf, const R* __restrict
     }
     small_product<R, false>(a, i0, Y, store_row(X));
     __syncthreads();
-    const double off = rmean;
+    const double off = rmean * down;
     double t[2] = {0.0, 0.0};
 #pragma unroll
     for (int u = 0; u < CPT; ++u) {
       if (cell[u] < 0) continue;
-      z[u] = (double)X[at[u]];
+      z[u] = (double)X[at[u]] * down;
       r[u] -= off;
       t[0] += r[u] * z[u];
       t[1] += r[u] * r[u];
