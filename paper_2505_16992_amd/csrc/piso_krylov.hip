@@ -1160,8 +1160,11 @@ static int pcg_launched(piso_ctx* c, hipStream_t s, const PcgOps<R>& o, const BT
     k_cg_init<R, BT, 2><<<G, kWG, 0, s>>>(c->grid, o.Pf, o.Dinv, b, mean, sign, x, o.x, o.r, o.d0, o.pB);
   else
     k_cg_init<R, BT, 3><<<G, kWG, 0, s>>>(c->grid, o.Pf, o.Dinv, b, mean, sign, x, o.x, o.r, o.d0, o.pB);
-  k_cg_check<<<1, kWG, 0, s>>>(o.pB, G, 1, max_iter, tol2, met2, st, o.fdm ? fdm_rejected(c) : nullptr, nullptr, 0);
+  const bool only = max_iter <= 0;   // no iterations: the initial state alone
+  k_cg_check<<<1, kWG, 0, s>>>(o.pB, G, 1, max_iter, tol2, met2, st, o.fdm ? fdm_rejected(c) : nullptr,
+                               only ? c->h_cg : nullptr, only ? ++c->wait_seq : 0);
   if (int rc = check(c, "k_cg_init")) return rc;
+  if (only) return wait_pinned(c, s, &c->h_cg->seq, "k_cg_check");
   if (o.fdm) {
     if (int rc = fdm_apply<R>(c, s, (const R*)o.r, o.z, st, o.pB)) return rc;
   } else if (o.mg) {
@@ -1195,10 +1198,6 @@ static int pcg_launched(piso_ctx* c, hipStream_t s, const PcgOps<R>& o, const BT
   if (o.fdm && hint > 0) check_every = 2;
   int chunk = std::max(check_every, (hint + 1) & ~1);
   int launched = 0;
-  if (max_iter <= 0) {   // no iterations: the initial state alone
-    k_cg_check<<<1, kWG, 0, s>>>(o.pB, G, 0, max_iter, tol2, met2, st, nullptr, c->h_cg, ++c->wait_seq);
-    if (int rc = wait_pinned(c, s, &c->h_cg->seq, "k_cg_check")) return rc;
-  }
   while (!c->h_cg->done && launched < max_iter) {
     const int n = std::min(chunk, max_iter - launched + 1);
     chunk = check_every;

@@ -84,3 +84,24 @@ def test_one_group_solve_of_any_scale(dims, periodic):
         got = _pressure(ctx, sys, u, p, ub, scale, 1e-7, 100)
         say(dims, scale, one, got)
         assert got["status"] == 0 and abs(got["iters"] - one["iters"]) <= 1
+
+
+@pytest.mark.parametrize("dims,periodic", [((18, 16), (0, 1)), ((128, 100), ()), ((48, 40, 32), (0, 2)), ((24, 24, 24), (0, 2))])
+def test_no_iterations(dims, periodic):
+    """A step whose solves may not iterate (piso_step takes max_iter = 0) reports the residual of
+    their starts, the same whatever the preconditioner."""
+    api = _api()
+    case = _case(dims, periodic)
+    ctx = api.Context(case.domain, "f64")
+    u, p, S, ub, nu = [dev(x, ctx.dtype) for x in random_state(case, seed=7)]
+    rels = []
+    for precond in (0, 1):
+        o = ctx.default_opts()
+        o.pres.precond = precond
+        ctx.step(u, p, nu, S, ub, case.dt, o)   # leaves its partial sums behind
+        o.pres.max_iter = 0
+        _, _, info = ctx.step(u, p, nu, S, ub, case.dt, o, info=True)
+        assert all(q["status"] == 1 and q["iters"] == 0 for q in info["pres"])
+        rels.append([q["rel_residual"] for q in info["pres"]])
+    say(dims, rels)
+    assert np.allclose(rels[0], rels[1], rtol=1e-8)
