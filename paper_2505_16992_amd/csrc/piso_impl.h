@@ -252,8 +252,9 @@ struct piso_ctx {
   // solve, then the first, second and later MIXED refinement sweeps
   int pcg_hint[3][5][4] = {};
   int pcg_kind = 4;               // kind of the next pressure solves (set around them)
-  // the same of the Jacobi BiCGStab: [transposed][plain, first, later MIXED sweeps]
-  int bi_hint[2][3] = {};
+  // the same of the Jacobi BiCGStab, of the last two solves: [transposed][plain, first, later
+  // MIXED sweeps]
+  int bi_hint[2][3][2] = {};
   int bi_slot = 0;                // slot of the next velocity solves
   // The PCG copies P_f and D^-1 into g_Pf / g_Dinv and builds the coarse operators from
   // them.  A caller that knows the operator has not changed since the last solve (the

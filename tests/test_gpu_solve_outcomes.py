@@ -105,3 +105,43 @@ def test_no_iterations(dims, periodic):
         rels.append([q["rel_residual"] for q in info["pres"]])
     say(dims, rels)
     assert np.allclose(rels[0], rels[1], rtol=1e-8)
+
+
+def test_easy_velocity_solve_after_a_hard_one():
+    """What a solve costs does not hang on the one before: an easy system after one that
+    converges in several times its iterations, and after one that fails, takes the time it takes
+    by itself (launching the other's iterations made it 3.5 to 5 times that)."""
+    api = _api()
+    case = _case((96, 96), (0,))
+    ctx = api.Context(case.domain, "f64")
+    u, p, S, ub, nu = random_state(case, seed=8)
+    t = ctx.dtype
+    o = ctx.default_opts().vel
+    o.precond = 0   # Jacobi alone, without the ILU(0) restart
+    x0 = dev(u, t)
+
+    def system(dt, nu):
+        sys = ctx.new_system()
+        ctx.assemble(sys, x0, dev(p, t), dev(nu, t), dev(S, t), dev(ub, t), dt)
+        return sys
+
+    def solve(sys, max_iter=500):
+        x = x0.clone()
+        o.max_iter = max_iter
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        info = ctx.solve_velocity(sys, x, o)
+        b.record()
+        b.synchronize()
+        return a.elapsed_time(b), info
+
+    easy, hard = system(0.01, nu), system(1e3, 0 * nu + 100.0)
+    alone = min(solve(easy)[0] for _ in range(8))
+    for limit, status in ((500, 0), (150, 1)):
+        after = []
+        for _ in range(6):
+            _, info = solve(hard, limit)
+            assert info["status"] == status
+            after.append(solve(easy)[0])
+        say("alone %.3f ms, after one of %d iterations (status %d): %.3f" % (alone, info["iters"], status, min(after)))
+        assert min(after) < 1.7 * alone
