@@ -251,8 +251,10 @@ typedef struct {
  *   PISO_MG_GRAPH=1    table-driven coarse-level kernels on single-block grids too
  *   PISO_NO_QUAD=1     no vectorised (four cells per thread) kernels
  *   PISO_NO_GRAPH=1    launch the PCG iterations one by one instead of replaying a graph
- *   PISO_CG_GROUPS=n   work-groups of the Krylov kernels (0 or unset: sized to the grid,
- *                      at most 2048) */
+ *   PISO_CG_GROUPS=n   work-groups of the pressure Krylov kernels (0 or unset: sized to the
+ *                      grid, at most 2048; solves of small grids that otherwise run whole in
+ *                      one work-group are then launched over the chip, as they are while
+ *                      their kernels are timed) */
 int piso_create(const piso_domain_desc* desc, int32_t precision, piso_ctx** out);
 void piso_destroy(piso_ctx* ctx);
 const char* piso_last_error(const piso_ctx* ctx);

@@ -725,6 +725,7 @@ int small_pcg(piso_ctx* c, hipStream_t s, const R* Pf, const R* b, const double*
 }
 
 bool small_bi_use(const piso_ctx* c) {
+  if (c->timing.enabled || c->cg_grid != 0) return false;   // as the pressure solve
   return c->N <= (c->dim == 3 ? 4 * kBiWG : kSmallCells);   // what the registers hold
 }
 

@@ -145,3 +145,27 @@ def test_easy_velocity_solve_after_a_hard_one():
             after.append(solve(easy)[0])
         say("alone %.3f ms, after one of %d iterations (status %d): %.3f" % (alone, info["iters"], status, min(after)))
         assert min(after) < 1.7 * alone
+
+
+@pytest.mark.parametrize("dims,periodic", [((20, 20), ()), ((9, 7, 5), (0, 2))])
+def test_launched_forms_on_request(dims, periodic, monkeypatch):
+    """Kernel timing and PISO_CG_GROUPS select the launched velocity solve on small grids: FP32
+    vectors there, FP64 ones in one work-group, so the results differ in their last bits."""
+    api = _api()
+    case = _case(dims, periodic)
+    state = random_state(case, seed=9)
+    ctx = api.Context(case.domain, "f32")
+    monkeypatch.setenv("PISO_CG_GROUPS", "4")
+    groups = api.Context(case.domain, "f32")
+    sys, u, _, _ = _system(ctx, case, state)
+    o = ctx.default_opts().vel
+    out = []
+    for c, timed in ((ctx, False), (ctx, True), (groups, False)):
+        c.set_timing(timed)
+        x = u.clone()
+        assert c.solve_velocity(sys, x, o)["status"] == 0
+        c.set_timing(False)
+        out.append(x)
+    small, timed, grouped = out
+    assert not torch.equal(small, timed) and torch.equal(timed, grouped)
+    assert rel(host(small), host(timed)) < 1e-5
