@@ -70,7 +70,7 @@ typedef enum {
 typedef enum {
   PISO_OK = 0,
   PISO_NOT_CONVERGED = 1,   /* solve stopped at max_iter above its tolerance */
-  PISO_BREAKDOWN = 2,       /* BiCGStab breakdown (rho or omega vanished) */
+  PISO_BREAKDOWN = 2,       /* BiCGStab: omega or r-hat.v vanished; CG: d.M d not positive */
   PISO_E_ARG = -1,          /* invalid argument (null pointer, bad size, bad option) */
   PISO_E_TOPOLOGY = -2,     /* invalid block layout (see piso_create) */
   PISO_E_HIP = -3,          /* a HIP runtime call failed */

@@ -367,6 +367,9 @@ __global__ void __launch_bounds__(kWG) k_mix_add(int n, double* __restrict__ x64
 //   bi1_k: rho_k = rh.r, convergence, beta_k, p = r + beta (p - omega v), v = C K^-1 p
 //   bi2_k: alpha_k = rho_k / rh.v, s = r - alpha v, t = C K^-1 s
 //   bi3_k: omega_k = t.s / t.t, x += K^-1 (alpha p + omega s), r = s - omega t
+// Where rho_k is exactly zero (a residual without a part along rh: one-way couplings, for one)
+// the iteration goes on from r as a new start, rh = p = r; it breaks down where omega or rh.v
+// vanish.
 
 template <typename R, int D, bool TRANS>
 __device__ __forceinline__ R coef_p(const R* __restrict__ C, int j, int P, int N) {
@@ -536,7 +539,7 @@ k_bi_check(const double* __restrict__ part3, int G, int first, int k_total, doub
 template <typename R, int D, bool TRANS>
 __global__ void __launch_bounds__(kWG)
 k_bi_1(Grid g, const R* __restrict__ iA, const R* __restrict__ C, const R* __restrict__ r,
-       const R* __restrict__ rh, const R* __restrict__ p_old, const R* __restrict__ v_old,
+       R* __restrict__ rh, const R* __restrict__ p_old, const R* __restrict__ v_old,
        R* __restrict__ p_new, R* __restrict__ v_new, BiState* st, const double* __restrict__ part3,
        double* __restrict__ part1, int Gp, int k) {
   if (st->all_done) return;
@@ -544,18 +547,19 @@ k_bi_1(Grid g, const R* __restrict__ iA, const R* __restrict__ C, const R* __res
   reduce_partials<2 * D>(part3, Gp, t);
   const int ko = k & 1, kp = (k + 1) & 1;
   R beta[D], omega[D];
-  bool act[D];
+  bool act[D], fresh[D];
   int nact = 0;
 #pragma unroll
   for (int c = 0; c < D; ++c) {
     act[c] = !st->done[c];
+    fresh[c] = false;
     beta[c] = R(0);
     omega[c] = R(0);
     if (!act[c]) continue;
     const double rho = t[c], rr = t[D + c];
     const bool conv = rr <= st->tol2 * st->bb[c];
     const bool bad = !std::isfinite(rho) || !std::isfinite(rr);
-    const bool brk = !conv && !bad && (rho == 0.0 || st->omega[kp][c] == 0.0);
+    const bool brk = !conv && !bad && st->omega[kp][c] == 0.0;
     if (conv || bad || brk) {
       if (lead()) {
         st->rr[c] = rr;
@@ -569,8 +573,9 @@ k_bi_1(Grid g, const R* __restrict__ iA, const R* __restrict__ C, const R* __res
     beta[c] = (R)((rho / st->rho[kp][c]) * (st->alpha[kp][c] / st->omega[kp][c]));
     omega[c] = (R)st->omega[kp][c];
     ++nact;
+    fresh[c] = rho == 0.0;   // then beta is 0, too
     if (lead()) {
-      st->rho[ko][c] = rho;
+      st->rho[ko][c] = fresh[c] ? rr : rho;
       st->rr[c] = rr;
     }
   }
@@ -616,6 +621,7 @@ k_bi_1(Grid g, const R* __restrict__ iA, const R* __restrict__ C, const R* __res
       }
       p_new[o + P] = pP;
       v_new[o + P] = v;
+      if (fresh[c]) rh[o + P] = r[o + P];
       acc[c] += (double)rh[o + P] * (double)v;
     }
   }
@@ -830,24 +836,25 @@ k_ilu_sweep(Grid g, const R* __restrict__ A, const R* __restrict__ C, const R* _
 // rho_k = rh.r, convergence and breakdown, beta_k; p = r + beta (p - omega v).
 template <typename R, int D>
 __global__ void __launch_bounds__(kWG)
-k_bii_p(int N, const R* __restrict__ r, const R* __restrict__ p_old, const R* __restrict__ v_old,
+k_bii_p(int N, const R* __restrict__ r, R* __restrict__ rh, const R* __restrict__ p_old, const R* __restrict__ v_old,
         R* __restrict__ p_new, BiState* st, const double* __restrict__ part3, int Gp, int k) {
   if (st->all_done) return;
   double t[2 * D];
   reduce_partials<2 * D>(part3, Gp, t);
   const int ko = k & 1, kp = (k + 1) & 1;
   R beta[D], omega[D];
-  bool act[D];
+  bool act[D], fresh[D];
   int nact = 0;
 #pragma unroll
   for (int c = 0; c < D; ++c) {
     act[c] = !st->done[c];
+    fresh[c] = false;
     beta[c] = omega[c] = R(0);
     if (!act[c]) continue;
     const double rho = t[c], rr = t[D + c];
     const bool conv = rr <= st->tol2 * st->bb[c];
     const bool bad = !std::isfinite(rho) || !std::isfinite(rr);
-    const bool brk = !conv && !bad && (rho == 0.0 || st->omega[kp][c] == 0.0);
+    const bool brk = !conv && !bad && st->omega[kp][c] == 0.0;
     if (conv || bad || brk) {
       if (lead()) {
         st->rr[c] = rr;
@@ -861,8 +868,9 @@ k_bii_p(int N, const R* __restrict__ r, const R* __restrict__ p_old, const R* __
     beta[c] = (R)((rho / st->rho[kp][c]) * (st->alpha[kp][c] / st->omega[kp][c]));
     omega[c] = (R)st->omega[kp][c];
     ++nact;
+    fresh[c] = rho == 0.0;   // then beta is 0, too
     if (lead()) {
-      st->rho[ko][c] = rho;
+      st->rho[ko][c] = fresh[c] ? rr : rho;
       st->rr[c] = rr;
     }
   }
@@ -878,6 +886,7 @@ k_bii_p(int N, const R* __restrict__ r, const R* __restrict__ p_old, const R* __
       if (!act[c]) continue;
       const size_t o = (size_t)c * N + P;
       p_new[o] = r[o] + beta[c] * (p_old[o] - omega[c] * v_old[o]);
+      if (fresh[c]) rh[o] = r[o];
     }
   }
 }
@@ -1563,8 +1572,8 @@ static int bicgstab_run(piso_ctx* c, hipStream_t s, bool trans, const R* A, cons
         R* vn = vb[(it + 1) & 1];
         if (ilu) {
           // p, M^-1 p, v = C M^-1 p; s, M^-1 s, t = C M^-1 s; x, r
-          if (D == 2) k_bii_p<R, 2><<<G, kWG, 0, s>>>(N, r, po, vo, pn, st, p3, G, it);
-          else k_bii_p<R, 3><<<G, kWG, 0, s>>>(N, r, po, vo, pn, st, p3, G, it);
+          if (D == 2) k_bii_p<R, 2><<<G, kWG, 0, s>>>(N, r, rh, po, vo, pn, st, p3, G, it);
+          else k_bii_p<R, 3><<<G, kWG, 0, s>>>(N, r, rh, po, vo, pn, st, p3, G, it);
           ILU_SWEEPS(pn, ph);
           BII_SPMV(1, ph, rh, vn, p1);
           if (D == 2) k_bii_s<R, 2><<<G, kWG, 0, s>>>(N, r, vn, sb, st, p1, G, it);

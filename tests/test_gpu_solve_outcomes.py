@@ -169,3 +169,39 @@ def test_launched_forms_on_request(dims, periodic, monkeypatch):
     small, timed, grouped = out
     assert not torch.equal(small, timed) and torch.equal(timed, grouped)
     assert rel(host(small), host(timed)) < 1e-5
+
+
+@pytest.mark.parametrize("precond", [0, 2])
+@pytest.mark.parametrize("prec", ["f64", "f32", "mixed"])
+@pytest.mark.parametrize("dims,periodic", [((20, 20), (0, 1)), ((64, 64), (0, 1)), ((12, 8, 32), (0, 1, 2))])
+def test_residual_without_a_part_along_its_start(dims, periodic, prec, precond):
+    """Couplings one way along x and a right-hand side in one cell: the first iteration leaves a
+    residual orthogonal to the start's to the last bit (rho = 0).  The solve goes on from it, in
+    one work-group and launched, with C and C^T, Jacobi and ILU(0): x = 0.25^k along the row."""
+    api = _api()
+    ctx = api.Context(_case(dims, periodic).domain, prec)
+    sys = ctx.new_system()
+    sys["A"].fill_(1.0)
+    sys["C"][1, 0].fill_(-0.25)   # the cell above along x depends on this one
+    sys["b"][:, 0] = 1.0
+    o = ctx.default_opts().vel
+    o.precond, o.rtol = precond, 1e-6 if prec == "f32" else 1e-10
+    row = 0.25 ** np.arange(dims[0]) / (1.0 - 0.25 ** dims[0])
+    tol = 1e-5 if prec == "f32" else 1e-9
+    for transposed in (False, True):
+        for timed in (False, True):
+            ctx.set_timing(timed)
+            if transposed:
+                g = ctx.new_system_grad()
+                zero = torch.zeros_like(sys["b"])
+                info = ctx.solve_velocity_backward(sys, zero, sys["b"], g, o)
+                x, want = g["db"], np.roll(row[::-1], 1)
+            else:
+                x = torch.zeros_like(sys["b"])
+                info = ctx.solve_velocity(sys, x, o)
+                want = row
+            ctx.set_timing(False)
+            got = host(x)
+            say(dims, prec, precond, transposed, timed, info["status"], info["iters"], rel(got[:, :dims[0]], want[None]))
+            assert info["status"] == 0
+            assert np.abs(got[:, :dims[0]] - want).max() < tol and np.abs(got[:, dims[0]:]).max() == 0
