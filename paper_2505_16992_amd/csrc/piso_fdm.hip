@@ -771,7 +771,8 @@ constexpr int kFdmSelectWG = 512;
 static_assert(kFdmRungs <= kFdmSelectWG / 64, "a wave per rung");
 __global__ void __launch_bounds__(kFdmSelectWG)
 k_fdm_select(const float* __restrict__ st, int planes, int splits, int rungs, int dim, int pa, int line,
-             int3 faces, int last_open, float limit, double* __restrict__ prof, FdmSel* sel) {
+             int3 faces, int last_open, float limit, double* __restrict__ prof, FdmSel* sel, CgState* host,
+             unsigned long long seq) {
   __shared__ float spread[kFdmRungs];
   const int lane = threadIdx.x & 63, q = threadIdx.x >> 6;
   const size_t G = (size_t)planes * splits;
@@ -833,6 +834,10 @@ k_fdm_select(const float* __restrict__ st, int planes, int splits, int rungs, in
     sel->q = best;
     sel->kappa = top;
     sel->bad = top <= limit ? 0 : 1;
+    if (host) {   // pinned
+      host->status = top <= limit ? 0 : kFdmRejected;
+      publish(&host->seq, seq);
+    }
   }
   if (!line) return;
   for (int e = threadIdx.x; e < planes * dim; e += kFdmSelectWG) {
@@ -1200,7 +1205,7 @@ int fdm_groups(const piso_ctx* c) {
 }
 
 template <typename R>
-int fdm_setup(piso_ctx* c, hipStream_t s, const R* Pf) {
+int fdm_setup(piso_ctx* c, hipStream_t s, const R* Pf, bool wait) {
   const FdmState& f = c->fdm;
   FdmStats<R> a{};
   a.dim = c->dim;
@@ -1225,8 +1230,15 @@ int fdm_setup(piso_ctx* c, hipStream_t s, const R* Pf) {
     *nf[m] = m == a.pa || f.wrap[m] ? cells : cells / f.n[m] * (f.n[m] - 1);
   }
   k_fdm_stats<R><<<f.planes * f.splits, kWG, 0, s>>>(a, Pf, f.stats);
-  k_fdm_select<<<1, kFdmSelectWG, 0, s>>>(f.stats, f.planes, f.splits, f.rungs, c->dim, a.pa, f.line >= 0 ? 1 : 0, faces,
-                                 f.wrap[a.pa] ? 0 : 1, kFdmMaxSpread, f.prof, f.sel);
+  k_fdm_select<<<1, kFdmSelectWG, 0, s>>>(f.stats, f.planes, f.splits, f.rungs, c->dim, a.pa,
+                                           f.line >= 0 ? 1 : 0, faces,
+                                           f.wrap[a.pa] ? 0 : 1, kFdmMaxSpread, f.prof, f.sel,
+                                           wait ? c->h_cg : nullptr, wait ? ++c->wait_seq : 0);
+  if (wait) {
+    if (int rc = fdm_check(c)) return rc;
+    if (int rc = wait_pinned(c, s, &c->h_cg->seq, "k_fdm_select")) return rc;
+    if (c->h_cg->status == kFdmRejected) return PISO_OK;
+  }
   if (f.line >= 0) {
     const FdmLine<R> l = line_args<R>(c);
     k_fdm_factor<R><<<l.slabs * ((l.cols + 31) / 32), 64, 0, s>>>(l);
@@ -1268,7 +1280,7 @@ int fdm_update_apply(piso_ctx* c, hipStream_t s, R* x, const R* rin, R* rout, co
 
 #define INST(R)                                                                                                \
   template int fdm_groups<R>(const piso_ctx*);                                                                 \
-  template int fdm_setup<R>(piso_ctx*, hipStream_t, const R*);                                                 \
+  template int fdm_setup<R>(piso_ctx*, hipStream_t, const R*, bool);                                           \
   template int fdm_apply<R>(piso_ctx*, hipStream_t, const R*, R*, CgState*, double*);                          \
   template int fdm_update_apply<R>(piso_ctx*, hipStream_t, R*, const R*, R*, const R*, const R*, R*, CgState*, \
                                    const double*, int, int, double*);

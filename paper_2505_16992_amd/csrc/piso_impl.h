@@ -276,6 +276,11 @@ struct piso_ctx {
   bool zm_force = false;          // PISO_ZMARCH=1: at every size
   bool mg_struct = false;         // single block: coarse levels indexed by position
   piso::FdmState fdm;
+  // The operator judged last was rejected: the next one's verdict is waited for before anything
+  // is launched for it.  Else the preconditioner and a chunk of iterations that return at once
+  // are launched first: an FP32 solve by the V-cycle alone, with that wait, without it took on
+  // 64 x 60 cells 685 / 707 / 740 us, on 32^3 536 / 556 / 635, on 96^3 1384 / 1421 / 1507.
+  bool fdm_doubt = false;
   int mg_line_axis = 0;           // fine-level line smoothing along this axis (0: point Jacobi)
   int mg_line_L = 0;              // cells per line segment (8 segments per line)
   // Dirichlet faces: owning cell and side (2 * axis + high), and the boundary cells
@@ -530,9 +535,10 @@ int zm_launch_up(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const R
 enum PcgPre { kPreJacobi = 0, kPreMg = 1, kPreFdm = 2 };
 // Builds the plan of a single tensor-product block (sets c->fdm.on); needs mg_build.
 int fdm_build(piso_ctx* c, const piso_domain_desc* desc, const Topology& topo);
-// Chooses the rung for the operator Pf on the device, or marks it as rejected.
+// Chooses the rung for the operator Pf on the device, or marks it as rejected.  wait: leaves the
+// verdict in c->h_cg->status, too (0 or kFdmRejected).
 template <typename R>
-int fdm_setup(piso_ctx* c, hipStream_t s, const R* Pf);
+int fdm_setup(piso_ctx* c, hipStream_t s, const R* Pf, bool wait);
 const int* fdm_rejected(const piso_ctx* c);   // device flag
 // Whole solves of small grids in one launch, the state left in c->cg and c->h_cg (c->h_bi):
 // the pressure PCG with fast diagonalisation (gauge: x is freed of its mean) ...

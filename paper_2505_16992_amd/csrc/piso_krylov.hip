@@ -1276,15 +1276,29 @@ static int pcg_run(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const
     PISO_HIP(c, hipMemcpyAsync((void*)o.Dinv, Dinv, es * (size_t)N, hipMemcpyDeviceToDevice, s));
     c->pcg_op_copied = true;
   }
+  // an operator that the fast diagonalisation turns down: the same solve with multigrid
+  auto rejected = [&]() {
+    const bool same_op = c->pcg_same_op;
+    c->pcg_op_reject = c->pcg_same_op = c->fdm_doubt = true;
+    const int rc = pcg_run<R, BT>(c, s, Pf, Dinv, b, mean, sign, x0, xs, res, rtol, max_iter, check_every, precond,
+                                  iters_out, rel_out, status_out, hint_slot, nullptr);
+    c->pcg_same_op = same_op;
+    return rc;
+  };
   if (!(c->pcg_op_pre >> pre & 1)) {
+    const bool wait = o.fdm && c->fdm_doubt;
     if (o.fdm) {
-      if (int rc = fdm_setup<R>(c, s, Pf)) return rc;
+      if (int rc = fdm_setup<R>(c, s, Pf, wait)) return rc;
     } else if (o.mg) {
       if (int rc = mg_setup<R>(c, s, o.Pf)) return rc;
     }
     c->pcg_op_src = Pf;
     c->pcg_op_es = (int)es;
     c->pcg_op_pre |= 1 << pre;
+    if (wait) {
+      if (c->h_cg->status == kFdmRejected) return rejected();
+      c->fdm_doubt = false;
+    }
   }
   // the fast diagonalisation gains one to five digits an iteration, so it ends anywhere below
   // the tolerance where the V-cycle's small steps end close to a digit below it on average:
@@ -1302,14 +1316,7 @@ static int pcg_run(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const
     *res = o.x;
   }
   const CgState& h = *c->h_cg;
-  if (h.status == kFdmRejected) {   // not an iteration was run: the same solve with multigrid
-    const bool same_op = c->pcg_same_op;
-    c->pcg_op_reject = c->pcg_same_op = true;
-    const int rc = pcg_run<R, BT>(c, s, Pf, Dinv, b, mean, sign, x0, xs, res, rtol, max_iter, check_every, precond,
-                                  iters_out, rel_out, status_out, hint_slot, nullptr);
-    c->pcg_same_op = same_op;
-    return rc;
-  }
+  if (h.status == kFdmRejected) return rejected();   // not an iteration was run
   if (small && gauged) *gauged = true;
   *iters_out += h.iters;
   *rel_out = h.bb > 0 ? std::sqrt(h.rr / h.bb) : 0.0;

@@ -205,3 +205,40 @@ def test_residual_without_a_part_along_its_start(dims, periodic, prec, precond):
             say(dims, prec, precond, transposed, timed, info["status"], info["iters"], rel(got[:, :dims[0]], want[None]))
             assert info["status"] == 0
             assert np.abs(got[:, :dims[0]] - want).max() < tol and np.abs(got[:, dims[0]:]).max() == 0
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32", "mixed"])
+@pytest.mark.parametrize("dims,periodic", [((64, 60), ()), ((24, 20), ()), ((32, 30, 28), (0, 2))])
+def test_rejected_operators(dims, periodic, prec, monkeypatch):
+    """A viscosity that varies over two decades at nu dt / h^2 >> 1: turned down by the fast
+    diagonalisation, the solve is the V-cycle's bit for bit, launched and on grids that otherwise
+    solve in one work-group.  From the second such operator on, nothing but its judgement is
+    launched ahead of the V-cycle; the next operator near a product is accepted."""
+    api = _api()
+    case = _case(dims, periodic)
+    u, p, S, ub, nu = random_state(case, seed=73)
+    wild = 10.0 ** np.random.default_rng(74).uniform(-2, 0, nu.shape)
+    out = []
+    for env in (None, "auto"):
+        if env:
+            monkeypatch.setenv("PISO_MG_LINE", env)
+        ctx = api.Context(case.domain, prec)
+        monkeypatch.delenv("PISO_MG_LINE", raising=False)
+        o = ctx.default_opts().pres
+        o.max_iter = 100
+        res = []
+        for k, (dt, v) in enumerate(((5.0, wild), (5.0, 1.5 * wild), (4.0, wild), (0.01, nu), (5.0, wild))):
+            case.dt = dt
+            sys, ud, pd, ubd = _system(ctx, case, (u, p, S, ub, v))
+            ctx.set_timing(k == 2)
+            x = pd.clone()
+            info = ctx.solve_pressure(sys, ud, ubd, pd, x, o)
+            count = {n: t[1] for n, t in ctx.get_timing().items()}
+            ctx.set_timing(False)
+            res.append((info["iters"], x, count))
+        out.append(res)
+    say(dims, prec, [[r[0] for r in res] for res in out], [res[2][2] for res in out])
+    for k in (0, 1, 2, 4):
+        assert out[0][k][0] == out[1][k][0] and torch.equal(out[0][k][1], out[1][k][1])
+    assert out[0][2][2] == out[1][2][2]
+    assert out[0][3][0] < out[1][3][0]
