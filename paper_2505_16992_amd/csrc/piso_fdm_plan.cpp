@@ -4,7 +4,6 @@
 #include <cmath>
 #include <cstdlib>
 #include <numeric>
-#include <system_error>
 #include <thread>
 
 namespace piso {
@@ -391,7 +390,7 @@ void fdm_plan(const piso_domain_desc* d, const Topology& topo, FdmPlan* plan) {
       }
       try {
         pool.emplace_back(planes, beg, end);
-      } catch (const std::system_error&) {
+      } catch (...) {   // std::system_error, or std::bad_alloc for the thread itself
         planes(beg, end);
       }
     }
@@ -471,7 +470,7 @@ void fdm_plan(const piso_domain_desc* d, const Topology& topo, FdmPlan* plan) {
     }
     try {
       pool.emplace_back(build, std::ref(b));
-    } catch (const std::system_error&) {
+    } catch (...) {
       build(b);
     }
   }
