@@ -161,18 +161,9 @@ def time_extras(ctx, case, precision, u0, S):
     return out
 
 
-def fast_diagonalisation(ctx, dom):
-    """Whether the pressure PCG of these workloads (tensor-product boxes and the O-H cylinder,
-    whose operators it accepts) runs with the fast diagonalisation: the size rules of the
-    library, and no multigrid form asked for by name."""
-    if os.environ.get("PISO_MG_LINE") or os.environ.get("PISO_ZMARCH"):
-        return False
-    return max(max(b) for b in dom.blocks) <= 512 and (ctx.dim == 2 or ctx.N >= 1 << 14)
-
-
 def pcg_roofline(ctx, dom, opts, tm, workload, precision):
     """(roofline, pressure_cg) records from per-class kernel times tm = {class: (ms,
-    launches)}: algorithmic bytes per launch of each fine-grid kernel class (each stream
+    launches)} of solves preconditioned as the context's last one: algorithmic bytes per launch of each fine-grid kernel class (each stream
     moved once) over its average duration; the roofline names the class with the
     largest total time."""
     N, d, es = ctx.N, ctx.dim, ctx.elem_bytes
@@ -195,7 +186,7 @@ def pcg_roofline(ctx, dom, opts, tm, workload, precision):
         # y, r, Dinv, Pf (d), level-1 correction -> z
         "mg_up0": ("k_mg_up0_q" if quad else "k_mg_up0", N * (d + 4) * es + (N // nch) * es),
     }
-    fdm = mg and fast_diagonalisation(ctx, dom)
+    fdm = ctx.pressure_preconditioner == "fast diagonalisation"
     if fdm:
         line = zm = False
         model["cg_update_restrict"] = ("k_fdm_row_update", N * 7 * es)   # x, r, d_new, q -> x, r', hat
@@ -236,9 +227,15 @@ def pcg_roofline(ctx, dom, opts, tm, workload, precision):
             "traffic": counter_traffic(kname, workload, precision),
             "avg_launch_us": round(avg * 1e3, 3), "bytes_per_launch": kbytes,
             "launches": tm[dom_k][1]}
-    iters = tm["cg_stencil"][1]
-    it_ms = sum(ms for ms, _ in tm.values()) / max(iters, 1)
-    it_bytes = sum(model[k][1] * tm[k][1] for k in fine) / max(iters, 1)
+    iters = max(tm["cg_stencil"][1], 1)
+    # kernels of the preconditioner also run once at the start of a solve: with the fast
+    # diagonalisation, whose solves take a few iterations, an iteration is charged one
+    # application (its last product runs once in each), not a share of the first
+    applied = max(tm["mg_up0"][1], 1) if fdm else iters
+    per_it = {k: iters if not fdm or k in ("cg_stencil", "cg_update_restrict") else applied
+              for k in tm if not (fdm and k == "mg_down0")}
+    it_ms = sum(tm[k][0] / n for k, n in per_it.items())
+    it_bytes = sum(model[k][1] * tm[k][1] / per_it[k] for k in fine if k in per_it)
     pcg = {"preconditioner": "fast diagonalisation" if fdm else ("multigrid" if mg else "jacobi"),
            "fine_smoother": None if fdm else (("lines along %s" % "xyz"[ctx.mg_line_axis])
                                               if mg and ctx.mg_line_axis else "point"),
@@ -264,14 +261,17 @@ def pcg_micro(ctx, case, precision, workload, iters, precond):
     ctx.assemble(sys_, u0, p0, nu, S, ub, case.dt)
     us = u0.clone()
     ctx.solve_velocity(sys_, us, opts.vel)
-    if precond == 1 and bool(ctx.mg_levels) and fast_diagonalisation(ctx, case.domain):
-        iters = min(iters, 6)   # a few digits each: the residual is exhausted soon after
     fixed = type(opts.pres)()
     fixed.rtol, fixed.max_iter, fixed.check_every, fixed.precond = 1e-30, iters, iters, precond
     fixed.inner_rtol, fixed.max_refine = 1e-30, 0
     p = torch.zeros_like(p0)
+    ctx.solve_pressure(sys_, us, ub, p0, p, opts.pres)
+    if ctx.pressure_preconditioner == "fast diagonalisation":
+        # a few digits each: the residual is exhausted soon after
+        fixed.max_iter = fixed.check_every = min(iters, 6)
+    p.zero_()
     out = {"mode": "pcg_micro", "workload": workload, "cells": ctx.N, "precision": precision,
-           "preconditioner": "multigrid" if precond == 1 else "jacobi"}
+           "preconditioner": ctx.pressure_preconditioner}
     if precision != "mixed":
         ctx.solve_pressure(sys_, us, ub, p0, p, fixed)     # warm-up (graph recording, setup)
         torch.cuda.synchronize()

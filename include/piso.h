@@ -292,6 +292,11 @@ int piso_mg_smoother(const piso_ctx* ctx, int32_t* line_axis);
  * the one-quad-per-thread kernels, PISO_ZMARCH=1 takes the marching ones at every size. */
 int piso_mg_marching(const piso_ctx* ctx, int32_t* groups);
 
+/* What preconditioned the context's last pressure solve (App. A.6): *kind = 0 Jacobi, 1 the
+ * multigrid V-cycle, 2 the fast diagonalisation that takes its place where grid and operator
+ * allow (see PISO_PRECOND_MG), -1 before the first solve. */
+int piso_pressure_preconditioner(const piso_ctx* ctx, int32_t* kind);
+
 /* Default options for a precision: vel rtol 1e-7 (F32) / 1e-10 (F64, MIXED), Jacobi with
  * the ILU(0) restart on failure (PISO_PRECOND_JACOBI_ILU0);
  * pres rtol 1e-10 (F64), 1e-6 (F32), 1e-8 (MIXED), multigrid-preconditioned; MIXED inner

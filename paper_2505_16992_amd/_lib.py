@@ -123,6 +123,7 @@ _SIGS = {
     "piso_set_timing": (I32, [VP, I32]),
     "piso_adjoint_reset": (I32, [VP]),
     "piso_mg_smoother": (I32, [VP, C.POINTER(I32)]),
+    "piso_pressure_preconditioner": (I32, [VP, C.POINTER(I32)]),
     "piso_get_timing": (I32, [VP, I32, C.POINTER(F64), C.POINTER(C.c_int64)]),
 }
 

@@ -106,6 +106,14 @@ class Context:
         self._check(self.lib.piso_mg_marching(self.h, C.byref(zg)), "piso_mg_marching")
         self.mg_marching_groups = int(zg.value)   # > 0: the plane-marching fine-grid kernels run
 
+    @property
+    def pressure_preconditioner(self):
+        """What preconditioned the last pressure solve: "jacobi", "multigrid" or "fast
+        diagonalisation" (None before the first)."""
+        k = C.c_int32(-1)
+        self._check(self.lib.piso_pressure_preconditioner(self.h, C.byref(k)), "piso_pressure_preconditioner")
+        return None if k.value < 0 else ("jacobi", "multigrid", "fast diagonalisation")[k.value]
+
     def __del__(self):
         h = getattr(self, "h", None)
         try:

@@ -580,6 +580,12 @@ int piso_mg_marching(const piso_ctx* c, int32_t* groups) {
   return PISO_OK;
 }
 
+int piso_pressure_preconditioner(const piso_ctx* c, int32_t* kind) {
+  if (!c || !kind) return PISO_E_ARG;
+  *kind = c->pcg_last;
+  return PISO_OK;
+}
+
 int piso_mg_smoother(const piso_ctx* c, int32_t* line_axis) {
   if (!c || !line_axis) return PISO_E_ARG;
   *line_axis = c->mg_line_axis;

@@ -267,6 +267,7 @@ struct piso_ctx {
   int pcg_op_pre = 0;             // preconditioners set up for it: bits 1 << PcgPre
   bool pcg_op_reject = false;     // ... and the fast diagonalisation turned it down
   bool pcg_op_copied = false;     // P_f and D^-1 are in g_Pf and g_Dinv
+  int pcg_last = -1;              // PcgPre of the last solve
   std::vector<piso::MgLevel> mg;  // coarse levels 1..L of the pressure preconditioner
   piso::Grid mg_g1{};             // level 1 as a block table (offsets, dims, division magic)
   piso::MgTiles mg_tiles{};       // work-group tiles of the fine-grid restriction
@@ -533,7 +534,8 @@ int zm_launch_up(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const R
 // ---- fast-diagonalisation preconditioner (piso_fdm.hip) ----
 // Preconditioners of the pressure PCG as it runs them.
 enum PcgPre { kPreJacobi = 0, kPreMg = 1, kPreFdm = 2 };
-// Builds the plan of a single tensor-product block (sets c->fdm.on); needs mg_build.
+// Builds the plan of blocks that form a box near a tensor product (sets c->fdm.on); needs
+// mg_build.
 int fdm_build(piso_ctx* c, const piso_domain_desc* desc, const Topology& topo);
 // Chooses the rung for the operator Pf on the device, or marks it as rejected.  wait: leaves the
 // verdict in c->h_cg->status, too (0 or kFdmRejected).

@@ -1318,6 +1318,7 @@ static int pcg_run(piso_ctx* c, hipStream_t s, const R* Pf, const R* Dinv, const
   const CgState& h = *c->h_cg;
   if (h.status == kFdmRejected) return rejected();   // not an iteration was run
   if (small && gauged) *gauged = true;
+  c->pcg_last = pre;
   *iters_out += h.iters;
   *rel_out = h.bb > 0 ? std::sqrt(h.rr / h.bb) : 0.0;
   // whichever way it ended (limit of iterations, breakdown), a residual within the caller's

@@ -235,6 +235,7 @@ def test_rejected_operators(dims, periodic, prec, monkeypatch):
             info = ctx.solve_pressure(sys, ud, ubd, pd, x, o)
             count = {n: t[1] for n, t in ctx.get_timing().items()}
             ctx.set_timing(False)
+            assert ctx.pressure_preconditioner == ("fast diagonalisation" if k == 3 and not env else "multigrid")
             res.append((info["iters"], x, count))
         out.append(res)
     say(dims, prec, [[r[0] for r in res] for res in out], [res[2][2] for res in out])
@@ -242,3 +243,24 @@ def test_rejected_operators(dims, periodic, prec, monkeypatch):
         assert out[0][k][0] == out[1][k][0] and torch.equal(out[0][k][1], out[1][k][1])
     assert out[0][2][2] == out[1][2][2]
     assert out[0][3][0] < out[1][3][0]
+
+
+def test_preconditioner_of_the_last_solve(monkeypatch):
+    """What the context reports of its last pressure solve, by grid, option and request."""
+    api = _api()
+    fdm, mg = "fast diagonalisation", "multigrid"
+    for dims, periodic, env, precond, want in [((24, 20), (), None, 1, fdm), ((24, 20), (), "auto", 1, mg),
+                                               ((24, 20), (), None, 0, "jacobi"), ((70, 64), (0,), None, 1, fdm),
+                                               ((513, 8), (0,), None, 1, mg), ((512, 8), (0,), None, 1, fdm),
+                                               ((32, 32, 15), (0, 2), None, 1, mg), ((32, 32, 16), (0, 2), None, 1, fdm)]:
+        case = _case(dims, periodic)
+        if env:
+            monkeypatch.setenv("PISO_MG_LINE", env)
+        ctx = api.Context(case.domain, "f32")
+        monkeypatch.delenv("PISO_MG_LINE", raising=False)
+        assert ctx.pressure_preconditioner is None
+        u, p, S, ub, nu = [dev(x, ctx.dtype) for x in random_state(case, seed=10)]
+        o = ctx.default_opts()
+        o.pres.precond = precond
+        ctx.step(u, p, nu, S, ub, case.dt, o)
+        assert ctx.pressure_preconditioner == want, (dims, env, precond)
