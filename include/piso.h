@@ -124,13 +124,14 @@ typedef enum {
                                multigrid for the pressure as the way to a faster solver
                                (Sec. 6, App. A.6); the converged solution is the same.
                                Where the blocks together form one box of cells (walls or
-                               periodic sides, axes of at most 512 cells) with a metric
-                               near a tensor product, the pressure
+                               periodic sides, axes of at most 512 cells, in 3D at least
+                               16,384 cells) with a metric near a tensor product, the pressure
                                operator is close to one that 1D eigenbases diagonalise, and
                                that exact inverse takes the V-cycle's place for every
                                operator close enough to it (judged per solve, on the device;
                                PISO_MG_LINE or PISO_ZMARCH set at piso_create keep the
-                               V-cycle). */
+                               V-cycle).  Solves with it aim at 0.2 rtol; one that ends
+                               above that but within rtol is PISO_OK like any other. */
   PISO_PRECOND_ILU0 = 2,    /* velocity BiCGStab only: ILU(0) of C in red-black order (App. A.6
                                names ILU for BiCGStab).  Cells of one colour couple only to the
                                other colour, so the factors need no fill-in except on the
@@ -247,7 +248,9 @@ typedef struct {
  *
  * Environment read at creation (all optional; for measurement and comparison):
  *   PISO_MG_LINE=0     point Jacobi on the fine multigrid level; =1 lines wherever the
- *                      grid allows them (see piso_mg_smoother)
+ *                      grid allows them (see piso_mg_smoother); any other value: the
+ *                      library's choice between them.  Each keeps the V-cycle where the fast
+ *                      diagonalisation would take its place, as does PISO_ZMARCH
  *   PISO_MG_GRAPH=1    table-driven coarse-level kernels on single-block grids too
  *   PISO_NO_QUAD=1     no vectorised (four cells per thread) kernels
  *   PISO_NO_GRAPH=1    launch the PCG iterations one by one instead of replaying a graph
