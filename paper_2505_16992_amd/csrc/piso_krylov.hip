@@ -1030,7 +1030,9 @@ int wait_pinned(piso_ctx* c, hipStream_t s, const unsigned long long* seq, const
     if (__atomic_load_n(seq, __ATOMIC_ACQUIRE) == n) return PISO_OK;
     __builtin_ia32_pause();
     if (spin % 16384) continue;
-    if (hipStreamQuery(s) == hipErrorNotReady) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;   // captured kernels never answer
+    (void)hipStreamIsCapturing(s, &cap);
+    if (cap == hipStreamCaptureStatusNone && hipStreamQuery(s) == hipErrorNotReady) {
       (void)hipGetLastError();
       continue;
     }

@@ -264,3 +264,25 @@ def test_preconditioner_of_the_last_solve(monkeypatch):
         o.pres.precond = precond
         ctx.step(u, p, nu, S, ub, case.dt, o)
         assert ctx.pressure_preconditioner == want, (dims, env, precond)
+
+
+@pytest.mark.parametrize("name", ["tgv", "channel", "box"])
+def test_a_step_under_capture_is_refused(name):
+    """A step reads its solves' states back, so it cannot be captured: the call says so (and does
+    not wait for kernels that will not run), and the context goes on outside."""
+    api = _api()
+    case = {"tgv": lambda: cases.taylor_green(16), "channel": lambda: cases.channel(24, 24, 32),
+            "box": lambda: _case((64, 60), ())}[name]()
+    ctx = api.Context(case.domain, "f64")
+    u, p, S, ub, nu = [dev(x, ctx.dtype) for x in random_state(case, seed=11)]
+    u1, p1 = ctx.step(u, p, nu, S, ub, case.dt)
+    torch.cuda.synchronize()
+    s, g = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    with torch.cuda.stream(s):
+        g.capture_begin()
+        with pytest.raises(RuntimeError):
+            ctx.step(u, p, nu, S, ub, case.dt)
+        with pytest.raises(RuntimeError):
+            g.capture_end()
+    u2, p2 = ctx.step(u, p, nu, S, ub, case.dt)
+    assert torch.equal(u1, u2) and torch.equal(p1, p2)
