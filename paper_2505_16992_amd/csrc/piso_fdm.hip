@@ -832,7 +832,6 @@ k_fdm_select(const float* __restrict__ st, int planes, int splits, int rungs, in
     }
   if (threadIdx.x == 0) {
     sel->q = best;
-    sel->kappa = top;
     sel->bad = top <= limit ? 0 : 1;
     if (host) {   // pinned
       host->status = top <= limit ? 0 : kFdmRejected;

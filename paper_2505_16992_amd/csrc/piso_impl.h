@@ -149,7 +149,8 @@ constexpr double kMgOmegaCoarse = 0.9;  // damping of the Jacobi sweeps on the c
 // do not: one solve with a viscosity random over a factor of 1 / 8 / 16 / 32 / 64 at
 // nu dt / h^2 >> 1 takes 0.91 / 1.74 / 2.21 / 2.79 / 3.46 ms against 2.47 - 2.71 ms (256^2
 // F64), 0.54 / 1.01 / 1.26 / 1.59 / 2.01 against 1.42 - 1.58 (256^2 F32) and 1.10 / 1.84 /
-// 2.24 / 2.99 / 3.54 against 4.30 - 4.10 (96^3 MIXED).
+// 2.24 / 2.99 / 3.54 against 4.30 - 4.10 (96^3 MIXED).  So the line lies where the two cross in
+// 2D; in 3D, where that series does not reach a crossing, the same line is on the safe side.
 constexpr float kFdmMaxSpread = 24.f;
 // 3D blocks below this many cells keep the V-cycle.  Not for speed: with the fast
 // diagonalisation a step of the developed 32 x 24 x 16 channel takes 2 + 2 iterations whether
@@ -157,7 +158,8 @@ constexpr float kFdmMaxSpread = 24.f;
 // saving of those starts, which callers (and the tests, on that grid) read off the iteration
 // counts, is lost in the rounding to whole iterations; with the V-cycle it shows (F64 14 + 12
 // against 12 + 10, MIXED 12 + 9 against 9 + 5).  The price, measured: 1.34 against 0.50 ms
-// for that step in F64, 0.80 against 0.43 in F32.
+// for that step in F64, 0.80 against 0.43 in F32; adjoint solves and divergence-free gradients
+// of such blocks, whose starts nobody compares, pay it too.
 constexpr int kFdmMinCells3 = 1 << 14;
 
 // Grids whose solves run whole in one work-group (piso_small.hip): as many cells as its
@@ -178,7 +180,6 @@ constexpr int kMgPinGroups = 64;    // coarse-level launches up to this many wor
 // weights of the rungs and the choice among them, in the Krylov precision.
 struct FdmSel {
   int q, bad;       // rung; 1: no rung is close enough
-  double kappa;     // spread of the face-weight ratios
   double mean;      // mean of the residual last transformed
 };
 struct FdmState {
