@@ -32,6 +32,17 @@ struct CgState {
   unsigned long long seq;   // pinned copy: number of the wait that this state answers
 };
 
+// What the host reads of a solve's state, to its pinned copy.
+__device__ __forceinline__ void answer(CgState* host, const CgState& st, unsigned long long seq) {
+  host->rr = st.rr;
+  host->bb = st.bb;
+  host->done = st.done;
+  host->iters = st.iters;
+  host->status = st.status;
+  host->zero_rhs = st.zero_rhs;
+  publish(&host->seq, seq);
+}
+
 struct BiState {
   double rho[2][3], alpha[2][3], omega[2][3];
   double rr[3], bb[3], tol2, pad0;

@@ -96,12 +96,7 @@ k_cg_check(const double* __restrict__ partB, int G, int first, int max_k, double
       st->done = 1;
     }
   }
-  if (host) {
-    CgState o = *st;
-    o.seq = seq - 1;
-    *host = o;
-    publish(&host->seq, seq);
-  }
+  if (host) answer(host, *st, seq);
 }
 
 template <typename R, int D, bool ZOP = false>
